@@ -3,8 +3,9 @@
 One step = one cgd_coarse_grain call over the dense particle bed: PCM
 deposition of 20M particles into a 256 x 256 x 512 hex mesh (box 1 x 1 x 2,
 h = 1/256), then 4 backward-Euler pseudo-steps of T = b^2/4 with b = 4h,
-each a conjugate-gradient solve (preconditioned by a Chebyshev polynomial of
-the operator) to rtol 1e-6.  Inputs are resident in HBM before timing.
+each an implicit finite-volume Laplacian solve at rtol 1e-6 (all steps at once
+by the library's direct solve in the grid's cosine modes).  Inputs are
+resident in HBM before timing.
 value = fields coarse-grained per second.
 
 Prints one JSON line.  Also reports:
@@ -84,21 +85,24 @@ def traffic_from_profiles():
 
 # Timed kernels (cgd_timing_read kinds) that are one kernel each; "deposit"
 # spans several and is split into its stages.
-SOLVE_KERNELS = ("cg_sweep1", "cg_sweep2", "cg_precond_pass1", "cg_precond_pass_mid", "cg_precond_pass_last",
+DIRECT = "direct_transform_passes"
+SOLVE_KERNELS = (DIRECT, "cg_sweep1", "cg_sweep2", "cg_precond_pass1", "cg_precond_pass_mid", "cg_precond_pass_last",
                  "cg_first_sweep1", "cg_first_sweep2", "cg_first_precond_pass1", "cg_first_precond_pass_mid",
                  "cg_first_precond_pass_last")
 DEPOSIT_KERNELS = ("deposit_bin", "deposit_scatter", "deposit_accum")
 
 
-def roofline_of(tim, ms_per_field):
+def roofline_of(tim, ms_per_field, solve):
     """Every timed kernel ranked by its total time on the last timed step;
     the dominant one (most total time) gives the roofline line: its
     algorithmic bytes per launch over its mean launch time, against 8 TB/s.
-    Also the whole solve's and the whole call's algorithmic bytes over their
-    time."""
+    solve: the direct solve's (passes, ms of all of them, bytes per pass),
+    timed as cgd.diffuse calls of their own; its five transform passes count
+    as launches of one kernel.  Also the whole solve's and the whole call's
+    algorithmic bytes over their time."""
     rows = []
     for k in SOLVE_KERNELS + DEPOSIT_KERNELS:
-        n, ms, bpl = tim[k]
+        n, ms, bpl = solve if k == DIRECT and solve else tim.get(k, (0, 0.0, 0.0))
         if n:
             rows.append((k, n, ms, bpl))
     rows.sort(key=lambda r: -r[2])
@@ -223,8 +227,8 @@ def bench_batched(args):
     torch.cuda.synchronize()
     dt_loop = time.perf_counter() - t
     it_total = int(iters.sum())
-    # preconditioned CG: 8 (z = M r) + 12 (direction) + 20 (update) bytes per cell and iteration
-    alg_bytes = 40.0 * mesh.cells * it_total
+    # direct solve: five transform passes of 8 bytes per cell
+    alg_bytes = 40.0 * mesh.cells * n_rhs
     rel = None
     if not args.no_check:
         from oracle import cgd_oracle as O
@@ -244,9 +248,9 @@ def bench_batched(args):
             "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
             "config": {"workload": f"batched {args.snapshots} snapshots x {F} fields, 128^3 hex, "
                                    f"{int(off[-1])} particles, b=4h, 4 backward-Euler steps, "
-                                   f"polynomial-preconditioned CG rtol {args.rtol:g}",
-                       "right_hand_sides": n_rhs, "cg_iters_total": it_total,
-                       "cg_iters_per_rhs_step_mean": round(it_total / (n_rhs * steps), 2),
+                                   f"direct solve in the grid's cosine modes, rtol {args.rtol:g}",
+                       "right_hand_sides": n_rhs, "cg_iters_total_with_stats": it_total,
+                       "cg_iters_per_rhs_step_mean_with_stats": round(it_total / (n_rhs * steps), 2),
                        "autotune_choice": chosen, "autotune_ms": [round(x, 3) for x in tune_ms]},
             "looped_single_calls": {"value": round(n_rhs / dt_loop, 2), "unit": "fields/s",
                                     "ms": round(dt_loop * 1e3, 2)},
@@ -500,10 +504,9 @@ def main():
         "config": {"workload": f"dense bed {shape[0]}x{shape[1]}x{shape[2]} hex, box 1x1x2, "
                                f"{args.particles} particles, F={args.fields}, b=4h, 4 "
                                f"{'backward-Euler' if args.scheme == 'be' else 'Crank-Nicolson'} "
-                               f"steps, CG preconditioned by a Chebyshev polynomial of A (degree 4, 8 or 12 by predicted "
-                               f"cost{'; 12 at dtau/h^2 = 1' if args.scheme == 'be' else ''}), rtol {args.rtol:g}",
+                               f"steps, direct solve in the grid's cosine modes, rtol {args.rtol:g}",
                    "particles": args.particles, "cells": int(mesh.cells), "fields": args.fields,
-                   "cg_iters_per_step": r["iters"]},
+                   "cg_iters_per_step_with_stats": r["iters"]},
         "rel_l2": r["rel_l2"],
         "deposit_bit_exact": r["deposit_bit_exact"],
         "roofline": r["roofline"],
@@ -551,7 +554,24 @@ def run_dense(args, w, mesh, pos, vals, scheme, steps, warmup, check=True):
     value = F * steps / dt
     print(f"[bench] {w.name} {scheme}: {ms_per_field:.2f} ms per field, {value:.2f} fields/s",
           file=sys.stderr, flush=True)
-    res = {"value": value, "ms_per_field": ms_per_field, "iters": iters, "roofline": roofline_of(tim, ms_per_field),
+    solve = None
+    if not any(tim[k][0] for k in SOLVE_KERNELS if k != DIRECT):
+        # no CG kernel ran in the timed step: the direct solve, timed on its own
+        # on the deposited fields (five passes of 8 bytes per cell)
+        dep = cgd.deposit(mesh, pos, vals)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        total = 0.0
+        for i in range(4):
+            work = dep.clone()
+            ev[0].record()
+            cgd.diffuse(mesh, work, w.bandwidth, w.n_steps, rtol=args.rtol, scheme=scheme)
+            ev[1].record()
+            torch.cuda.synchronize()
+            total += ev[0].elapsed_time(ev[1]) if i else 0.0
+        solve = (5, total / 3, 8.0 * F * mesh.cells)
+        del dep, work
+    res = {"value": value, "ms_per_field": ms_per_field, "iters": iters,
+           "roofline": roofline_of(tim, ms_per_field, solve),
            "rel_l2": None, "deposit_bit_exact": None}
     if check:
         from oracle import cgd_oracle as O
@@ -631,8 +651,7 @@ def secondary(args, w, mesh, pos, vals):
         r = run_dense(args, ww, mw, pw, vw, "be", 5, 1, check=True)
         mw.close()
         return {"workload": "the dense bed turned so that its long axis is x: 512 x 256 x 256 hex in a 2 x 1 x 1 "
-                            "box (h = 1/256), 20M particles, 4 backward-Euler steps (rows of 512 cells: solved with "
-                            "x and y exchanged)", "unit": "fields/s", "value": round(r["value"], 2),
+                            "box (h = 1/256), 20M particles, 4 backward-Euler steps", "unit": "fields/s", "value": round(r["value"], 2),
                 "ms_per_field": round(r["ms_per_field"], 3), "cg_iters_per_step": r["iters"],
                 "rel_l2": r["rel_l2"], "deposit_bit_exact": r["deposit_bit_exact"],
                 "roofline_dominant": {k: r["roofline"][k] for k in ("kernel", "avg_us", "frac")},

@@ -279,7 +279,17 @@ cgd_status cgd_deposit_noalloc(cgd_mesh m, int64_t n, const float* pos, int32_t 
  *  o:         solver options, nullable (defaults)
  *  st:        host, nullable: iteration counts, residuals, mass before/after
  *
- * The convergence test is read back one chunk of iterations late, so the
+ * With st == NULL a uniform hex grid is solved directly where that is the
+ * faster way: the operator is diagonal in the axes' cosine modes, so all
+ * n_steps are one multiplication between a forward and an inverse transform
+ * (float64 arithmetic on float32 vectors; within 1e-7 of the exact solution
+ * in relative L2, closer than the CG at its default tolerance).  Statistics,
+ * x0_mode != 0, precond = 1, rtol < 5e-7, axes of more than 512 cells other
+ * than 1024, one or two steps on long axes that are no power of two, and a
+ * max_iter below the CG's own bound are solved by CG, as is a field whose
+ * modes overflow float32 or are not finite (then with the CG's status).
+ *
+ * The convergence test of the CG is read back one chunk of iterations late, so the
  * device always has queued work: the first chunk of a step runs to the
  * iteration at which the previous solve on this mesh stopped, the next holds
  * one iteration, later ones o->check_every iterations (all of them
@@ -293,7 +303,8 @@ cgd_status cgd_diffuse(cgd_mesh m, int32_t F, float* field, double bandwidth,
 
 /* cgd_deposit followed by cgd_diffuse (Section 2.6): the whole method.
  * field: device float32 [F, cells], written.
- * From a zero guess (x0_mode 0), a call with the arguments of the
+ * The diffusion is that of cgd_diffuse, directly or by CG.
+ * By CG, from a zero guess (x0_mode 0), a call with the arguments of the
  * previous one on the mesh (grid, F, bandwidth, n_steps, max_iter, rtol,
  * precond, scheme) enqueues each step's iterations of that call, plus one
  * until two such calls in a row have taken the same counts (twice as many
@@ -341,7 +352,9 @@ cgd_status cgd_velocity_from_momentum(int64_t cells, int32_t n_comp, const float
  * The whole call (offset upload, deposit, solve, statistics read-back) is
  * captured in a hipGraph for a given argument set and replayed afterwards
  * (the per-launch candidate first runs once with read-backs to learn its
- * budgets).
+ * budgets).  With st == NULL the direct solve of cgd_diffuse takes the place
+ * of all this under the same conditions: nothing is tuned or captured, and
+ * every snapshot's fields are the bits of its own cgd_coarse_grain.
  *
  *  n_snap:  1.. ; n_snap * F <= 4096
  *  offsets: HOST int64 [n_snap + 1]; snapshot j owns particles

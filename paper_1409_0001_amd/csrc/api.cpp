@@ -8,6 +8,7 @@
 #include <string>
 
 #include "cg_common.h"
+#include "spectral.h"
 #include "tet_data.h"
 
 namespace cgd {
@@ -125,15 +126,15 @@ struct DeviceGuard {
 // of the direct path (when the caller passes none).  The diffusion that
 // follows in cgd_coarse_grain reuses that memory only after the deposit's
 // last kernel has read it, in stream order.
+// reserve: what the call's diffusion will ask for (0: none follows).
 static cgd_status deposit_buffers(cgd_mesh m, int64_t n, int32_t F, int64_t* user_acc, int64_t** acc,
-                                  DepositInfo** info, void** temp) {
+                                  DepositInfo** info, void** temp, size_t reserve) {
     const size_t tiled = m->kind != 1 ? deposit_hex_temp_bytes(m, n, F) : 0;
     size_t acc_bytes = (user_acc || tiled) ? 0 : ((size_t)F * m->cells * sizeof(int64_t) + 255) & ~(size_t)255;
     // tet meshes: the particles' spatial ordering after the accumulators
     const size_t order = m->kind == 1 ? deposit_tet_temp_bytes(m, n) : 0;
     size_t need = kSmallFixed + acc_bytes + tiled + order;
-    size_t diff = m->kind == 0 ? diffuse_hex_workspace(m, F) : diffuse_tet_workspace(m, F);
-    cgd_status rc = ensure_workspace(m, need > diff ? need : diff);
+    cgd_status rc = ensure_workspace(m, need > reserve ? need : reserve);
     if (rc != CGD_OK) return rc;
     char* base = static_cast<char*>(m->ws.ptr);
     *info = reinterpret_cast<DepositInfo*>(base + kOffDeposit);
@@ -229,6 +230,7 @@ void cgd_mesh_destroy(cgd_mesh m) {
     for (int i = 0; i < 2; ++i)
         if (m->ev[i]) (void)hipEventDestroy(m->ev[i]);
     destroy_batched(m);
+    destroy_spectral(m);
     for (hipEvent_t e : m->timing.pool) (void)hipEventDestroy(e);
     for (hipEvent_t e : m->timing.used) (void)hipEventDestroy(e);
     destroy_tet_data(m);
@@ -284,11 +286,16 @@ static cgd_status check_common(cgd_mesh m, int32_t F, const char* who) {
     return CGD_OK;
 }
 
+static size_t cg_workspace(cgd_mesh m, int32_t F) {
+    return m->kind == 0 ? diffuse_hex_workspace(m, F) : diffuse_tet_workspace(m, F);
+}
+
 // frac_bits: host [F] or NULL; in: -1 (automatic) or a forced scale 0..62
 // (validated by the caller), out: the scale used.  The call waits for the
 // stream when st is given or some scale was automatic.
 static cgd_status do_deposit(cgd_mesh m, int64_t n, const float* pos, int32_t F, const float* values,
-                             float* field, int64_t* acc, int32_t* frac_bits, cgd_solve_stats* st, hipStream_t s) {
+                             float* field, int64_t* acc, int32_t* frac_bits, cgd_solve_stats* st, hipStream_t s,
+                             size_t reserve) {
     int64_t* acc_buf;
     DepositInfo* info;
     void* temp;
@@ -296,7 +303,7 @@ static cgd_status do_deposit(cgd_mesh m, int64_t n, const float* pos, int32_t F,
     bool need_auto = false;
     for (int f = 0; f < CGD_MAX_FIELDS; ++f) fs.s[f] = (frac_bits && f < F) ? frac_bits[f] : -1;
     for (int f = 0; f < F; ++f) need_auto = need_auto || fs.s[f] < 0;
-    cgd_status rc = deposit_buffers(m, n, F, acc, &acc_buf, &info, &temp);
+    cgd_status rc = deposit_buffers(m, n, F, acc, &acc_buf, &info, &temp, reserve);
     if (rc != CGD_OK) return rc;
     if (m->kind == 0)
         rc = deposit_hex(m, n, pos, F, values, field, acc_buf, info, temp, fs, &m->timing, s);
@@ -381,7 +388,8 @@ cgd_status cgd_deposit(cgd_mesh m, int64_t n, const float* pos, int32_t F, const
         return CGD_E_HIP;
     }
     if (st) memset(st, 0, sizeof(*st));
-    return do_deposit(m, n, pos, F, values, field, acc, frac_bits, st, static_cast<hipStream_t>(stream));
+    return do_deposit(m, n, pos, F, values, field, acc, frac_bits, st, static_cast<hipStream_t>(stream),
+                      cg_workspace(m, F));
 }
 
 static cgd_status fill_opts(const cgd_solver_opts* o, int32_t F, float* field, double bandwidth,
@@ -432,6 +440,7 @@ static cgd_status do_diffuse(cgd_mesh m, const DiffuseArgs& a, cgd_solve_stats* 
         set_error("x0_mode 3: the network must be created for this hex mesh's grid, on its device");
         return CGD_E_INVALID;
     }
+    if (spectral_applies(m, a, a.F, st != nullptr)) return diffuse_spectral(m, a, s);
     if (m->kind == 0) return diffuse_hex(m, a, st, s);
     return diffuse_tet(m, a, st, s);
 }
@@ -475,6 +484,10 @@ cgd_status cgd_coarse_grain(cgd_mesh m, int64_t n, const float* pos, int32_t F, 
     }
     if (st) memset(st, 0, sizeof(*st));
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (spectral_applies(m, a, a.F, st != nullptr)) {
+        rc = do_deposit(m, n, pos, F, values, field, nullptr, nullptr, nullptr, s, kSmallFixed + spectral_bytes(m, F));
+        return rc < 0 ? rc : diffuse_spectral(m, a, s);
+    }
     // Every mesh kind, from a zero guess: a call with the parameters of the
     // previous one on this mesh enqueues, per step, the iterations that call
     // took plus a margin of one, with no read-back between steps (launches
@@ -496,7 +509,7 @@ cgd_status cgd_coarse_grain(cgd_mesh m, int64_t n, const float* pos, int32_t F, 
     int bud[CGD_MAX_STEPS];
     for (int i = 0; i < a.n_steps; ++i) bud[i] = have ? std::max(1, hb.iters[i] + margin) : 0;
     for (int round = have ? 0 : 1; round < 2; ++round) {
-        rc = do_deposit(m, n, pos, F, values, field, nullptr, nullptr, st, s);
+        rc = do_deposit(m, n, pos, F, values, field, nullptr, nullptr, st, s, cg_workspace(m, F));
         cgd_status dep_rc = rc;
         if (rc < 0 && rc != CGD_E_NONFINITE) return rc;
         if (round == 0) {

@@ -27,6 +27,7 @@
 #include <vector>
 
 #include "cg_common.h"
+#include "spectral.h"
 #include "hex_bin.h"
 #include "precond_lds.h"
 #include "stencil_tile.h"
@@ -770,13 +771,15 @@ cgd_status autotune_batched(cgd_mesh m, int n_rhs, int* chosen, double* ms_out, 
 
 cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offsets, const float* pos, int32_t F,
                                 const float* values, const DiffuseArgs& da, float* fields, cgd_solve_stats* st_out,
-                                hipStream_t s) {
+                                hipStream_t s, bool cg_only) {
     const HexGeom& g = m->hex;
     const int n_rhs = n_snap * F;
     const int64_t total = offsets[n_snap];
     const size_t cells = (size_t)m->cells;
+    // a forced candidate (CGD_BATCHED_CFG) is one of the CG solvers below
+    const bool direct = !cg_only && spectral_applies(m, da, n_rhs, st_out != nullptr) && !getenv("CGD_BATCHED_CFG");
     int ci = 0;
-    cgd_status rc = autotune_batched(m, n_rhs, &ci, nullptr, nullptr);
+    cgd_status rc = direct ? CGD_OK : autotune_batched(m, n_rhs, &ci, nullptr, nullptr);
     if (rc != CGD_OK) return rc;
     const int vec = batched_vec(g);
     const std::vector<Cfg> cands = vec ? candidates(vec) : std::vector<Cfg>();
@@ -787,7 +790,7 @@ cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offse
     }
     const bool per_launch = ci == c_launch;
     Cfg c = {};
-    if (!per_launch) {
+    if (!per_launch && !direct) {
         c = cands[ci];
         if (da.precond != 0 && c.deg >= 4) {
             // plain CG: the degree-2 configuration of the same shape (else the
@@ -802,15 +805,16 @@ cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offse
             c = cands[ci];
         }
     }
-    const int grid = per_launch ? 0 : grid_for(c, n_rhs);
+    const int grid = per_launch || direct ? 0 : grid_for(c, n_rhs);
     const BLayout L = batched_layout(n_rhs, n_snap, da.n_steps);
     const size_t small = L.small;
     // deposit: the tiled path's bucketed records, else int64 accumulators
     const size_t tile_bytes = tiled_deposit_temp_bytes((int64_t)cells, total, n_snap, F);
     const bool tiled = tile_bytes > 0;
     const size_t dep_bytes = tiled ? tile_bytes : (size_t)n_rhs * cells * 8;
-    const size_t solver_bytes = per_launch ? diffuse_hex_workspace(m, std::min(kGroup, n_rhs))
-                                           : (size_t)grid * 5 * cells * 4;
+    const size_t solver_bytes = direct       ? spectral_bytes(m, n_rhs)
+                                : per_launch ? diffuse_hex_workspace(m, std::min(kGroup, n_rhs))
+                                             : (size_t)grid * 5 * cells * 4;
     rc = ensure_workspace(m, small + std::max(dep_bytes, solver_bytes));
     if (rc != CGD_OK) return rc;
     // the same arrays in pinned host memory, after the region the other calls use
@@ -888,7 +892,7 @@ cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offse
         fill_prod12(a);
     }
     a.xsegs = 1;
-    a.ygroups = per_launch ? 1 : (g.ny + c.ty - 1) / c.ty;
+    a.ygroups = per_launch || direct ? 1 : (g.ny + c.ty - 1) / c.ty;
     a.n_steps = da.n_steps;
     a.rtol2 = da.rtol * da.rtol;
     a.max_iter = da.max_iter;
@@ -896,9 +900,7 @@ cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offse
     a.relres = d_relres;
     a.status = d_status;
 
-    // everything the call does, in stream order; budget: the per-launch
-    // solver's iterations per step (nullptr: host read-backs, not capturable)
-    auto enqueue_all = [&](hipStream_t q, const int* budget) -> cgd_status {
+    auto enqueue_deposit = [&](hipStream_t q) -> cgd_status {
         CGD_HIP_TRY(hipMemcpyAsync(d_off, h_off, 8 * ((size_t)n_snap + 1), hipMemcpyHostToDevice, q));
         hipLaunchKernelGGL(k_bdep_init, dim3((std::max(n_rhs, 2 * n_snap) + 255) / 256), dim3(256), 0, q, d);
         if (tiled) {
@@ -930,8 +932,38 @@ cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offse
             }
             hipLaunchKernelGGL(k_bfinalize, dim3(512, n_rhs), dim3(kDBlock), 0, q, d);
         }
+        return CGD_OK;
+    };
+    if (direct) {
+        // The direct solve needs no iteration counts, so nothing is learned,
+        // tuned or captured: five launches per group of right-hand sides.
+        // Per right-hand side the status array holds whether a mode was not
+        // finite; then the whole call goes round again by CG, which says
+        // what it makes of such values.
+        rc = enqueue_deposit(s);
+        if (rc != CGD_OK) return rc;
+        rc = spectral_enqueue(m, da, n_rhs, static_cast<float*>(big), d_status, nullptr, s);
+        if (rc != CGD_OK) return rc;
+        CGD_HIP_TRY(hipMemcpyAsync(pin + P.status, base + L.status, L.maxbits - L.status, hipMemcpyDeviceToHost, s));
+        CGD_HIP_TRY(hipStreamSynchronize(s));
+        for (int r = 0; r < n_rhs; ++r)
+            if (h_status[r])
+                return coarse_grain_batched(m, n_snap, offsets, pos, F, values, da, fields, st_out, s, true);
+        for (int j = 0; j < n_snap; ++j)
+            if (h_counters[2 * j + 1]) {
+                set_error("non-finite particle positions or values were skipped");
+                return CGD_E_NONFINITE;
+            }
+        return CGD_OK;
+    }
+
+    // everything the call does, in stream order; budget: the per-launch
+    // solver's iterations per step (nullptr: host read-backs, not capturable)
+    auto enqueue_all = [&](hipStream_t q, const int* budget) -> cgd_status {
+        cgd_status r = enqueue_deposit(q);
+        if (r != CGD_OK) return r;
         if (want_mass) hipLaunchKernelGGL(k_bmass, dim3(n_rhs), dim3(1024), 0, q, fields, a.cells, g.vol, d_mass);
-        cgd_status r = per_launch ? solve_grouped(m, fields, n_rhs, da, static_cast<char*>(big), budget, d_iters,
+        r = per_launch ? solve_grouped(m, fields, n_rhs, da, static_cast<char*>(big), budget, d_iters,
                                                   d_relres, d_status, q)
                                   : launch_solver(c, a, grid, q);
         if (r != CGD_OK) return r;

@@ -76,6 +76,7 @@ struct IterBudget {
 
 struct TetData;  // defined in tet.cpp
 struct RectOp;   // below
+struct SpecTables;  // spectral.h
 
 // Event-pair timing of selected kernels (cgd_timing_enable).
 struct Timing {
@@ -115,6 +116,7 @@ struct cgd_mesh_s {
     int64_t cells;
     cgd::HexGeom hex;
     cgd::TetData* tet = nullptr;
+    cgd::SpecTables* spec = nullptr;  // transform tables of the direct solve (made on its first use)
     cgd::RectOp* rop = nullptr;    // rectilinear grids with a separable diffusivity: the sweeps' operator
     cgd::Workspace ws;
     void* pinned = nullptr;        // small pinned host buffer for read-backs
@@ -300,7 +302,7 @@ bool unet_matches(cgd_unet u, int nx, int ny, int nz, int device);
 // batched.hip
 cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offsets, const float* pos, int32_t F,
                                 const float* values, const DiffuseArgs& da, float* fields, cgd_solve_stats* st_out,
-                                hipStream_t s);
+                                hipStream_t s, bool cg_only = false);
 cgd_status autotune_batched(cgd_mesh m, int n_rhs, int* chosen, double* ms_out, int* n_cand);
 void destroy_batched(cgd_mesh m);
 

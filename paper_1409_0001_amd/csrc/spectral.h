@@ -1,0 +1,73 @@
+// Direct solve of the implicit steps on uniform hex grids (spectral.hip).
+#pragma once
+
+#include "cgd_internal.h"
+
+namespace cgd {
+
+// Tables of one axis, by its length (device pointers; see k_spec_tables).
+struct SpecAxis {
+    int n = 0;
+    double* lam = nullptr;   // eigenvalues 4 sin^2(pi k / 2n) at the stored positions [n]
+    double2* tw = nullptr;   // FFT lengths: e^{-2 pi i q / n} [n]
+    double2* pw = nullptr;   //    and e^{-i pi k / 2n} [n / 2]
+    double* fe = nullptr;    // dense lengths: packed half-size matrices, forward even and odd modes,
+    double* fo = nullptr;
+    double* ie = nullptr;    //    inverse even and odd modes
+    double* io = nullptr;
+};
+
+// Owned by a mesh, made on its first direct solve.
+struct SpecTables {
+    double* dev = nullptr;
+    SpecAxis axis[3];  // the axes of more than one cell, the contiguous one first
+};
+
+// One pass of transforms along one axis of all fields.
+struct SpecPass {
+    const float* in;
+    float* out;
+    int64_t cells;        // per field
+    int32_t n;            // length of a line
+    int64_t lines;        // lines per field
+    int64_t pairs;        // FFT: pairs of lines per field
+    int64_t inner;        // strided lines: neighbouring lines (at unit stride),
+    int64_t inner_pairs;  //    their pairs, the stride between points of a line
+    int64_t estride;      //    and between groups of neighbouring lines
+    int64_t ostride;
+    int32_t vec2;         // both lines of a pair (contiguous lines: two points) in one aligned 8-byte access
+    int32_t first, last;  // first: clears *bad; last: writes nothing where *bad is set
+    const double2* tw;
+    const double2* pw;
+    const double* fe;
+    const double* fo;
+    const double* ie;
+    const double* io;
+    double sf, sf0, si, si0;  // FFT: scale of a mode (mode 0) forward and inverse
+    // the gain pass: mu = c0 lam0[line % n0] + c1 lam1[line / n0] + cm lamm[mode]
+    double cm, c0, c1;
+    const double* lamm;
+    const double* lam0;
+    const double* lam1;
+    int64_t n0;
+    int32_t n_steps, cn;
+    int* bad;       // device, per field: set when a mode is not finite
+    int* bad_host;  // nullable: the same in pinned host memory
+};
+
+// Whether a call on n_fields fields is answered by the direct solve (stats:
+// its statistics are asked for).
+bool spectral_applies(const cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stats);
+// Bytes of the scratch vector W for F fields.
+size_t spectral_bytes(const cgd_mesh m, int32_t F);
+// Enqueues all steps of `da` on n_fields fields at da.field [n_fields][cells]
+// (da.F is not used), with W as scratch.  Where a field has a mode that is
+// not finite, its entries of bad and bad_host (nullable, cleared by the
+// caller) are set and the field is left as it was.
+cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, float* W, int* bad, int* bad_host,
+                            hipStream_t s);
+// The diffusion of cgd_diffuse by the direct solve; waits for the stream.
+cgd_status diffuse_spectral(cgd_mesh m, const DiffuseArgs& da, hipStream_t s);
+void destroy_spectral(cgd_mesh m);
+
+}  // namespace cgd

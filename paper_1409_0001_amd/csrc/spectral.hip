@@ -1,0 +1,1019 @@
+// Direct solve of the implicit steps on uniform hex grids.
+//
+// The zero-flux finite-volume Laplacian of a uniform box is diagonal in the
+// products of the axes' cosine modes (DCT-II): with c_a = dtau / h_a^2 the
+// step matrix A = I + sum_a c_a L_a has the eigenvalues
+// 1 + sum_a 4 c_a sin^2(pi k_a / 2 N_a).  All n steps of a call are then one
+// multiplication of the modes by gain(k) = 1 / A(k)^n (backward Euler) or
+// (2 / A(k) - 1)^n with half dtau in c_a (Crank-Nicolson), between a forward
+// and an inverse transform.
+//
+// Passes over memory (three axes): x forward, y forward, z forward + gain +
+// z inverse in one kernel, y inverse, x inverse; 8 bytes per cell each, the
+// four inner ones in place on one workspace vector.  Arithmetic is float64 in
+// registers and LDS throughout (gfx950 issues float64 and unpacked float32
+// multiply-adds at the same rate), and only the vectors between passes are
+// float32: what an iterate of the CG holds, rounded four times instead of
+// twice per iteration.
+//
+// A transform of length 128, 256, 512 or 1024 runs as a complex FFT of two
+// lines at once (k_fft); any other length up to 512 as two half-size matrix
+// products on the float64 matrix cores, the even modes from x[m] + x[N-1-m]
+// and the odd ones from x[m] - x[N-1-m] (k_dense).
+#include <math.h>
+
+#include <stdlib.h>
+
+#include <algorithm>
+#include <new>
+
+#include "cg_common.h"
+#include "spectral.h"
+
+namespace cgd {
+
+namespace {
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+struct Cd {
+    double x, y;
+};
+__device__ __forceinline__ Cd cadd(Cd a, Cd b) { return {a.x + b.x, a.y + b.y}; }
+__device__ __forceinline__ Cd csub(Cd a, Cd b) { return {a.x - b.x, a.y - b.y}; }
+__device__ __forceinline__ Cd cmul(Cd a, Cd b) { return {a.x * b.x - a.y * b.y, fma(a.x, b.y, a.y * b.x)}; }
+__device__ __forceinline__ Cd cmulj(Cd a) { return {a.y, -a.x}; }  // -i a
+
+// Forward DFTs (kernel e^{-2 pi i n k / R}) in registers.
+__device__ __forceinline__ void dft4(Cd& a, Cd& b, Cd& c, Cd& d) {
+    const Cd s0 = cadd(a, c), s1 = csub(a, c), s2 = cadd(b, d), s3 = cmulj(csub(b, d));
+    a = cadd(s0, s2);
+    c = csub(s0, s2);
+    b = cadd(s1, s3);
+    d = csub(s1, s3);
+}
+
+template <int R>
+__device__ __forceinline__ void dft(Cd* v);
+
+template <>
+__device__ __forceinline__ void dft<8>(Cd* v) {
+    constexpr double kH = 0.70710678118654752440;
+    dft4(v[0], v[2], v[4], v[6]);
+    dft4(v[1], v[3], v[5], v[7]);
+    // odd branch times e^{-2 pi i k / 8}; slots hold k = 0..3 at 1, 3, 5, 7
+    const Cd o0 = v[1], o1 = {(v[3].x + v[3].y) * kH, (v[3].y - v[3].x) * kH}, o2 = cmulj(v[5]),
+             o3 = {(v[7].y - v[7].x) * kH, -(v[7].x + v[7].y) * kH};
+    const Cd e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6];
+    v[0] = cadd(e0, o0);
+    v[4] = csub(e0, o0);
+    v[1] = cadd(e1, o1);
+    v[5] = csub(e1, o1);
+    v[2] = cadd(e2, o2);
+    v[6] = csub(e2, o2);
+    v[3] = cadd(e3, o3);
+    v[7] = csub(e3, o3);
+}
+
+template <>
+__device__ __forceinline__ void dft<16>(Cd* v) {
+    // 4 x 4: X[k1 + 4 k2] = sum_n2 e^{-2 pi i n2 k1 / 16} (sum_n1 x[4 n1 + n2] (-i)^{n1 k1}) (-i)^{n2 k2}
+    constexpr double c1 = 0.92387953251128675613, s1 = 0.38268343236508977173, kH = 0.70710678118654752440;
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) dft4(v[n2], v[4 + n2], v[8 + n2], v[12 + n2]);
+    // v[4 k1 + n2] *= w16^{n2 k1}
+    const Cd w1 = {c1, -s1}, w3 = {s1, -c1}, w9 = {-c1, s1};
+    v[5] = cmul(v[5], w1);
+    v[6] = {(v[6].x + v[6].y) * kH, (v[6].y - v[6].x) * kH};
+    v[7] = cmul(v[7], w3);
+    v[9] = {(v[9].x + v[9].y) * kH, (v[9].y - v[9].x) * kH};
+    v[10] = cmulj(v[10]);
+    v[11] = {(v[11].y - v[11].x) * kH, -(v[11].x + v[11].y) * kH};
+    v[13] = cmul(v[13], w3);
+    v[14] = {(v[14].y - v[14].x) * kH, -(v[14].x + v[14].y) * kH};
+    v[15] = cmul(v[15], w9);
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1) dft4(v[4 * k1], v[4 * k1 + 1], v[4 * k1 + 2], v[4 * k1 + 3]);
+    // slot 4 k1 + k2 holds X[k1 + 4 k2]
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = a + 1; b < 4; ++b) {
+            const Cd t = v[4 * a + b];
+            v[4 * a + b] = v[4 * b + a];
+            v[4 * b + a] = t;
+        }
+}
+
+// The gain of a mode whose eigenvalue of A is 1 + mu.
+__device__ __forceinline__ double mode_gain(double mu, int n, int cn) {
+    const double d = 1.0 + mu;
+    double r = __builtin_amdgcn_rcp(d);  // 4.6e-8 off at most (measured over 1 .. 1e6)
+    r = fma(r, fma(-d, r, 1.0), r);      // 2.1e-15
+    double base = cn ? fma(2.0, r, -1.0) : r;
+    double g = 1.0;
+    for (int e = n;; base *= base) {
+        if (e & 1) g *= base;
+        e >>= 1;
+        if (!e) break;
+    }
+    return g;
+}
+
+// A field with a mode that is not finite: the last pass leaves it alone, and
+// the host solves it by CG.
+__device__ __forceinline__ void mark_bad(const SpecPass& a) {
+    __hip_atomic_store(a.bad + blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (a.bad_host) a.bad_host[blockIdx.y] = 1;
+}
+__device__ __forceinline__ void clear_bad(const SpecPass& a) {
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(a.bad + blockIdx.y, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool is_bad(const SpecPass& a) {
+    return __hip_atomic_load(a.bad + blockIdx.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
+// ------------------------------------------------------------------- FFT
+
+template <int N>
+struct FftCfg;
+template <>
+struct FftCfg<128> {
+    static constexpr int R1 = 16, R2 = 8, R3 = 1, P = 32;
+};
+template <>
+struct FftCfg<256> {
+    static constexpr int R1 = 16, R2 = 16, R3 = 1, P = 16;
+};
+template <>
+struct FftCfg<512> {
+    static constexpr int R1 = 8, R2 = 8, R3 = 8, P = 16;
+};
+template <>
+struct FftCfg<1024> {
+    static constexpr int R1 = 16, R2 = 8, R3 = 8, P = 16;
+};
+
+constexpr int kE = 16;  // points of a line held by a thread
+
+// LDS slot of point m of pair p.  Strided lines: the P pairs of a point side
+// by side (a wave's 16 consecutive pairs read 128 bytes).  Contiguous lines:
+// a pair's points side by side, one slot of padding in 16, so that lanes at a
+// stride of 8 or 16 points fall in distinct banks.
+template <int N, int P, bool XK>
+__device__ __forceinline__ int slot(int m, int p) {
+    return XK ? p * (N + N / 16) + m + (m >> 4) : m * P + p;
+}
+template <int N, bool XK>
+constexpr int fft_lds_doubles() {
+    return FftCfg<N>::P * (XK ? N + N / 16 : N);
+}
+
+// One Stockham stage of radix R over what the threads hold (slot j of a
+// thread: point t + T j), L the product of the earlier radices: twiddles and
+// butterflies; the outputs' places are out_place below.
+template <int N, int R, int L>
+__device__ __forceinline__ void stage(Cd* v, int t, const double2* __restrict__ tw) {
+    constexpr int T = N / kE, B = kE / R;
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+        Cd u[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) u[r] = v[i + r * B];
+        if (L > 1) {
+            const double2 q = tw[((t + T * i) % L) * (N / (L * R))];
+            const Cd w = {q.x, q.y};
+            Cd c = w;
+#pragma unroll
+            for (int r = 1; r < R; ++r) {
+                u[r] = cmul(u[r], c);
+                if (r + 1 < R) c = cmul(c, w);
+            }
+        }
+        dft<R>(u);
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[i + r * B] = u[r];
+    }
+}
+
+template <int N, int R, int L>
+__device__ __forceinline__ int out_place(int t, int j) {
+    constexpr int T = N / kE, B = kE / R;
+    const int b = t + T * (j % B), r = j / B;
+    return (b / L) * (L * R) + (b % L) + r * L;
+}
+
+// Moves the outputs of a stage to the next one's inputs through LDS, real
+// and imaginary parts one after the other (half the LDS, so twice the blocks
+// per compute unit).
+template <int N, int P, bool XK, int R, int L>
+__device__ __forceinline__ void exchange(Cd* v, double* sh, int t, int p) {
+    constexpr int T = N / kE;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kE; ++j) sh[slot<N, P, XK>(out_place<N, R, L>(t, j), p)] = v[j].x;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kE; ++j) v[j].x = sh[slot<N, P, XK>(t + T * j, p)];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kE; ++j) sh[slot<N, P, XK>(out_place<N, R, L>(t, j), p)] = v[j].y;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kE; ++j) v[j].y = sh[slot<N, P, XK>(t + T * j, p)];
+}
+
+// The complex DFT of a line pair; in and out: slot j holds point t + T j.
+// The value again, as one the compiler does not know: index arithmetic on it
+// is done anew instead of being kept in registers over a whole transform (16
+// offsets of 64 bits cost the 32 registers that the points then spill).
+__device__ __forceinline__ int again(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+template <int N, int P, bool XK>
+__device__ __forceinline__ void fft_line(Cd* v, double* sh, int t, int p, const double2* __restrict__ tw) {
+    constexpr int R1 = FftCfg<N>::R1, R2 = FftCfg<N>::R2, R3 = FftCfg<N>::R3;
+    stage<N, R1, 1>(v, t, tw);
+    exchange<N, P, XK, R1, 1>(v, sh, t, p);
+    stage<N, R2, R1>(v, t, tw);
+    if constexpr (R3 > 1) {
+        exchange<N, P, XK, R2, R1>(v, sh, t, p);
+        stage<N, R3, R1 * R2>(v, t, tw);
+    }
+}
+
+// Between the natural order (slot j: point t + T j) and the pairs (k, N - k)
+// of k = t + T i, i < 8 (slot i: point k, slot 8 + i: point N - k; k = 0 pairs
+// with N / 2): only the upper half of the points changes hands, its real and
+// imaginary parts side by side in LDS.
+template <int N, int P, bool XK>
+__device__ __forceinline__ void to_pairs(Cd* v, double* sh, int t, int p) {
+    constexpr int T = N / kE, H = kE / 2;
+    __syncthreads();
+#pragma unroll
+    for (int j = H; j < kE; ++j) {
+        sh[slot<N, P, XK>(t + T * (j - H), p)] = v[j].x;
+        sh[slot<N, P, XK>(t + T * j, p)] = v[j].y;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const int k = t + T * i, n = k ? N - k : N / 2;
+        v[H + i] = {sh[slot<N, P, XK>(n - N / 2, p)], sh[slot<N, P, XK>(n, p)]};
+    }
+}
+
+template <int N, int P, bool XK>
+__device__ __forceinline__ void from_pairs(Cd* v, double* sh, int t, int p) {
+    constexpr int T = N / kE, H = kE / 2;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const int k = t + T * i, n = k ? N - k : N / 2;
+        sh[slot<N, P, XK>(n - N / 2, p)] = v[H + i].x;
+        sh[slot<N, P, XK>(n, p)] = v[H + i].y;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = H; j < kE; ++j)
+        v[j] = {sh[slot<N, P, XK>(t + T * (j - H), p)], sh[slot<N, P, XK>(t + T * j, p)]};
+}
+
+// Modes of both lines from the pair (k, N - k) of the packed transform:
+// m = {Xa[k], Xa[N-k], Xb[k], Xb[N-k]} (k = 0: modes 0 and N / 2), times s
+// (mode 0: s0); w = e^{-i pi k / 2N}.
+__device__ __forceinline__ v4d modes_of(Cd zk, Cd zn, Cd w, bool k0, double s, double s0) {
+    if (k0) {
+        constexpr double kH = 0.70710678118654752440;
+        return v4d{zk.x * s0, zn.x * (kH * s), zk.y * s0, zn.y * (kH * s)};
+    }
+    const double hs = 0.5 * s;
+    const Cd a = {hs * (zk.x + zn.x), hs * (zk.y - zn.y)}, b = {hs * (zk.y + zn.y), hs * (zn.x - zk.x)};
+    const Cd ua = cmul(w, a), ub = cmul(w, b);
+    return v4d{ua.x, -ua.y, ub.x, -ub.y};
+}
+// The reverse (s, s0: the inverse's factors).
+__device__ __forceinline__ void pair_of(v4d m, Cd w, bool k0, double s, double s0, Cd* zk, Cd* zn) {
+    if (k0) {
+        constexpr double kR = 1.41421356237309504880;
+        *zk = {m.x * s0, m.z * s0};
+        *zn = {m.y * (kR * s), m.w * (kR * s)};
+        return;
+    }
+    const Cd cw = {w.x * s, -w.y * s};
+    const Cd a = cmul(cw, Cd{m.x, -m.y}), b = cmul(cw, Cd{m.z, -m.w});
+    *zk = {a.x - b.y, a.y + b.x};
+    *zn = {a.x + b.y, b.x - a.y};
+}
+
+// MODE 0 forward, 1 inverse, 2 forward + gain + inverse.  XK: lines
+// contiguous in memory (two rows per pair), else strided (two neighbouring
+// lines per pair, P pairs per block).
+template <int N, int MODE, bool XK>
+__global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
+    constexpr int T = N / kE, P = FftCfg<N>::P, H = kE / 2;
+    __shared__ double sh[fft_lds_doubles<N, XK>()];
+    if (MODE == 1 && a.last && is_bad(a)) return;
+    if (MODE == 0 && a.first) clear_bad(a);
+    int t = XK ? threadIdx.x % T : threadIdx.x / P;
+    const int p = XK ? threadIdx.x / T : threadIdx.x % P;
+    const int64_t q = (int64_t)blockIdx.x * P + p;
+    const bool live = q < a.pairs;
+    const float* __restrict__ in = a.in + (size_t)blockIdx.y * a.cells;
+    float* __restrict__ out = a.out + (size_t)blockIdx.y * a.cells;
+    const double2* __restrict__ tw = a.tw;
+    const double2* __restrict__ pw = a.pw;
+    const double sf = a.sf, sf0 = a.sf0, si = a.si, si0 = a.si0;
+    Cd v[kE];
+    bool two;
+    int64_t base, base2, line;
+    if (XK) {
+        line = 2 * q;
+        two = live && line + 1 < a.lines;
+        base = (live ? line : 0) * N;
+        base2 = two ? base + N : base;
+    } else {
+        const int64_t qq = live ? q : 0;
+        const int64_t o = qq / a.inner_pairs;
+        const int64_t i = (qq - o * a.inner_pairs) * 2;
+        line = o * a.inner + i;
+        two = live && i + 1 < a.inner;
+        base = o * a.ostride + i;
+        base2 = two ? base + 1 : base;
+    }
+    const int64_t es = a.estride;
+    if (MODE == 0 || MODE == 2) {
+        if (XK) {
+            // element 2m goes to point m, 2m + 1 to point N - 1 - m, which the
+            // mirror thread of the line holds
+            float2 xa[H], xb[H];
+            if (a.vec2) {
+#pragma unroll
+                for (int j = 0; j < H; ++j) {
+                    xa[j] = *reinterpret_cast<const float2*>(in + base + 2 * (t + T * j));
+                    xb[j] = *reinterpret_cast<const float2*>(in + base2 + 2 * (t + T * j));
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < H; ++j) {
+                    const int e = 2 * (t + T * j);
+                    xa[j] = make_float2(in[base + e], in[base + e + 1]);
+                    xb[j] = make_float2(in[base2 + e], in[base2 + e + 1]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < H; ++j) {
+                v[j] = {xa[j].x, two ? xb[j].x : 0.f};
+                const float ya = __shfl_xor(xa[j].y, T - 1), yb = __shfl_xor(xb[j].y, T - 1);
+                v[kE - 1 - j] = {ya, two ? yb : 0.f};
+            }
+        } else if (a.vec2) {
+            float2 x[kE];
+#pragma unroll
+            for (int j = 0; j < kE; ++j) {
+                const int m = t + T * j;
+                x[j] = *reinterpret_cast<const float2*>(in + base + es * (j < H ? 2 * m : 2 * N - 1 - 2 * m));
+            }
+#pragma unroll
+            for (int j = 0; j < kE; ++j) v[j] = {x[j].x, x[j].y};
+        } else {
+            float x[kE], y[kE];
+#pragma unroll
+            for (int j = 0; j < kE; ++j) {
+                const int m = t + T * j;
+                const int64_t o = es * (j < H ? 2 * m : 2 * N - 1 - 2 * m);
+                x[j] = in[base + o];
+                y[j] = in[base2 + o];
+            }
+#pragma unroll
+            for (int j = 0; j < kE; ++j) v[j] = {x[j], two ? y[j] : 0.f};
+        }
+        fft_line<N, P, XK>(v, sh, t, p, tw);
+        t = again(t);
+        to_pairs<N, P, XK>(v, sh, t, p);
+    }
+    t = again(t);
+    if (MODE == 0) {
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const int k = t + T * i;
+            const double2 c = pw[k];
+            const v4d m = modes_of(v[i], v[H + i], Cd{c.x, c.y}, k == 0, sf, sf0);
+            if (XK) {
+                if (live) *reinterpret_cast<float2*>(out + base + 2 * k) = make_float2((float)m.x, (float)m.y);
+                if (two) *reinterpret_cast<float2*>(out + base2 + 2 * k) = make_float2((float)m.z, (float)m.w);
+            } else if (a.vec2) {
+                if (live) {
+                    *reinterpret_cast<float2*>(out + base + es * (2 * k)) = make_float2((float)m.x, (float)m.z);
+                    *reinterpret_cast<float2*>(out + base + es * (2 * k + 1)) = make_float2((float)m.y, (float)m.w);
+                }
+            } else {
+                if (live) {
+                    out[base + es * (2 * k)] = (float)m.x;
+                    out[base + es * (2 * k + 1)] = (float)m.y;
+                }
+                if (two) {
+                    out[base2 + es * (2 * k)] = (float)m.z;
+                    out[base2 + es * (2 * k + 1)] = (float)m.w;
+                }
+            }
+        }
+        return;
+    }
+    if (MODE == 2) {
+        // the two lines' share of mu, from the modes they stand at on the
+        // other axes
+        const int64_t l1 = two ? line + 1 : line;
+        const int64_t y0 = line / a.n0, y1 = l1 / a.n0;
+        const double mua = a.c0 * a.lam0[line - y0 * a.n0] + (a.lam1 ? a.c1 * a.lam1[y0] : 0.0);
+        const double mub = a.c0 * a.lam0[l1 - y1 * a.n0] + (a.lam1 ? a.c1 * a.lam1[y1] : 0.0);
+        bool ok = true;
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const int k = t + T * i;
+            const double2 c = pw[k];
+            const Cd w = {c.x, c.y};
+            v4d m = modes_of(v[i], v[H + i], w, k == 0, 1.0, 1.0);
+            ok = ok && isfinite(m.x) && isfinite(m.y) && isfinite(m.z) && isfinite(m.w);
+            // 4 sin^2(pi k / 2N) and 4 cos^2 of the same for N - k (k = 0: modes 0 and N / 2)
+            const double lk = 4.0 * a.cm * c.y * c.y, ln = k ? 4.0 * a.cm * c.x * c.x : 2.0 * a.cm;
+            m.x *= mode_gain(mua + lk, a.n_steps, a.cn);
+            m.y *= mode_gain(mua + ln, a.n_steps, a.cn);
+            m.z *= mode_gain(mub + lk, a.n_steps, a.cn);
+            m.w *= mode_gain(mub + ln, a.n_steps, a.cn);
+            pair_of(m, w, k == 0, 1.0 / N, 1.0 / N, &v[i], &v[H + i]);
+        }
+        if (!ok && live) mark_bad(a);
+    } else {
+        float4 x[H];  // modes of line a (k, N - k), then of line b
+        if (XK) {
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                const float2 xa = *reinterpret_cast<const float2*>(in + base + 2 * (t + T * i));
+                const float2 xb = *reinterpret_cast<const float2*>(in + base2 + 2 * (t + T * i));
+                x[i] = make_float4(xa.x, xa.y, xb.x, xb.y);
+            }
+        } else if (a.vec2) {
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                const int64_t o = base + es * (2 * (t + T * i));
+                const float2 x0 = *reinterpret_cast<const float2*>(in + o);
+                const float2 x1 = *reinterpret_cast<const float2*>(in + o + es);
+                x[i] = make_float4(x0.x, x1.x, x0.y, x1.y);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                const int64_t o = es * (2 * (t + T * i));
+                x[i] = make_float4(in[base + o], in[base + o + es], in[base2 + o], in[base2 + o + es]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const int k = t + T * i;
+            const double2 c = pw[k];
+            const v4d m = {x[i].x, x[i].y, two ? x[i].z : 0.f, two ? x[i].w : 0.f};
+            pair_of(m, Cd{c.x, c.y}, k == 0, si, si0, &v[i], &v[H + i]);
+        }
+    }
+    t = again(t);
+    from_pairs<N, P, XK>(v, sh, t, p);
+    t = again(t);
+    // the inverse DFT by the forward one with real and imaginary parts swapped
+#pragma unroll
+    for (int j = 0; j < kE; ++j) v[j] = {v[j].y, v[j].x};
+    fft_line<N, P, XK>(v, sh, t, p, tw);
+    t = again(t);
+    if (XK) {
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+            const int e = 2 * (t + T * j);
+            const float2 xa = make_float2((float)v[j].y, __shfl_xor((float)v[kE - 1 - j].y, T - 1));
+            const float2 xb = make_float2((float)v[j].x, __shfl_xor((float)v[kE - 1 - j].x, T - 1));
+            if (a.vec2) {
+                if (live) *reinterpret_cast<float2*>(out + base + e) = xa;
+                if (two) *reinterpret_cast<float2*>(out + base2 + e) = xb;
+            } else {
+                if (live) {
+                    out[base + e] = xa.x;
+                    out[base + e + 1] = xa.y;
+                }
+                if (two) {
+                    out[base2 + e] = xb.x;
+                    out[base2 + e + 1] = xb.y;
+                }
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kE; ++j) {
+            const int m = t + T * j;
+            const int64_t o = es * (j < H ? 2 * m : 2 * N - 1 - 2 * m);
+            if (a.vec2) {
+                if (live) *reinterpret_cast<float2*>(out + base + o) = make_float2((float)v[j].y, (float)v[j].x);
+            } else {
+                if (live) out[base + o] = (float)v[j].y;
+                if (two) out[base2 + o] = (float)v[j].x;
+            }
+        }
+    }
+}
+
+// ----------------------------------------------------------- dense lengths
+
+constexpr int kTL = 32;  // lines per block
+
+// Row of D element r of v_mfma_f64_16x16x4f64 in a lane (column: lane % 16).
+__device__ __forceinline__ int d_row(int r, int lane) { return 4 * r + (lane >> 4); }
+
+// Even and odd halves in LDS, [m][line].  A wave forms one 16-row tile of
+// the half-size products for the block's 32 lines (SPLIT: for 16 of them):
+// its even and odd products of two column tiles are four independent
+// accumulator chains that share every matrix fragment read from L2 (512
+// bytes for 4 reduction rows).  A block has as many waves as tiles, so none
+// idles in the products, and at least four, for the latency of its loads.
+// Bound by the float64 matrix rate together with a block's load, product and
+// store phases one after the other: 66 us forward or back along n = 275 for
+// 7.5M cells (30 us at 78.6 TFLOP/s), 50 us along 147, 66 us for the gain
+// pass along 93; the CG it replaces took 2.1 ms for the same three steps.
+template <int MODE, bool XK, bool SPLIT>
+__global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
+    extern __shared__ double shd[];
+    constexpr int TLP = XK ? kTL + 1 : kTL;
+    constexpr int CT = SPLIT ? 1 : 2;
+    const int n = a.n, hm = (n + 1) / 2, ho = n / 2, mt = (hm + 15) / 16, rows = 16 * mt;
+    double* E = shd;
+    double* O = shd + (size_t)rows * TLP;
+    if (MODE == 1 && a.last && is_bad(a)) return;
+    if (MODE == 0 && a.first) clear_bad(a);
+    const float* __restrict__ in = a.in + (size_t)blockIdx.y * a.cells;
+    float* __restrict__ out = a.out + (size_t)blockIdx.y * a.cells;
+    const int64_t l0 = (int64_t)blockIdx.x * kTL;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int tile = SPLIT ? wave >> 1 : wave, c0 = SPLIT ? (wave & 1) * 16 : 0;
+    const bool work = tile < mt;  // (a block of few tiles has waves that only move data)
+    const int64_t es = a.estride;
+    auto base_of = [&](int64_t l) -> int64_t {
+        if (XK) return l * n;
+        const int64_t o = l / a.inner;
+        return o * a.ostride + (l - o * a.inner);
+    };
+    // E and O: x[m] +- x[N-1-m], or (inverse) the even and odd modes.  Loads
+    // at clamped places, four pairs in flight per thread.
+    auto fill = [&](const float* __restrict__ src, int64_t step, int m0, int dm, int line, bool ok) {
+        for (int m = m0; m < rows; m += 4 * dm) {
+            float u[4], w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int mc = std::min(m + i * dm, hm - 1);
+                u[i] = src[step * mc];
+                w[i] = src[step * (MODE == 1 ? std::min(hm + mc, n - 1) : n - 1 - mc)];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int mi = m + i * dm;
+                if (mi >= rows) break;
+                const double e = MODE == 1 || mi >= ho ? (double)u[i] : (double)u[i] + (double)w[i];
+                const double o = MODE == 1 ? (double)w[i] : (double)u[i] - (double)w[i];
+                E[mi * TLP + line] = ok && mi < hm ? e : 0.0;
+                O[mi * TLP + line] = ok && mi < ho ? o : 0.0;
+            }
+        }
+    };
+    if (XK) {
+        for (int line = wave; line < kTL; line += nw) {
+            const bool ok = l0 + line < a.lines;
+            fill(in + (ok ? base_of(l0 + line) : 0), 1, lane, 64, line, ok);
+        }
+    } else {
+        const int line = threadIdx.x % kTL;
+        const bool ok = l0 + line < a.lines;
+        fill(in + (ok ? base_of(l0 + line) : 0), es, threadIdx.x / kTL, 2 * nw, line, ok);
+    }
+    __syncthreads();
+    v4d ae[CT], ao[CT];
+    auto multiply = [&](const double* __restrict__ me, const double* __restrict__ mo) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) ae[c] = ao[c] = v4d{0, 0, 0, 0};
+        if (!work) return;
+        const double* fe = me + (size_t)tile * mt * 256 + lane;
+        const double* fo = mo + (size_t)tile * mt * 256 + lane;
+        const int at = (lane >> 4) * TLP + c0 + (lane & 15);
+        // 16 reduction rows at a time, the matrices' next fragments in flight
+        double ce[4], co[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ce[i] = fe[i * 64];
+            co[i] = fo[i * 64];
+        }
+        for (int k = 0; k < mt; ++k) {
+            double ne[4], no[4];
+            const size_t nk = (size_t)std::min(k + 1, mt - 1) * 256;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                ne[i] = fe[nk + i * 64];
+                no[i] = fo[nk + i * 64];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    const int o = (16 * k + 4 * i) * TLP + at + 16 * c;
+                    const double de = E[o], dd = O[o];
+                    if (XK) {
+                        ae[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(de, ce[i], ae[c], 0, 0, 0);
+                        ao[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(dd, co[i], ao[c], 0, 0, 0);
+                    } else {
+                        ae[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(ce[i], de, ae[c], 0, 0, 0);
+                        ao[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(co[i], dd, ao[c], 0, 0, 0);
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                ce[i] = ne[i];
+                co[i] = no[i];
+            }
+        }
+    };
+    if (MODE != 1) multiply(a.fe, a.fo);
+    if (MODE == 0) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = tile * 16 + (XK ? (lane & 15) : d_row(r, lane));
+                const int line = c0 + c * 16 + (XK ? d_row(r, lane) : (lane & 15));
+                if (l0 + line >= a.lines || k >= hm) continue;
+                float* dst = out + base_of(l0 + line);
+                dst[es * k] = (float)ae[c][r];
+                if (k < ho) dst[es * (hm + k)] = (float)ao[c][r];
+            }
+        }
+        return;
+    }
+    if (MODE == 2) {
+        __syncthreads();
+        bool ok = true;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int line = c0 + c * 16 + (lane & 15);
+            const int64_t l = std::min(l0 + line, a.lines - 1);
+            const int64_t y = l / a.n0;
+            const double mu = a.c0 * a.lam0[l - y * a.n0] + (a.lam1 ? a.c1 * a.lam1[y] : 0.0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = tile * 16 + d_row(r, lane);
+                double e = 0.0, o = 0.0;
+                if (k < hm) {
+                    ok = ok && isfinite(ae[c][r]);
+                    e = ae[c][r] * mode_gain(fma(a.cm, a.lamm[k], mu), a.n_steps, a.cn);
+                }
+                if (k < ho) {
+                    ok = ok && isfinite(ao[c][r]);
+                    o = ao[c][r] * mode_gain(fma(a.cm, a.lamm[hm + k], mu), a.n_steps, a.cn);
+                }
+                if (work) {
+                    E[k * TLP + line] = e;
+                    O[k * TLP + line] = o;
+                }
+            }
+        }
+        if (!ok) mark_bad(a);
+        __syncthreads();
+    }
+    multiply(a.ie, a.io);
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = tile * 16 + (XK ? (lane & 15) : d_row(r, lane));
+            const int line = c0 + c * 16 + (XK ? d_row(r, lane) : (lane & 15));
+            if (l0 + line >= a.lines || m >= hm) continue;
+            float* dst = out + base_of(l0 + line);
+            dst[es * m] = (float)(ae[c][r] + ao[c][r]);
+            if (m < ho) dst[es * (n - 1 - m)] = (float)(ae[c][r] - ao[c][r]);
+        }
+    }
+}
+
+// ------------------------------------------------------------------ tables
+
+// Per axis: the eigenvalues 4 sin^2(pi k / 2n) at the stored positions, then
+// for an FFT length e^{-2 pi i q / n} [n] and e^{-i pi k / 2n} [n / 2], for a
+// dense length the four packed half-size matrices (orthonormal scaling).
+__global__ __launch_bounds__(256) void k_spec_tables(int n, int fft, double* lam, double2* tw, double2* pw, double* fe,
+                                                    double* fo, double* ie, double* io) {
+    const int hm = (n + 1) / 2, ho = n / 2, mt = (hm + 15) / 16, ks = 4 * mt;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t p = t0; p < n; p += stride) {
+        int k;
+        if (fft) k = p == 0 ? 0 : (p == 1 ? n / 2 : ((p & 1) ? n - (int)p / 2 : (int)p / 2));
+        else k = p < hm ? 2 * (int)p : 2 * ((int)p - hm) + 1;
+        const double s = sinpi(0.5 * k / n);
+        lam[p] = 4.0 * s * s;
+    }
+    if (fft) {
+        for (int64_t q = t0; q < n; q += stride) {
+            double s, c;
+            sincospi(2.0 * (double)q / n, &s, &c);
+            tw[q] = make_double2(c, -s);
+            if (q < n / 2) {
+                sincospi(0.5 * (double)q / n, &s, &c);
+                pw[q] = make_double2(c, -s);
+            }
+        }
+        return;
+    }
+    const int64_t frag = (int64_t)mt * ks * 64;
+    for (int64_t i = t0; i < frag; i += stride) {
+        const int lane = (int)(i & 63);
+        const int64_t f = i >> 6;
+        const int row = (int)(f / ks) * 16 + (lane & 15), col = (int)(f % ks) * 4 + (lane >> 4);
+        // orthonormal DCT-II entry of mode k at point m
+        auto entry = [&](int k, int m) {
+            const int64_t ph = ((int64_t)k * (2 * m + 1)) % (4 * (int64_t)n);
+            return sqrt((k ? 2.0 : 1.0) / n) * cospi((double)ph / (2.0 * n));
+        };
+        fe[i] = row < hm && col < hm ? entry(2 * row, col) : 0.0;
+        fo[i] = row < ho && col < ho ? entry(2 * row + 1, col) : 0.0;
+        ie[i] = row < hm && col < hm ? entry(2 * col, row) : 0.0;
+        io[i] = row < ho && col < ho ? entry(2 * col + 1, row) : 0.0;
+    }
+}
+
+bool fft_length(int n) { return n == 128 || n == 256 || n == 512 || n == 1024; }
+
+// Doubles of one packed half-size matrix: tiles of 16 rows, 4 fragments of 64
+// per 16 reduction rows.
+size_t dense_fragment(int n) {
+    const size_t mt = ((n + 1) / 2 + 15) / 16;
+    return mt * 4 * mt * 64;
+}
+
+size_t table_doubles(int n) {
+    if (fft_length(n)) return (size_t)n + 2 * (size_t)n + (size_t)n;
+    return (((size_t)n + 1) & ~(size_t)1) + 4 * dense_fragment(n);
+}
+
+template <int N, int MODE, bool XK>
+void launch_fft(const SpecPass& a, int F, hipStream_t s) {
+    constexpr int P = FftCfg<N>::P;
+    const dim3 grid((unsigned)((a.pairs + P - 1) / P), F);
+    hipLaunchKernelGGL((k_fft<N, MODE, XK>), grid, dim3(P * N / kE), 0, s, a);
+}
+
+template <int MODE, bool XK>
+cgd_status launch_pass(const SpecPass& a, int F, hipStream_t s) {
+    switch (a.n) {
+        case 128: launch_fft<128, MODE, XK>(a, F, s); return CGD_OK;
+        case 256: launch_fft<256, MODE, XK>(a, F, s); return CGD_OK;
+        case 512: launch_fft<512, MODE, XK>(a, F, s); return CGD_OK;
+        case 1024: launch_fft<1024, MODE, XK>(a, F, s); return CGD_OK;
+        default: break;
+    }
+    const int mt = ((a.n + 1) / 2 + 15) / 16;
+    const size_t lds = (size_t)2 * mt * 16 * (XK ? kTL + 1 : kTL) * sizeof(double);
+    const dim3 grid((unsigned)((a.lines + kTL - 1) / kTL), F);
+    auto go = [&](auto kern, int nw) -> cgd_status {
+        if (lds > 64 * 1024)
+            CGD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(kern, grid, dim3(nw * 64), lds, s, a);
+        return CGD_OK;
+    };
+    // one or two tiles: a wave per tile and column tile, for the latency
+    if (mt <= 2) return go(k_dense<MODE, XK, true>, 4);
+    return go(k_dense<MODE, XK, false>, std::max(4, mt));
+}
+
+// The axes of more than one cell, contiguous one first.
+int axes_of(const HexGeom& g, int* n, double* h) {
+    const int32_t nn[3] = {g.nx, g.ny, g.nz};
+    int rank = 0;
+    for (int a = 0; a < 3; ++a)
+        if (nn[a] > 1) {
+            n[rank] = nn[a];
+            h[rank++] = g.h[a];
+        }
+    return rank;
+}
+
+}  // namespace
+
+// Fields per group: their vector W (with the field itself about 256 MB) stays
+// in the memory-side cache between the passes.
+static int fields_per_group(const cgd_mesh m, int F) {
+    const int64_t most = (int64_t)128 * 1024 * 1024 / (m->cells * (int64_t)sizeof(float));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(F, most));
+}
+
+size_t spectral_bytes(const cgd_mesh m, int32_t F) {
+    return (size_t)fields_per_group(m, F) * m->cells * sizeof(float);
+}
+
+// The direct solve stands in for the CG where nothing asks for the CG itself:
+// its iterations and residuals (statistics), a start from a guess, plain CG,
+// or a forced preconditioner degree; where the float32 result can meet the
+// stopping rule's meaning (rounding the result alone leaves a relative
+// residual of up to lmax 2^-25, 4e-7 at dtau / h^2 = 1, so tolerances below
+// the default stay with the CG's recursive residual); where the CG would
+// have converged within max_iter by its bound for the unpreconditioned
+// operator, so that a call that came back not converged still does; and
+// where it is the faster one: a transform takes about 2 ps per cell for an
+// FFT length and 2.5 + 0.022 n for a dense one (7.5M cells: 66 us at n = 275,
+// 50 at 147, 33 at 93), the CG 25 ps per cell and step at its best
+// (256 x 256 x 512, dtau / h^2 = 1) and 50 us and more per step in launches
+// on the smallest grids, so only one or two steps on lengths of hundreds that
+// are no FFT lengths are left to the CG.
+bool spectral_applies(const cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stats) {
+    if (m->kind != 0 || stats || da.x0_mode != 0 || da.precond != 0 || da.rtol < 5e-7) return false;
+    if (getenv("CGD_NO_DIRECT") || getenv("CGD_HEX_PRECOND_DEG")) return false;
+    int n[3];
+    double h[3];
+    const int rank = axes_of(m->hex, n, h);
+    if (rank < 2) return false;
+    const double dtau = da.bandwidth * da.bandwidth / 4.0 / da.n_steps * (da.scheme == 1 ? 0.5 : 1.0);
+    double k = 1.0, ps = 0.0;
+    for (int a = 0; a < rank; ++a) {
+        if (n[a] > 512 && !fft_length(n[a])) return false;
+        k += 4.0 * dtau / (h[a] * h[a]);
+        ps += 2.0 * (fft_length(n[a]) ? 2.0 : 2.5 + 0.022 * n[a]);
+    }
+    const double mcells = 1e-6 * (double)m->cells * n_fields;
+    if (25.0 + mcells * ps > da.n_steps * (50.0 + mcells * 25.0)) return false;
+    const double r = sqrt(k);
+    return 0.5 * r * log(2.0 * r / std::min(da.rtol, 1.0)) + 1.0 <= (double)da.max_iter;
+}
+
+void destroy_spectral(cgd_mesh m) {
+    if (!m->spec) return;
+    if (m->spec->dev) (void)hipFree(m->spec->dev);
+    delete m->spec;
+    m->spec = nullptr;
+}
+
+static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
+    if (m->spec) return CGD_OK;
+    int n[3];
+    double h[3];
+    const int rank = axes_of(m->hex, n, h);
+    size_t total = 0;
+    for (int a = 0; a < rank; ++a) total += table_doubles(n[a]);
+    SpecTables* t = new (std::nothrow) SpecTables();
+    if (!t) return CGD_E_NOMEM;
+    void* dev = nullptr;
+    if (hipMalloc(&dev, total * sizeof(double)) != hipSuccess) {
+        (void)hipGetLastError();
+        delete t;
+        set_error("allocation of the transform tables failed");
+        return CGD_E_NOMEM;
+    }
+    t->dev = static_cast<double*>(dev);
+    m->spec = t;
+    double* p = t->dev;
+    for (int a = 0; a < rank; ++a) {
+        for (int b = 0; b < a; ++b)
+            if (n[b] == n[a]) t->axis[a] = t->axis[b];
+        SpecAxis& x = t->axis[a];
+        if (x.n) continue;
+        x.n = n[a];
+        x.lam = p;
+        const bool fft = fft_length(n[a]);
+        if (fft) {
+            x.tw = reinterpret_cast<double2*>(p + n[a]);
+            x.pw = x.tw + n[a];
+        } else {
+            const size_t frag = dense_fragment(n[a]);
+            x.fe = p + ((n[a] + 1) & ~1);
+            x.fo = x.fe + frag;
+            x.ie = x.fo + frag;
+            x.io = x.ie + frag;
+        }
+        hipLaunchKernelGGL(k_spec_tables, dim3(64), dim3(256), 0, s, n[a], (int)fft, x.lam, x.tw, x.pw, x.fe, x.fo,
+                           x.ie, x.io);
+        p += table_doubles(n[a]);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        destroy_spectral(m);
+        set_error(std::string("transform tables: ") + hipGetErrorString(e));
+        return CGD_E_HIP;
+    }
+    return CGD_OK;
+}
+
+cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, float* W, int* bad, int* bad_host,
+                            hipStream_t s) {
+    cgd_status rc = spectral_tables(m, s);
+    if (rc != CGD_OK) return rc;
+    int n[3];
+    double h[3], c[3];
+    const int rank = axes_of(m->hex, n, h);
+    const double dtau = da.bandwidth * da.bandwidth / 4.0 / da.n_steps * (da.scheme == 1 ? 0.5 : 1.0);
+    for (int a = 0; a < rank; ++a) c[a] = dtau / (h[a] * h[a]);
+    SpecPass pass[3];
+    for (int ax = 0; ax < rank; ++ax) {
+        SpecPass& p = pass[ax];
+        p = SpecPass{};
+        const SpecAxis& t = m->spec->axis[ax];
+        const double nn = n[ax];
+        p.cells = m->cells;
+        p.n_steps = da.n_steps;
+        p.cn = da.scheme == 1;
+        p.n = n[ax];
+        p.tw = t.tw;
+        p.pw = t.pw;
+        p.fe = t.fe;
+        p.fo = t.fo;
+        p.ie = t.ie;
+        p.io = t.io;
+        p.sf = sqrt(2.0 / nn);
+        p.sf0 = sqrt(1.0 / nn);
+        p.si = sqrt(0.5 / nn);
+        p.si0 = sqrt(1.0 / nn);
+        p.lines = m->cells / n[ax];
+        int64_t st = 1;
+        for (int b = 0; b < ax; ++b) st *= n[b];
+        p.estride = st;
+        p.inner = st;
+        p.inner_pairs = (st + 1) / 2;
+        p.ostride = st * n[ax];
+        p.pairs = ax == 0 ? (p.lines + 1) / 2 : p.inner_pairs * (p.lines / st);
+        p.vec2 = ax > 0 && st % 2 == 0;
+        p.in = W;
+        p.out = W;
+    }
+    SpecPass& z = pass[rank - 1];
+    z.cm = c[rank - 1];
+    z.lamm = m->spec->axis[rank - 1].lam;
+    z.n0 = n[0];
+    z.c0 = c[0];
+    z.lam0 = m->spec->axis[0].lam;
+    if (rank == 3) {
+        z.c1 = c[1];
+        z.lam1 = m->spec->axis[1].lam;
+    }
+    const int group = fields_per_group(m, n_fields);
+    for (int f0 = 0; f0 < n_fields; f0 += group) {
+        const int nf = std::min(group, n_fields - f0);
+        float* field = da.field + (size_t)f0 * m->cells;
+        for (int ax = 0; ax < rank; ++ax) {
+            pass[ax].bad = bad + f0;
+            pass[ax].bad_host = bad_host ? bad_host + f0 : nullptr;
+        }
+        SpecPass x = pass[0];
+        x.in = field;
+        x.first = 1;
+        x.vec2 = reinterpret_cast<uintptr_t>(field) % 8 == 0;  // (FFT lengths are even, so every row is aligned)
+        rc = launch_pass<0, true>(x, nf, s);
+        if (rc == CGD_OK && rank == 3) rc = launch_pass<0, false>(pass[1], nf, s);
+        if (rc == CGD_OK) rc = launch_pass<2, false>(z, nf, s);
+        if (rc == CGD_OK && rank == 3) rc = launch_pass<1, false>(pass[1], nf, s);
+        if (rc != CGD_OK) return rc;
+        x.in = W;
+        x.out = field;
+        x.first = 0;
+        x.last = 1;
+        rc = launch_pass<1, true>(x, nf, s);
+        if (rc != CGD_OK) return rc;
+    }
+    CGD_HIP_TRY(hipGetLastError());
+    return CGD_OK;
+}
+
+cgd_status diffuse_spectral(cgd_mesh m, const DiffuseArgs& da, hipStream_t s) {
+    cgd_status rc = ensure_workspace(m, kSmallFixed + spectral_bytes(m, da.F));
+    if (rc != CGD_OK) return rc;
+    rc = ensure_pinned(m, kPinBytes);
+    if (rc != CGD_OK) return rc;
+    char* base = static_cast<char*>(m->ws.ptr);
+    int* bad_host = reinterpret_cast<int*>(static_cast<char*>(m->pinned) + kPinStatus);
+    for (int f = 0; f < da.F; ++f) bad_host[f] = 0;
+    rc = spectral_enqueue(m, da, da.F, reinterpret_cast<float*>(base + kSmallFixed),
+                          reinterpret_cast<int*>(base + kOffStatus), bad_host, s);
+    if (rc != CGD_OK) return rc;
+    CGD_HIP_TRY(hipStreamSynchronize(s));
+    timing_collect(&m->timing);
+    // fields the transforms cannot carry (their sums overflow float32, or a
+    // value is not finite) are as they were: each is solved by CG
+    int todo[CGD_MAX_FIELDS], n_todo = 0;
+    for (int f = 0; f < da.F; ++f)
+        if (bad_host[f]) todo[n_todo++] = f;
+    cgd_status worst = CGD_OK;
+    for (int i = 0; i < n_todo; ++i) {
+        DiffuseArgs d1 = da;
+        d1.F = 1;
+        d1.field = da.field + (size_t)todo[i] * m->cells;
+        rc = diffuse_hex(m, d1, nullptr, s);
+        if (rc < 0 && rc != CGD_E_BREAKDOWN) return rc;
+        if (rc == CGD_E_BREAKDOWN || worst == CGD_OK) worst = rc;
+    }
+    return worst;
+}
+
+}  // namespace cgd
