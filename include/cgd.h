@@ -481,8 +481,10 @@ cgd_status cgd_conv3_wgrad(int32_t nx, int32_t ny, int32_t nz, int32_t ci, int32
  *  10  first iteration, kind 5's pass reading b (b.b as well)
  *  11  first iteration, kind 6's pass
  *  12  first iteration, kind 7's pass
- *  13  tiled hex deposit: binning and tile counts
+ *  13  tiled hex deposit: binning and tile counts (F <= 4 on up to 2,048
+ *      tiles: binning and records in tile order per chunk of particles)
  *  14  tiled hex deposit: prefix sum and scatter of records into tiles
+ *      (F > 4 or more tiles)
  *  15  tiled hex deposit: fixed-point sums in LDS and the finished field
  *  16  tet / face-slot polynomial preconditioning, pass w = B v
  *  17  tet / face-slot polynomial preconditioning, pass v = g (B w + s w + q v)

@@ -160,6 +160,12 @@ struct TileArgs {
     uint32_t* counts;      // [n_snap * ntiles]: particles per tile
     uint32_t* offsets;     // [n_snap * ntiles + 1]
     uint32_t* cursor;      // [n_snap * ntiles]
+    // Ordered path: records stay within their chunk of `chunk` particles, in
+    // tile order; row r of starts ([nt + 1] uint16 each) holds where each
+    // tile's run begins in chunk r (snapshot j's chunks are the rows from
+    // off[j] / chunk + j on).
+    int chunk;
+    uint16_t* starts;
     // Tile-bucketed records [total]: F = 1: (cell within its tile, bits of
     // field 0's value), 8 bytes; F >= 2: (cell, fields 0, 1, 2), 16 bytes
     // (one scattered write per particle instead of one per field).
@@ -215,14 +221,93 @@ __global__ void k_tile_clear(TileArgs a) {
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nt; t += gridDim.x * blockDim.x) a.counts[t] = 0u;
 }
 
+// Exclusive prefix sum over a block of NT threads, and the total (two
+// barriers; sh: NT / 64 entries).
+template <int NT, typename U>
+__device__ inline U block_exclusive(U s, U* sh, U* total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    U incl = s;
+    for (int o = 1; o < 64; o <<= 1) {
+        const U y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) sh[wave] = incl;
+    __syncthreads();
+    U before = 0, all = 0;
+    for (int w = 0; w < NT / 64; ++w) {
+        const U v = sh[w];
+        before += w < wave ? v : 0;
+        all += v;
+    }
+    __syncthreads();
+    *total = all;
+    return before + incl - s;
+}
+
+// The edges of all three axes into LDS.
+__device__ inline void load_edges(const TileArgs& a, double* redge) {
+    const int ne = a.rl.n[0] + a.rl.n[1] + a.rl.n[2] + 3;  // <= kRectEdges (host)
+    for (int i = threadIdx.x; i < ne; i += kTBlock) redge[i] = a.rl.e[i];
+}
+
+// Host cells of G particles of a thread (-1: not finite, nf, or outside).
+// RECT: by the rectilinear edges (RectLoc's definition), from a copy of the
+// edges in LDS: per axis the largest i < n with e_i <= x by binary lifting
+// (steps of decreasing powers of two, the same count for every lane), the G
+// particles interleaved.
+template <bool RECT, int G>
+__device__ inline void bin_group(const TileArgs& a, const double* redge, const float* px, const float* py,
+                                 const float* pz, int32_t* k, bool* nf) {
+    if constexpr (RECT) {
+        // a non-finite coordinate on any axis counts as non-finite; a
+        // point outside the closed box on any axis is dropped
+        double p[G][3];
+        bool in[G];
+        int id[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            p[i][0] = (double)px[i];
+            p[i][1] = (double)py[i];
+            p[i][2] = (double)pz[i];
+            nf[i] = !(isfinite(p[i][0]) && isfinite(p[i][1]) && isfinite(p[i][2]));
+            in[i] = !nf[i];
+            id[i] = 0;
+        }
+        int off = 0, mul = 1;
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            const int na = a.rl.n[ax];
+            const double* e = redge + off;
+            int ia[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                in[i] = in[i] && p[i][ax] >= e[0] && p[i][ax] <= e[na];
+                ia[i] = 0;
+            }
+            for (int step = na > 1 ? 1 << (31 - __clz(na - 1)) : 0; step > 0; step >>= 1) {
+#pragma unroll
+                for (int i = 0; i < G; ++i) {
+                    const int c = ia[i] + step;
+                    ia[i] = (c < na && e[min(c, na - 1)] <= p[i][ax]) ? c : ia[i];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < G; ++i) id[i] += mul * ia[i];
+            off += na + 1;
+            mul *= na;
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) k[i] = in[i] ? id[i] : -1;
+    } else {
+#pragma unroll
+        for (int i = 0; i < G; ++i) k[i] = (int32_t)hex_cell(a.g, px[i], py[i], pz[i], &nf[i]);
+    }
+}
+
 // Pass 1 (grid: blocks x snapshots): host cells (stored), dropped counts,
 // particles per tile, and the max |v| / non-finite count of every field over
 // the block's chunk of nsub_bin * kTChunk particles (the values of the direct
 // path's k_absmax, folded into this pass).
-// RECT: the host cell by the rectilinear edges (RectLoc's definition), from
-// a copy of the edges in LDS: per axis the largest i < n with e_i <= x by
-// binary lifting (steps of decreasing powers of two, the same count for
-// every lane), the kBPer particles of a thread interleaved.
 template <bool RECT, bool PACK>
 __global__ __launch_bounds__(kTBlock) void k_tile_bin(TileArgs a) {
     __shared__ uint32_t hist[kMaxTiles];
@@ -240,10 +325,7 @@ __global__ __launch_bounds__(kTBlock) void k_tile_bin(TileArgs a) {
         bmax[threadIdx.x] = 0u;
         bbad[threadIdx.x] = 0ull;
     }
-    if constexpr (RECT) {
-        const int ne = a.rl.n[0] + a.rl.n[1] + a.rl.n[2] + 3;  // <= kRectEdges (host)
-        for (int i = threadIdx.x; i < ne; i += kTBlock) redge[i] = a.rl.e[i];
-    }
+    if constexpr (RECT) load_edges(a, redge);
     __syncthreads();
     unsigned long long dropped = 0ull, nfpos = 0ull;
     const int npass = a.nsub_bin * (kTChunk / (kTBlock * kBPer));
@@ -267,50 +349,7 @@ __global__ __launch_bounds__(kTBlock) void k_tile_bin(TileArgs a) {
         const int64_t p0 = cb + (int64_t)sub * (kTBlock * kBPer) + threadIdx.x;
         int32_t k[kBPer];
         bool nf[kBPer];
-        if constexpr (RECT) {
-            // a non-finite coordinate on any axis counts as non-finite; a
-            // point outside the closed box on any axis is dropped
-            double p[kBPer][3];
-            bool in[kBPer];
-            int id[kBPer];
-#pragma unroll
-            for (int i = 0; i < kBPer; ++i) {
-                p[i][0] = (double)px[i];
-                p[i][1] = (double)py[i];
-                p[i][2] = (double)pz[i];
-                nf[i] = !(isfinite(p[i][0]) && isfinite(p[i][1]) && isfinite(p[i][2]));
-                in[i] = !nf[i];
-                id[i] = 0;
-            }
-            int off = 0, mul = 1;
-#pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-                const int na = a.rl.n[ax];
-                const double* e = redge + off;
-                int ia[kBPer];
-#pragma unroll
-                for (int i = 0; i < kBPer; ++i) {
-                    in[i] = in[i] && p[i][ax] >= e[0] && p[i][ax] <= e[na];
-                    ia[i] = 0;
-                }
-                for (int step = na > 1 ? 1 << (31 - __clz(na - 1)) : 0; step > 0; step >>= 1) {
-#pragma unroll
-                    for (int i = 0; i < kBPer; ++i) {
-                        const int c = ia[i] + step;
-                        ia[i] = (c < na && e[min(c, na - 1)] <= p[i][ax]) ? c : ia[i];
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < kBPer; ++i) id[i] += mul * ia[i];
-                off += na + 1;
-                mul *= na;
-            }
-#pragma unroll
-            for (int i = 0; i < kBPer; ++i) k[i] = in[i] ? id[i] : -1;
-        } else {
-#pragma unroll
-            for (int i = 0; i < kBPer; ++i) k[i] = (int32_t)hex_cell(a.g, px[i], py[i], pz[i], &nf[i]);
-        }
+        bin_group<RECT, kBPer>(a, redge, px, py, pz, k, nf);
         if (sub + 1 < npass) load(sub + 1);
 #pragma unroll
         for (int i = 0; i < kBPer; ++i) {
@@ -386,22 +425,9 @@ __global__ __launch_bounds__(kTBlock) void k_tile_scan(TileArgs a) {
     const int t0 = min((int)threadIdx.x * per, nt), t1 = min(t0 + per, nt);
     uint32_t s = 0u;
     for (int t = t0; t < t1; ++t) s += a.counts[t];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = s;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0u, total = 0u;
-    for (int w = 0; w < kTBlock / 64; ++w) {
-        const uint32_t v = wsum[w];
-        before += w < wave ? v : 0u;
-        total += v;
-    }
+    uint32_t total;
+    uint32_t run = block_exclusive<kTBlock>(s, wsum, &total);
     if (threadIdx.x == 0) a.offsets[nt] = total;
-    uint32_t run = before + incl - s;
     for (int t = t0; t < t1; ++t) {
         a.offsets[t] = run;
         a.cursor[t] = run;
@@ -499,35 +525,43 @@ __global__ __launch_bounds__(kTBlock) void k_tile_scatter(TileArgs a) {
     }
 }
 
-// Pass 3 for F <= 4 on grids of at most kStageMaxTiles tiles, staged in LDS
-// (grid: blocks x snapshots, C particles per block).  A block's run of
-// records in a tile is short (about 8 on the dense bed), so records written
-// straight from the particles' registers reach each cache line one at a time
-// and lines left partly written in L2 go to HBM piecewise (2.5 bytes written
-// per record byte).  Here the block ranks its particles per tile with LDS
-// atomics, prefix-sums the counts, places every record at its tile's
-// block-local position in LDS, reserves one range per tile from the cursors,
-// and then writes the staged records in order: consecutive lanes store
-// consecutive records of a run.  The cell ids and values are read once.
+// Passes 1 and 3 in one for F <= 4 on grids of at most kStageMaxTiles tiles
+// (grid: blocks x snapshots, C particles per block): binning, the counters
+// and max |v| of pass 1, and the block's records ordered by tile in LDS and
+// stored, in order, in the block's own part of the record array, with the
+// start of every tile's run.  Nothing is counted over the whole grid before
+// a record can be placed, so positions and values are read once, no host
+// cells go through memory, and every store is contiguous; the accumulation
+// gathers a tile's runs.  Bound by the LDS rank atomics and the float64
+// binning next to its 20 + 8 bytes per particle: 20M particles into 2,048
+// tiles 124 us, where counting, prefix sum and scatter took 217 us and moved
+// 720 MB in place of 485.
 // NV fields: the 8-byte record at NV = 1, the 16-byte record (fields 0..2)
-// above, and at NV = 4 field 3's value in its own staged array.  C is as
-// large as the LDS allows: 16384 at NV = 1, 8192 at 2 or 3, 4096 at 4.
+// above, and at NV = 4 field 3's value in its own staged array.
 constexpr int kStageMaxTiles = 2 * kTBlock;  // the prefix sum takes two tiles per thread
 template <int NV>
 struct StageRec { using T = uint4; };
 template <>
 struct StageRec<1> { using T = uint2; };
-template <int C, int NV>
-__global__ __launch_bounds__(kTBlock) void k_tile_scatter_staged(TileArgs a) {
-    static_assert(C % kTBlock == 0 && NV >= 1 && NV <= 4, "whole passes, at most four fields");
+constexpr size_t order_stage_bytes(int c, size_t rec, bool rect) {
+    return std::max(c * rec, rect ? (size_t)kRectEdges * sizeof(double) : (size_t)0);
+}
+template <int C, int NV, bool RECT>
+__global__ __launch_bounds__(kTBlock) void k_tile_order(TileArgs a) {
+    static_assert(C % kTBlock == 0 && NV >= 1 && NV <= 4 && C <= 16384, "whole passes, at most four fields");
     constexpr int P = C / kTBlock;  // particles per thread
+    constexpr int G = P % 4 == 0 ? 4 : 2;  // ... binned together
     using Rec = typename StageRec<NV>::T;
-    __shared__ Rec stage[C];                        // (cell, value bits), tile by tile
+    // the edges are done with before the first record is staged
+    __shared__ __align__(16) unsigned char pool[order_stage_bytes(C, sizeof(Rec), RECT)];
+    Rec* stage = reinterpret_cast<Rec*>(pool);      // (cell, value bits), tile by tile
+    double* redge = reinterpret_cast<double*>(pool);
     __shared__ uint32_t stage3[NV == 4 ? C : 1];    // field 3's value bits, in the same order
     __shared__ uint32_t hist[kStageMaxTiles];       // the block's particles per tile
-    __shared__ uint32_t loc[kStageMaxTiles];        // block-local start of each tile's run
-    __shared__ uint32_t base[kStageMaxTiles];       // its start in the tile's global range
+    __shared__ uint32_t loc[kStageMaxTiles];        // start of each tile's run
     __shared__ uint32_t wsum[kTBlock / 64];
+    __shared__ uint32_t bmax[NV];
+    __shared__ unsigned long long bbad[NV];
     const int j = blockIdx.y;
     int64_t s0, s1;
     snap_range(a, j, s0, s1);
@@ -536,147 +570,344 @@ __global__ __launch_bounds__(kTBlock) void k_tile_scatter_staged(TileArgs a) {
     const int64_t ce = min(cb + (int64_t)C, s1);
     const int nt = a.ntiles;  // <= kStageMaxTiles (host)
     for (int t = threadIdx.x; t < nt; t += kTBlock) hist[t] = 0u;
-    int32_t kk[P];
+    if (threadIdx.x < NV) {
+        bmax[threadIdx.x] = 0u;
+        bbad[threadIdx.x] = 0ull;
+    }
+    if constexpr (RECT) load_edges(a, redge);
+    // every load is unconditional (clamped index); the next group's positions
+    // are in flight while one is binned
     uint32_t vv[NV][P];
+    float px[G], py[G], pz[G];
+    auto load = [&](int i0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int64_t p = min(cb + threadIdx.x + (int64_t)(i0 + i) * kTBlock, ce - 1);
+            px[i] = a.pos[3 * p];
+            py[i] = a.pos[3 * p + 1];
+            pz[i] = a.pos[3 * p + 2];
+        }
+    };
+    load(0);
 #pragma unroll
     for (int i = 0; i < P; ++i) {
-        const int64_t p = cb + threadIdx.x + (int64_t)i * kTBlock;
-        kk[i] = p < ce ? a.cellbuf[p] : -1;
+        const int64_t p = min(cb + threadIdx.x + (int64_t)i * kTBlock, ce - 1);
 #pragma unroll
-        for (int f = 0; f < NV; ++f) vv[f][i] = p < ce ? __float_as_uint(a.values[(size_t)f * a.total + p]) : 0u;
+        for (int f = 0; f < NV; ++f) vv[f][i] = __float_as_uint(a.values[(size_t)f * a.total + p]);
     }
     __syncthreads();
+    int32_t kk[P];
     uint32_t rank[P];
+    unsigned long long dropped = 0ull, nfpos = 0ull;
 #pragma unroll
-    for (int i = 0; i < P; ++i) rank[i] = kk[i] >= 0 ? atomicAdd(&hist[kk[i] >> a.cpt_log2], 1u) : 0u;
+    for (int i0 = 0; i0 < P; i0 += G) {
+        int32_t k[G];
+        bool nf[G];
+        bin_group<RECT, G>(a, redge, px, py, pz, k, nf);
+        if (i0 + G < P) load(i0 + G);
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const bool in = cb + threadIdx.x + (int64_t)(i0 + i) * kTBlock < ce;
+            if (in && k[i] < 0) {
+                ++dropped;
+                nfpos += nf[i] ? 1ull : 0ull;
+            }
+            kk[i0 + i] = in ? k[i] : -1;
+            rank[i0 + i] = kk[i0 + i] >= 0 ? atomicAdd(&hist[kk[i0 + i] >> a.cpt_log2], 1u) : 0u;
+        }
+    }
+#pragma unroll
+    for (int f = 0; f < NV; ++f) {
+        uint32_t m = 0u;
+        unsigned long long bad = 0ull;
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const bool in = cb + threadIdx.x + (int64_t)i * kTBlock < ce;
+            const uint32_t x = in ? vv[f][i] & 0x7fffffffu : 0u;
+            if (x >= 0x7f800000u) {
+                ++bad;
+                vv[f][i] = 0u;  // adds nothing
+            } else {
+                m = x > m ? x : m;
+            }
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint32_t mo = __shfl_xor(m, o);
+            m = mo > m ? mo : m;
+            bad += __shfl_xor(bad, o);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            if (m) atomicMax(&bmax[f], m);
+            if (bad) atomicAdd(&bbad[f], bad);
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        dropped += __shfl_xor(dropped, o);
+        nfpos += __shfl_xor(nfpos, o);
+    }
+    if ((threadIdx.x & 63) == 0 && dropped) {
+        atomicAdd(a.dropped + (size_t)j * a.cnt_jstride, dropped);
+        if (nfpos) atomicAdd(a.nf_pos + (size_t)j * a.cnt_jstride, nfpos);
+    }
     __syncthreads();
-    // exclusive prefix sum of the counts: tiles 2 tid and 2 tid + 1 per thread,
-    // a wave scan by shuffles, then the wave totals
+    if (threadIdx.x < NV) {
+        const int f = threadIdx.x;
+        if (bmax[f]) atomic_max_if_larger(&a.maxbits[j * a.F + f], bmax[f]);
+        if (bbad[f]) atomicAdd(&a.nf_val[(size_t)j * a.cnt_jstride + f * a.nf_val_stride], bbad[f]);
+    }
+    // exclusive prefix sum of the counts: tiles 2 tid and 2 tid + 1 per thread
     const int t0 = 2 * (int)threadIdx.x;
     const uint32_t h0 = t0 < nt ? hist[t0] : 0u, h1 = t0 + 1 < nt ? hist[t0 + 1] : 0u;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = h0 + h1;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
-    if (lane == 63) wsum[wave] = incl;
-    uint32_t* cursor = a.cursor + (size_t)j * nt;
-    for (int t = threadIdx.x; t < nt; t += kTBlock) {
-        const uint32_t c = hist[t];
-        base[t] = c ? atomicAdd(&cursor[t], c) : 0u;
-    }
-    __syncthreads();
-    uint32_t before = 0u, total = 0u;
-    for (int w = 0; w < kTBlock / 64; ++w) {
-        const uint32_t s = wsum[w];
-        before += w < wave ? s : 0u;
-        total += s;
-    }
-    const uint32_t ex = before + incl - (h0 + h1);
+    uint32_t total;
+    const uint32_t ex = block_exclusive<kTBlock>(h0 + h1, wsum, &total);
     if (t0 < nt) loc[t0] = ex;
     if (t0 + 1 < nt) loc[t0 + 1] = ex + h0;
     __syncthreads();
+    uint16_t* row = a.starts + (size_t)(s0 / C + j + blockIdx.x) * (nt + 1);
+    for (int t = threadIdx.x; t < nt; t += kTBlock) row[t] = (uint16_t)loc[t];
+    if (threadIdx.x == 0) row[nt] = (uint16_t)total;
 #pragma unroll
     for (int i = 0; i < P; ++i) {
         if (kk[i] < 0) continue;
         const uint32_t k = loc[kk[i] >> a.cpt_log2] + rank[i];  // < total <= C
+        const uint32_t cl = (uint32_t)kk[i] & ((uint32_t)a.cpt - 1u);
         if constexpr (NV == 1) {
-            stage[k] = make_uint2((uint32_t)kk[i], vv[0][i]);
+            stage[k] = make_uint2(cl, vv[0][i]);
         } else {
-            stage[k] = make_uint4((uint32_t)kk[i], vv[0][i], vv[1][i], NV > 2 ? vv[NV > 2 ? 2 : 0][i] : 0u);
+            stage[k] = make_uint4(cl, vv[0][i], vv[1][i], NV > 2 ? vv[NV > 2 ? 2 : 0][i] : 0u);
             if constexpr (NV == 4) stage3[k] = vv[3][i];
         }
     }
     __syncthreads();
-    const uint32_t mask = (uint32_t)a.cpt - 1u;
     for (uint32_t k = threadIdx.x; k < total; k += kTBlock) {
-        const Rec e = stage[k];
-        const uint32_t t = e.x >> a.cpt_log2;
-        const uint32_t g = base[t] + (k - loc[t]);
         if constexpr (NV == 1) {
-            a.rec[g] = make_uint2(e.x & mask, e.y);
+            a.rec[cb + k] = stage[k];
         } else {
-            a.rec4[g] = make_uint4(e.x & mask, e.y, e.z, e.w);
-            if constexpr (NV == 4) a.rv[g] = __uint_as_float(stage3[k]);
+            a.rec4[cb + k] = stage[k];
+            if constexpr (NV == 4) a.rv[cb + k] = __uint_as_float(stage3[k]);
         }
     }
 }
 
+// rint(v 2^S); FINITE: v is known to be finite, else 0 for one that is not.
+template <bool FINITE = false>
 __device__ inline long long quantise(float v, int S) {
-    return isfinite(v) ? __double2ll_rn(ldexp((double)v, S)) : 0ll;
+    return FINITE || isfinite(v) ? __double2ll_rn(ldexp((double)v, S)) : 0ll;
+}
+
+// (float)(ldexp((double)v, -S) / V), the finished field value.  The division
+// (some 15 float64 instructions) is a multiplication by rs = 2^-S / V
+// instead: the product is within 3 units in the last place of the quotient
+// that would be rounded, and both round to the same float32 unless they lie
+// within that of a tie between two float32 numbers (or outside float32's
+// normal range), where the division decides.
+__device__ inline float finish_value(long long v, int S, double V, double rs, bool fast) {
+    const double d = (double)v, q = d * rs;
+    const unsigned long long b = (unsigned long long)__double_as_longlong(q);
+    const uint32_t low = (uint32_t)b & 0x1fffffffu, e = (uint32_t)(b >> 52) & 0x7ffu;
+    if (fast && low - (0x10000000u - 8u) > 16u && e - 897u < 253u) return (float)q;  // 2^-126 <= |q| < 2^127
+    if (!v) return 0.f;
+    return (float)(ldexp(d, -S) / V);
 }
 
 // Pass 4: one workgroup per tile (of all snapshots): exact int64 sums in LDS
 // of the quantised values rint(v 2^S_f), then the tile's
 // field = float32((acc 2^-S_f) / V) (and the accumulators when asked for).
-// R16: the records hold the cell and fields 0..2.
-template <bool R16>
-__global__ __launch_bounds__(kTBlock) void k_tile_accum(TileArgs a) {
-    __shared__ unsigned long long lacc[kTileWords];
+// R16: the records hold the cell and fields 0..2.  SEG: the tile's records
+// are a run in each chunk of the ordering pass.  The runs that are not empty
+// are numbered and their lengths prefix-summed (NSEG chunks at a time), and
+// a wave finds the runs of 64 consecutive records together, so any
+// distribution of the particles over the chunks (sorted input: few long
+// runs) loads every lane alike: each wave takes a contiguous share of the
+// records, finds the run of its first one by two 64-way steps, and then per
+// 64 records reads the 64 runs from there on, which hold them all; a
+// record's run is the number of first records up to it.  (A binary search per
+// lane, 11 LDS round trips, took 182 us on the dense bed for the whole
+// kernel, the 64-way steps for every 64 records 150, this 142.)
+// Else they are one range of the bucketed array.  Bound by vector
+// instructions (about 45 per 64 records for the run, 25 to quantise and add
+// each value, 25 per 64 cells to finish) and, at one workgroup per compute
+// unit, by the latencies between its phases; with the ordering pass 266 us
+// for the dense bed's deposit where counting, scattering and adding took 307.
+// Dynamic LDS: the accumulators, then the runs.
+template <int NT>
+constexpr int accum_segs() { return 2 * NT; }
+template <bool R16, bool SEG, int NT>
+__global__ __launch_bounds__(NT) void k_tile_accum(TileArgs a) {
+    constexpr int NSEG = accum_segs<NT>();
+    extern __shared__ unsigned long long lacc[];
+    uint32_t* const P = reinterpret_cast<uint32_t*>(lacc + (size_t)a.F * a.cpt);  // [NSEG] where run q's records begin
+    uint32_t* const D = P + NSEG;  // [NSEG] record index minus position, relative to the snapshot's first particle
     __shared__ int S[CGD_MAX_FIELDS];
-    const int T = blockIdx.x;
-    const int j = T / a.ntiles, t = T - j * a.ntiles;
-    const int64_t c0 = (int64_t)t * a.cpt;
-    const int nc = (int)min<int64_t>(a.cpt, a.cells - c0);
-    for (int i = threadIdx.x; i < a.F * a.cpt; i += kTBlock) lacc[i] = 0ull;
-    if (threadIdx.x < a.F) {
-        int64_t s0, s1;
-        snap_range(a, j, s0, s1);
-        S[threadIdx.x] = frac_bits_used(a.maxbits[j * a.F + threadIdx.x], a.force_s ? a.force_s[threadIdx.x] : -1,
-                                        e_n_dev(s1 - s0));
-    }
-    __syncthreads();
-    const uint32_t r0 = a.offsets[T], r1 = a.offsets[T + 1];
-    const int S0 = S[0];
-    constexpr int U = 4;  // records per thread whose loads are in flight together
-    for (uint32_t r = r0 + threadIdx.x; r < r1; r += U * kTBlock) {
-        uint4 e[U];
+    __shared__ unsigned long long wsum[NT / 64];
+    const int lane = threadIdx.x & 63;
+    // SEG: a workgroup takes several tiles one after the other (one of 128 KB
+    // fits a compute unit, so nothing else hides its latencies): the next
+    // tile's run starts are loaded while this one's records are added, and
+    // the accumulators are cleared as they are read out.  Consecutive
+    // workgroups go to the XCDs in turn; each XCD takes groups of 32
+    // consecutive tiles at a time, one per compute unit, so that the lines in
+    // which neighbouring tiles' runs meet (a run is 64 bytes on the dense bed)
+    // are read into one L2 once.
+    const int ntot = a.n_snap * a.ntiles;
+    auto tile_of = [&](int i) {
+        return SEG && i < ntot / 256 * 256 ? ((i / 256) * 8 + i % 8) * 32 + i / 8 % 32 : i;
+    };
+    const int q0 = 2 * (int)threadIdx.x;
+    uint16_t run[2][2];
+    int64_t s0, s1;
+    int nchunks = 0;
+    const uint16_t* col = nullptr;
+    auto load_runs = [&](int b0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t rr = r + u * kTBlock;
+        for (int i = 0; i < 2; ++i) {
+            const uint16_t* c = col + (size_t)min(b0 + q0 + i, nchunks - 1) * (a.ntiles + 1);
+            run[i][0] = c[0];
+            run[i][1] = c[1];
+        }
+    };
+    auto enter = [&](int T) {
+        const int j = T / a.ntiles, t = T - j * a.ntiles;
+        snap_range(a, j, s0, s1);
+        if constexpr (SEG) {
+            nchunks = (int)((s1 - s0 + a.chunk - 1) / a.chunk);
+            col = a.starts + (size_t)(s0 / a.chunk + j) * (a.ntiles + 1) + t;
+            if (nchunks > 0) load_runs(0);
+        }
+    };
+    enter(tile_of(blockIdx.x));
+    for (int i = threadIdx.x; i < a.F * a.cpt; i += NT) lacc[i] = 0ull;
+    for (int ti = blockIdx.x; ti < ntot; ti += gridDim.x) {
+        const int T = tile_of(ti);
+        const int j = T / a.ntiles, t = T - j * a.ntiles;
+        const int64_t c0 = (int64_t)t * a.cpt;
+        const int nc = (int)min<int64_t>(a.cpt, a.cells - c0);
+        if (threadIdx.x < a.F)
+            S[threadIdx.x] = frac_bits_used(a.maxbits[j * a.F + threadIdx.x], a.force_s ? a.force_s[threadIdx.x] : -1,
+                                            e_n_dev(s1 - s0));
+        __syncthreads();
+        const int S0 = S[0], S1 = R16 ? S[1] : 0, S2 = R16 && a.F > 2 ? S[2] : 0;
+        constexpr int U = 4;  // records per thread whose loads are in flight together
+        uint4 e[U];
+        int64_t x[U];
+        bool in[U];
+        auto load = [&](int u) {
             if constexpr (R16) {
-                e[u] = rr < r1 ? a.rec4[rr] : make_uint4(0u, 0u, 0u, 0u);
+                e[u] = a.rec4[x[u]];
             } else {
-                const uint2 e2 = rr < r1 ? a.rec[rr] : make_uint2(0u, 0u);
+                const uint2 e2 = a.rec[x[u]];
                 e[u] = make_uint4(e2.x, e2.y, 0u, 0u);
             }
-        }
+        };
+        // adds the records x[u], loaded, of the lanes with in[u]
+        auto add = [&]() {
+            for (int f = 3; f < a.F; ++f) {
+                float v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const long long q = quantise(__uint_as_float(e[u].y), S0);
-            if (q != 0) atomicAdd(&lacc[e[u].x], (unsigned long long)q);
-            if constexpr (R16) {
-                const long long q1 = quantise(__uint_as_float(e[u].z), S[1]);
-                if (q1 != 0) atomicAdd(&lacc[a.cpt + e[u].x], (unsigned long long)q1);
-                if (a.F > 2) {
-                    const long long q2 = quantise(__uint_as_float(e[u].w), S[2]);
-                    if (q2 != 0) atomicAdd(&lacc[2 * a.cpt + e[u].x], (unsigned long long)q2);
+                for (int u = 0; u < U; ++u) v[u] = a.rv[(size_t)(f - 3) * a.total + x[u]];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (in[u]) atomicAdd(&lacc[f * a.cpt + e[u].x], (unsigned long long)quantise<SEG>(v[u], S[f]));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (!in[u]) continue;
+                atomicAdd(&lacc[e[u].x], (unsigned long long)quantise<SEG>(__uint_as_float(e[u].y), S0));
+                if constexpr (R16) {
+                    atomicAdd(&lacc[a.cpt + e[u].x], (unsigned long long)quantise<SEG>(__uint_as_float(e[u].z), S1));
+                    if (a.F > 2)
+                        atomicAdd(&lacc[2 * a.cpt + e[u].x], (unsigned long long)quantise<SEG>(__uint_as_float(e[u].w), S2));
                 }
             }
-        }
-        for (int f = 3; f < a.F; ++f) {
-            float v[U];
+        };
+        if constexpr (SEG) {
+            const int64_t p0 = s0;  // this tile's snapshot (the next tile's replaces s0, s1 and the runs below)
+            const int nch = nchunks;
+            for (int b0 = 0; b0 < nch; b0 += NSEG) {
+                const int ns = min(NSEG, nch - b0);
+                uint32_t st[2], len[2];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t rr = r + u * kTBlock;
-                v[u] = rr < r1 ? a.rv[(size_t)(f - 3) * a.total + rr] : 0.f;
-            }
+                for (int i = 0; i < 2; ++i) {
+                    st[i] = run[i][0];
+                    len[i] = q0 + i < ns ? run[i][1] - run[i][0] : 0u;
+                }
+                if (b0 + NSEG < nch) load_runs(b0 + NSEG);
+                else if (ti + (int)gridDim.x < ntot) enter(tile_of(ti + gridDim.x));
+                // lengths in the low, numbers of runs in the high half
+                const unsigned long long kRun = 1ull << 32;
+                unsigned long long all;
+                unsigned long long at0 = block_exclusive<NT>(len[0] + len[1] + (len[0] ? kRun : 0ull) + (len[1] ? kRun : 0ull),
+                                                             wsum, &all);  // (barriers: the last runs are done with)
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const long long q = quantise(v[u], S[f]);
-                if (q != 0) atomicAdd(&lacc[f * a.cpt + e[u].x], (unsigned long long)q);
+                for (int i = 0; i < 2; ++i) {
+                    if (len[i]) {
+                        const uint32_t q = (uint32_t)(at0 >> 32), p = (uint32_t)at0;
+                        P[q] = p;
+                        D[q] = (uint32_t)(b0 + q0 + i) * (uint32_t)a.chunk + st[i] - p;
+                        at0 += len[i] + kRun;
+                    }
+                }
+                __syncthreads();
+                const int nr = (int)(all >> 32);
+                const uint32_t total = (uint32_t)all;  // <= NSEG * 16384
+                const uint32_t share = (total + NT - 1) / NT * 64;
+                const uint32_t w0 = (threadIdx.x >> 6) * share, w1 = min(w0 + share, total);
+                if (w0 >= w1) continue;
+                constexpr int ST = NSEG / 64;
+                int b = (__popcll(__ballot(lane * ST < nr && P[min(lane * ST, nr - 1)] <= w0)) - 1) * ST;  // (P[0] = 0)
+                b += __popcll(__ballot(lane < ST && b + lane < nr && P[min(b + lane, nr - 1)] <= w0)) - 1;
+                b = __builtin_amdgcn_readfirstlane(b);
+                for (uint32_t i0 = w0; i0 < w1; i0 += 64 * U) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const uint32_t i = i0 + 64 * u;  // (past the share: lanes idle on the last run)
+                        uint32_t v = P[min(b + lane, nr - 1)];
+                        if (b + 1 < nr && (uint32_t)__builtin_amdgcn_readlane(v, 1) <= i) {
+                            ++b;  // the last 64 records ended with their run
+                            v = P[min(b + lane, nr - 1)];
+                        }
+                        const uint32_t rel = v - i;  // lane 0: not positive (a large number, or 0)
+                        const bool head = lane > 0 && b + lane < nr && rel < 64u;
+                        // lanes without a first record among the 64 push 0 to lane 0
+                        const int got = __builtin_amdgcn_ds_permute(head ? (int)rel * 4 : 0, head ? 1 : 0);
+                        const unsigned long long m = __ballot(lane > 0 && got != 0);
+                        const int mine = b + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0)) +
+                                         (int)(m >> lane & 1);
+                        in[u] = i + lane < w1;
+                        x[u] = p0 + (int64_t)(uint32_t)(D[min(mine, nr - 1)] + min(i + lane, total - 1));
+                        load(u);
+                        b = min(__builtin_amdgcn_readlane(mine, 63), nr - 1);
+                    }
+                    add();
+                }
+            }
+            if (nch == 0 && ti + (int)gridDim.x < ntot) enter(tile_of(ti + gridDim.x));
+        } else {
+            const uint32_t r0 = a.offsets[T], r1 = a.offsets[T + 1];
+            for (uint32_t r = r0 + threadIdx.x; r < r1 && r >= r0; r += U * NT) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    in[u] = u * NT < r1 - r;  // (compared, not added to: no wrap near 2^32 records)
+                    x[u] = in[u] ? r + u * NT : r1 - 1;
+                    load(u);
+                }
+                add();
             }
         }
-    }
-    __syncthreads();
-    for (int f = 0; f < a.F; ++f) {
-        const size_t o = ((size_t)j * a.F + f) * a.cells + c0;
-        for (int i = threadIdx.x; i < nc; i += kTBlock) {
-            const long long v = (long long)lacc[f * a.cpt + i];
-            a.field[o + i] = (float)(ldexp((double)v, -S[f]) / (a.vcell ? a.vcell[c0 + i] : a.vol));
-            if (a.acc) a.acc[o + i] = v;
+        __syncthreads();
+        for (int f = 0; f < a.F; ++f) {
+            const size_t o = ((size_t)j * a.F + f) * a.cells + c0;
+            const double rs = ldexp(1.0, -S[f]) / a.vol;
+            const bool fast = !a.vcell && rs >= 0x1p-900 && rs <= 0x1p900;
+            for (int i = threadIdx.x; i < nc; i += NT) {
+                const long long v = (long long)lacc[f * a.cpt + i];
+                if (SEG) lacc[f * a.cpt + i] = 0ull;
+                a.field[o + i] = finish_value(v, S[f], a.vcell ? a.vcell[c0 + i] : a.vol, rs, fast);
+                if (a.acc) a.acc[o + i] = v;
+            }
         }
+        __syncthreads();
     }
 }
 
@@ -775,11 +1006,53 @@ static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 static size_t rec_bytes(int F) { return F == 1 ? 8 : 16; }
 static size_t rv_fields(int F) { return F > 3 ? (size_t)(F - 3) : 0; }
 
+// kTChunk-particle chunks per block of a bucketing pass: one (longer chunks
+// measured slower on the dense bed and on the batched launch); an
+// environment override for tuning runs.
+static int tile_nsub(const char* env) {
+    if (const char* e = getenv(env)) return std::max(1, atoi(e));
+    return 1;
+}
+
+// The ordered path (k_tile_order): the whole plan.
+struct OrderPlan {
+    int cpt, ntiles, chunk;
+    size_t starts_bytes;
+};
+// F <= 4 and a grid of at most kStageMaxTiles tiles (else the counting
+// passes).  Tiles are halved, down to 64 cells, while all snapshots together
+// have fewer than 512, so that the accumulation fills the 256 compute units
+// on small grids too (24^3 cells are one largest tile: 9.9 us on one unit).
+// Chunks are as large as a block's LDS orders (16384 particles at F = 1,
+// 8192 at 2 or 3, 6144 at 4), for long runs, where that still makes 512
+// blocks, else 2048: 20,000 particles in two chunks of 16384 took 42 us to
+// bin and scatter, in ten of 2048 they take 7.4.
+static bool order_plan(int64_t cells, int64_t total, int32_t n_snap, int32_t F, OrderPlan* p) {
+    int cpt, nt;
+    if (F > 4 || !tile_plan(cells, total, F, &cpt, &nt) || nt > kStageMaxTiles || tile_nsub("CGD_DEPOSIT_NSUB") != 1)
+        return false;
+    if (!getenv("CGD_DEPOSIT_CPT"))
+        while ((int64_t)n_snap * nt < 512 && cpt > 64) {
+            cpt >>= 1;
+            nt = (int)((cells + cpt - 1) / cpt);
+        }
+    const int most = F == 1 ? 16384 : (F <= 3 ? 8192 : 6144);
+    p->cpt = cpt;
+    p->ntiles = nt;
+    p->chunk = total >= (int64_t)256 * most ? most : 2048;
+    p->starts_bytes = 2 * ((size_t)(total / p->chunk) + n_snap + 1) * (nt + 1);
+    return true;
+}
+
 size_t tiled_deposit_temp_bytes(int64_t cells, int64_t total, int32_t n_snap, int32_t F) {
     int cpt, nt;
     if (!tile_plan(cells, total, F, &cpt, &nt)) return 0;
-    return al256(4 * (size_t)total) + al256(rec_bytes(F) * total) + al256(4 * rv_fields(F) * total) +
-           al256(4 * (3 * (size_t)n_snap * nt + 1));
+    const size_t recs = al256(rec_bytes(F) * total) + al256(4 * rv_fields(F) * total);
+    const size_t counted = recs + al256(4 * (size_t)total) + al256(4 * (3 * (size_t)n_snap * nt + 1));
+    OrderPlan op;
+    // (the counting passes' bytes are the documented need; the ordered path's
+    // are fewer but for the smallest calls)
+    return order_plan(cells, total, n_snap, F, &op) ? std::max(counted, recs + al256(op.starts_bytes)) : counted;
 }
 
 void deposit_info_init(DepositInfo* info, const ScaleForce& fs, hipStream_t s) {
@@ -790,12 +1063,32 @@ size_t deposit_hex_temp_bytes(const cgd_mesh m, int64_t n, int32_t F) {
     return tiled_deposit_temp_bytes(m->cells, n, 1, F);
 }
 
-// kTChunk-particle chunks per block of a bucketing pass: one (longer chunks
-// measured slower on the dense bed and on the batched launch); an
-// environment override for tuning runs.
-static int tile_nsub(const char* env) {
-    if (const char* e = getenv(env)) return std::max(1, atoi(e));
-    return 1;
+template <int C, int NV>
+static void launch_order_c(const TileArgs& a, int64_t max_n, hipStream_t s) {
+    const dim3 grid((unsigned)std::max<int64_t>(1, (max_n + C - 1) / C), a.n_snap);
+    if (a.rect) hipLaunchKernelGGL((k_tile_order<C, NV, true>), grid, dim3(kTBlock), 0, s, a);
+    else hipLaunchKernelGGL((k_tile_order<C, NV, false>), grid, dim3(kTBlock), 0, s, a);
+}
+static void launch_order(const TileArgs& a, int64_t max_n, hipStream_t s) {
+    const bool small = a.chunk == 2048;
+    if (a.F == 1) small ? launch_order_c<2048, 1>(a, max_n, s) : launch_order_c<16384, 1>(a, max_n, s);
+    else if (a.F == 2) small ? launch_order_c<2048, 2>(a, max_n, s) : launch_order_c<8192, 2>(a, max_n, s);
+    else if (a.F == 3) small ? launch_order_c<2048, 3>(a, max_n, s) : launch_order_c<8192, 3>(a, max_n, s);
+    else small ? launch_order_c<2048, 4>(a, max_n, s) : launch_order_c<6144, 4>(a, max_n, s);
+}
+
+template <bool R16, bool SEG, int NT>
+static cgd_status launch_accum(const TileArgs& a, hipStream_t s) {
+    auto kern = k_tile_accum<R16, SEG, NT>;
+    const size_t lds = (size_t)a.F * a.cpt * 8 + (SEG ? 8 * accum_segs<NT>() : 0);
+    if (lds > 64 * 1024)
+        CGD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const int all = a.n_snap * a.ntiles;
+    // SEG: as many workgroups as the 256 compute units hold
+    const int fit = 256 * (int)std::min<size_t>(160 * 1024 / (lds + 1024), 2048 / NT);
+    hipLaunchKernelGGL(kern, dim3(SEG ? std::min(all, fit) : all), dim3(NT), lds, s, a);
+    return CGD_OK;
 }
 
 cgd_status tiled_deposit(cgd_mesh m, const TiledDeposit& d, Timing* timing, hipStream_t s) {
@@ -814,6 +1107,13 @@ cgd_status tiled_deposit(cgd_mesh m, const TiledDeposit& d, Timing* timing, hipS
     a.F = d.F;
     a.g = hex_bin(m);
     a.cells = m->cells;
+    OrderPlan op;
+    const bool ordered = order_plan(m->cells, d.total, d.n_snap, d.F, &op);
+    if (ordered) {
+        cpt = op.cpt;
+        nt = op.ntiles;
+        a.chunk = op.chunk;
+    }
     a.cpt = cpt;
     a.cpt_log2 = __builtin_ctz((unsigned)cpt);
     a.ntiles = nt;
@@ -824,14 +1124,17 @@ cgd_status tiled_deposit(cgd_mesh m, const TiledDeposit& d, Timing* timing, hipS
         a.nsub = std::min(a.nsub, kPackMaxChunks);
         a.nsub_bin = std::min(a.nsub_bin, kPackMaxChunks);
     }
-    a.cellbuf = reinterpret_cast<int32_t*>(t);
-    t += al256(4 * (size_t)d.total);
+    if (!ordered) {
+        a.cellbuf = reinterpret_cast<int32_t*>(t);
+        t += al256(4 * (size_t)d.total);
+    }
     a.rec = reinterpret_cast<uint2*>(t);
     a.rec4 = reinterpret_cast<uint4*>(t);
     t += al256(rec_bytes(d.F) * d.total);
     a.rv = reinterpret_cast<float*>(t);
     t += al256(4 * rv_fields(d.F) * d.total);
     const int all = d.n_snap * nt;
+    a.starts = reinterpret_cast<uint16_t*>(t);
     a.counts = reinterpret_cast<uint32_t*>(t);
     a.offsets = a.counts + all;
     a.cursor = a.offsets + all + 1;
@@ -848,49 +1151,51 @@ cgd_status tiled_deposit(cgd_mesh m, const TiledDeposit& d, Timing* timing, hipS
     a.rect = d.rect;
     a.rl = d.rl;
     a.vcell = d.vcell;
-    hipLaunchKernelGGL(k_tile_clear, dim3((all + 255) / 256), dim3(256), 0, s, a);
-    const int64_t bchunk = (int64_t)a.nsub_bin * kTChunk, schunk = (int64_t)a.nsub * kTChunk;
-    const int cblocks = (int)std::max<int64_t>(1, (d.max_n + bchunk - 1) / bchunk);
-    const int sblocks = (int)std::max<int64_t>(1, (d.max_n + schunk - 1) / schunk);
     // Timed as a whole (kind 2: 12 bytes of position and 12 per field and
     // particle, the direct path's count) and per stage (kinds 13..15, each
     // with the bytes it must move: binning reads positions and values and
-    // writes the host cell; the scatter reads cell and values and writes the
-    // records and the values of fields 3..; the accumulation reads them and
-    // writes the field, 4 bytes per cell and field).
+    // writes the host cell, or the ordered records; the scatter reads cell and
+    // values and writes the records and the values of fields 3..; the
+    // accumulation reads them and writes the field, 4 bytes per cell and
+    // field).
     const double np_ = (double)d.total;
+    const double recb = (double)rec_bytes(d.F) + 4.0 * (double)rv_fields(d.F);  // bytes written per particle
     int tm = timing ? timing_begin(timing, s) : -1;
     int t13 = timing ? timing_begin(timing, s) : -1;
-    if (d.rect) {
-        if (pack) hipLaunchKernelGGL((k_tile_bin<true, true>), dim3(cblocks, d.n_snap), dim3(kTBlock), 0, s, a);
-        else hipLaunchKernelGGL((k_tile_bin<true, false>), dim3(cblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+    if (ordered) {
+        launch_order(a, d.max_n, s);
+        if (timing) timing_end(timing, t13, 13, (12.0 + 4.0 * d.F + recb) * np_, s);
     } else {
-        if (pack) hipLaunchKernelGGL((k_tile_bin<false, true>), dim3(cblocks, d.n_snap), dim3(kTBlock), 0, s, a);
-        else hipLaunchKernelGGL((k_tile_bin<false, false>), dim3(cblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+        hipLaunchKernelGGL(k_tile_clear, dim3((all + 255) / 256), dim3(256), 0, s, a);
+        const int64_t bchunk = (int64_t)a.nsub_bin * kTChunk, schunk = (int64_t)a.nsub * kTChunk;
+        const int cblocks = (int)std::max<int64_t>(1, (d.max_n + bchunk - 1) / bchunk);
+        const int sblocks = (int)std::max<int64_t>(1, (d.max_n + schunk - 1) / schunk);
+        if (d.rect) {
+            if (pack) hipLaunchKernelGGL((k_tile_bin<true, true>), dim3(cblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+            else hipLaunchKernelGGL((k_tile_bin<true, false>), dim3(cblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+        } else {
+            if (pack) hipLaunchKernelGGL((k_tile_bin<false, true>), dim3(cblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+            else hipLaunchKernelGGL((k_tile_bin<false, false>), dim3(cblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+        }
+        if (timing) timing_end(timing, t13, 13, (12.0 + 4.0 * d.F + 4.0) * np_, s);
+        int t14 = timing ? timing_begin(timing, s) : -1;
+        hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kTBlock), 0, s, a);
+        if (d.F >= 2) {
+            if (pack) hipLaunchKernelGGL((k_tile_scatter<true, true>), dim3(sblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+            else hipLaunchKernelGGL((k_tile_scatter<true, false>), dim3(sblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+        } else {
+            if (pack) hipLaunchKernelGGL((k_tile_scatter<false, true>), dim3(sblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+            else hipLaunchKernelGGL((k_tile_scatter<false, false>), dim3(sblocks, d.n_snap), dim3(kTBlock), 0, s, a);
+        }
+        if (timing) timing_end(timing, t14, 14, (4.0 + 4.0 * d.F + recb) * np_, s);
     }
-    if (timing) timing_end(timing, t13, 13, (12.0 + 4.0 * d.F + 4.0) * np_, s);
-    int t14 = timing ? timing_begin(timing, s) : -1;
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kTBlock), 0, s, a);
-    if (nt <= kStageMaxTiles && d.F <= 4 && a.nsub == 1) {
-        // staged in LDS: C = 16384 / 8192 / 4096 particles per block at F = 1 / 2..3 / 4
-        const int c = d.F == 1 ? kTChunk : (d.F <= 3 ? kTChunk / 2 : kTChunk / 4);
-        const dim3 g((unsigned)std::max<int64_t>(1, (d.max_n + c - 1) / c), d.n_snap);
-        if (d.F == 1) hipLaunchKernelGGL((k_tile_scatter_staged<kTChunk, 1>), g, dim3(kTBlock), 0, s, a);
-        else if (d.F == 2) hipLaunchKernelGGL((k_tile_scatter_staged<kTChunk / 2, 2>), g, dim3(kTBlock), 0, s, a);
-        else if (d.F == 3) hipLaunchKernelGGL((k_tile_scatter_staged<kTChunk / 2, 3>), g, dim3(kTBlock), 0, s, a);
-        else hipLaunchKernelGGL((k_tile_scatter_staged<kTChunk / 4, 4>), g, dim3(kTBlock), 0, s, a);
-    } else if (d.F >= 2) {
-        if (pack) hipLaunchKernelGGL((k_tile_scatter<true, true>), dim3(sblocks, d.n_snap), dim3(kTBlock), 0, s, a);
-        else hipLaunchKernelGGL((k_tile_scatter<true, false>), dim3(sblocks, d.n_snap), dim3(kTBlock), 0, s, a);
-    } else {
-        if (pack) hipLaunchKernelGGL((k_tile_scatter<false, true>), dim3(sblocks, d.n_snap), dim3(kTBlock), 0, s, a);
-        else hipLaunchKernelGGL((k_tile_scatter<false, false>), dim3(sblocks, d.n_snap), dim3(kTBlock), 0, s, a);
-    }
-    const double recb = (double)rec_bytes(d.F) + 4.0 * (double)rv_fields(d.F);  // bytes written per particle
-    if (timing) timing_end(timing, t14, 14, (4.0 + 4.0 * d.F + recb) * np_, s);
     int t15 = timing ? timing_begin(timing, s) : -1;
-    if (d.F >= 2) hipLaunchKernelGGL(k_tile_accum<true>, dim3(all), dim3(kTBlock), 0, s, a);
-    else hipLaunchKernelGGL(k_tile_accum<false>, dim3(all), dim3(kTBlock), 0, s, a);
+    cgd_status rc;
+    if (!ordered) rc = d.F >= 2 ? launch_accum<true, false, kTBlock>(a, s) : launch_accum<false, false, kTBlock>(a, s);
+    // (a tile of few records is a quarter workgroup's work)
+    else if (np_ < 2048.0 * all) rc = d.F >= 2 ? launch_accum<true, true, 256>(a, s) : launch_accum<false, true, 256>(a, s);
+    else rc = d.F >= 2 ? launch_accum<true, true, kTBlock>(a, s) : launch_accum<false, true, kTBlock>(a, s);
+    if (rc != CGD_OK) return rc;
     if (timing)
         timing_end(timing, t15, 15,
                    recb * np_ + (4.0 * d.F + (d.vcell ? 8.0 : 0.0)) * (double)m->cells * d.n_snap,
