@@ -104,8 +104,8 @@ cgd_status cgd_mesh_create_tet_d(int64_t n_vert, const double* xyz, int64_t n_te
  * volume.  The operator is the finite-volume Laplacian with flux
  * D_f A_f / d_f (e_P - e_N) through each interior face (A_f the face area,
  * d_f the distance between the two cell centres, D_f the harmonic mean of
- * the two cells' diffusivities, 0 if either is 0), solved by
- * preconditioned CG (x0_mode 0).  When the diffusivity factors as
+ * the two cells' diffusivities, 0 if either is 0), solved directly (see
+ * cgd_diffuse) or by preconditioned CG (x0_mode 0).  When the diffusivity factors as
  * D(i,j,k) = Dx(i) Dy(j) Dz(k) (checked to 1e-6 relative at creation; NULL
  * counts) the operator is kept as per-axis factor arrays and applied by
  * stencil sweeps, with a Chebyshev polynomial preconditioner on a scaled
@@ -279,15 +279,19 @@ cgd_status cgd_deposit_noalloc(cgd_mesh m, int64_t n, const float* pos, int32_t 
  *  o:         solver options, nullable (defaults)
  *  st:        host, nullable: iteration counts, residuals, mass before/after
  *
- * With st == NULL a uniform hex grid is solved directly where that is the
- * faster way: the operator is diagonal in the axes' cosine modes, so all
- * n_steps are one multiplication between a forward and an inverse transform
+ * With st == NULL a uniform hex grid, and a rectilinear one whose
+ * diffusivity is one value on a box of cells and 0 elsewhere, is solved
+ * directly where that is the faster way: the operator is diagonal in the
+ * axes' modes (cosines where the cells are even), so all n_steps are one
+ * multiplication between a forward and an inverse transform
  * (float64 arithmetic on float32 vectors; within 1e-7 of the exact solution
  * in relative L2, closer than the CG at its default tolerance).  Statistics,
  * x0_mode != 0, precond = 1, rtol < 5e-7, axes of more than 512 cells other
  * than 1024, one or two steps on long axes that are no power of two, and a
- * max_iter below the CG's own bound are solved by CG, as is a field whose
- * modes overflow float32 or are not finite (then with the CG's status).
+ * max_iter below the CG's own bound are solved by CG, as are axes of uneven
+ * cells that are not their own mirror image and longer than 256 cells (or
+ * periodic), and a field whose modes overflow float32 or are not finite
+ * (then with the CG's status).
  *
  * The convergence test of the CG is read back one chunk of iterations late, so the
  * device always has queued work: the first chunk of a step runs to the

@@ -1,34 +1,57 @@
 // Direct solve of the implicit steps on uniform hex grids (spectral.hip).
 #pragma once
 
+#include <vector>
+
 #include "cgd_internal.h"
 
 namespace cgd {
 
-// Tables of one axis, by its length (device pointers; see k_spec_tables).
+// Tables of one axis (device pointers; see k_spec_tables).
 struct SpecAxis {
     int n = 0;
-    double* lam = nullptr;   // eigenvalues 4 sin^2(pi k / 2n) at the stored positions [n]
+    double* lam = nullptr;   // eigenvalues at the stored positions [n] (cosine axes: 4 sin^2(pi k / 2n))
     double2* tw = nullptr;   // FFT lengths: e^{-2 pi i q / n} [n]
     double2* pw = nullptr;   //    and e^{-i pi k / 2n} [n / 2]
-    double* fe = nullptr;    // dense lengths: packed half-size matrices, forward even and odd modes,
+    double* fe = nullptr;    // dense lengths: packed matrices, forward even and odd modes,
     double* fo = nullptr;
     double* ie = nullptr;    //    inverse even and odd modes
     double* io = nullptr;
 };
 
-// Owned by a mesh, made on its first direct solve.
+// What the transforms need to know of a mesh: the box of cells that diffuse
+// (a uniform grid: all of them; a rectilinear one: those with a diffusivity),
+// its axes of more than one cell, the contiguous one first.  Owned by the
+// mesh, made on its first call.
 struct SpecTables {
+    bool ok = false;          // the transforms apply to this mesh
+    int rank = 0;
+    int n[3] = {1, 1, 1};
+    bool eigen[3] = {};       // modes by eigenvectors (else cosine modes)
+    bool sym[3] = {};         // even and odd modes about the axis's middle
+    bool per[3] = {};
+    double scale[3] = {};     // eigenvalue of A - I over dtau = scale * lam
+    double diag = 0.0;        // bound of the diagonal of (A - I) / dtau
+    std::vector<double> h[3]; // eigen axes: cell widths
+    int64_t off = 0;          // the box's first cell in a field
+    int rows_y = 0;           // rows per plane where rows are not one after the other, else 0
+    int64_t sy = 0, sz = 0;   //    and the strides between rows and planes in a field
+    int64_t pitch = 0;        // else the stride between rows
+    int64_t cells = 0;        // of the box
     double* dev = nullptr;
-    SpecAxis axis[3];  // the axes of more than one cell, the contiguous one first
+    SpecAxis axis[3];
 };
 
 // One pass of transforms along one axis of all fields.
 struct SpecPass {
     const float* in;
     float* out;
-    int64_t cells;        // per field
+    int64_t cells;        // per field of W
+    int64_t fcells;       // per field of the caller's array (the first pass's input, the last one's output)
+    int64_t off, sy, sz, pitch;  // ... where its row r begins: off + r pitch, or (rows_y) off + (r % rows_y) sy + (r / rows_y) sz
+    int32_t rows_y;
     int32_t n;            // length of a line
+    int32_t hm, ho;       // dense: even and odd modes (n and 0: one full matrix)
     int64_t lines;        // lines per field
     int64_t pairs;        // FFT: pairs of lines per field
     int64_t inner;        // strided lines: neighbouring lines (at unit stride),
@@ -57,8 +80,8 @@ struct SpecPass {
 
 // Whether a call on n_fields fields is answered by the direct solve (stats:
 // its statistics are asked for).
-bool spectral_applies(const cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stats);
-// Bytes of the scratch vector W for F fields.
+bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stats);
+// Bytes of the scratch vector W for F fields, where spectral_applies.
 size_t spectral_bytes(const cgd_mesh m, int32_t F);
 // Enqueues all steps of `da` on n_fields fields at da.field [n_fields][cells]
 // (da.F is not used), with W as scratch.  Where a field has a mode that is

@@ -1,4 +1,5 @@
-// Direct solve of the implicit steps on uniform hex grids.
+// Direct solve of the implicit steps on uniform hex grids, and on rectilinear
+// ones whose diffusivity is one value on a box of cells and 0 elsewhere.
 //
 // The zero-flux finite-volume Laplacian of a uniform box is diagonal in the
 // products of the axes' cosine modes (DCT-II): with c_a = dtau / h_a^2 the
@@ -16,16 +17,29 @@
 // float32: what an iterate of the CG holds, rounded four times instead of
 // twice per iteration.
 //
+// Rectilinear grids: with one diffusivity d on the cells that diffuse at all
+// (the product of per-axis factors that are constant on one range of the axis
+// and 0 elsewhere; faces to cells of diffusivity 0 carry nothing), the
+// operator of that box is I + dtau d sum_a M_a^-1 K_a, and the modes of an
+// axis are the eigenvectors of its tridiagonal M_a^-1/2 K_a M_a^-1/2 (of the
+// cyclic one on a periodic axis), scaled by sqrt(h) on the way in and
+// 1 / sqrt(h) on the way out: cosines where the widths are equal between
+// zero-flux ends.  Cells outside the box keep their values.
+//
 // A transform of length 128, 256, 512 or 1024 runs as a complex FFT of two
-// lines at once (k_fft); any other length up to 512 as two half-size matrix
-// products on the float64 matrix cores, the even modes from x[m] + x[N-1-m]
-// and the odd ones from x[m] - x[N-1-m] (k_dense).
+// lines at once (k_fft); any other length up to 512 (and eigenvector modes) as
+// two half-size matrix products on the float64 matrix cores, the even modes
+// from x[m] + x[N-1-m] and the odd ones from x[m] - x[N-1-m] (k_dense): every
+// axis that is its own mirror image has only such modes; one that is not
+// takes one full-size product.
 #include <math.h>
 
 #include <stdlib.h>
 
 #include <algorithm>
+#include <cmath>
 #include <new>
+#include <string>
 
 #include "cg_common.h"
 #include "spectral.h"
@@ -132,6 +146,13 @@ __device__ __forceinline__ void clear_bad(const SpecPass& a) {
 }
 __device__ __forceinline__ bool is_bad(const SpecPass& a) {
     return __hip_atomic_load(a.bad + blockIdx.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
+// Where row r of the caller's array begins.
+__device__ __forceinline__ int64_t field_row(const SpecPass& a, int64_t r) {
+    if (!a.rows_y) return a.off + r * a.pitch;
+    const int64_t z = r / a.rows_y;
+    return a.off + (r - z * a.rows_y) * a.sy + z * a.sz;
 }
 
 // ------------------------------------------------------------------- FFT
@@ -322,19 +343,22 @@ __global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
     const int p = XK ? threadIdx.x / T : threadIdx.x % P;
     const int64_t q = (int64_t)blockIdx.x * P + p;
     const bool live = q < a.pairs;
-    const float* __restrict__ in = a.in + (size_t)blockIdx.y * a.cells;
-    float* __restrict__ out = a.out + (size_t)blockIdx.y * a.cells;
+    const float* __restrict__ in = a.in + (size_t)blockIdx.y * (XK && MODE == 0 ? a.fcells : a.cells);
+    float* __restrict__ out = a.out + (size_t)blockIdx.y * (XK && MODE == 1 ? a.fcells : a.cells);
     const double2* __restrict__ tw = a.tw;
     const double2* __restrict__ pw = a.pw;
     const double sf = a.sf, sf0 = a.sf0, si = a.si, si0 = a.si0;
     Cd v[kE];
     bool two;
     int64_t base, base2, line;
+    int64_t fbase = 0, fbase2 = 0;  // XK: the same rows in the caller's array
     if (XK) {
         line = 2 * q;
         two = live && line + 1 < a.lines;
         base = (live ? line : 0) * N;
         base2 = two ? base + N : base;
+        fbase = field_row(a, live ? line : 0);
+        fbase2 = two ? field_row(a, line + 1) : fbase;
     } else {
         const int64_t qq = live ? q : 0;
         const int64_t o = qq / a.inner_pairs;
@@ -353,15 +377,15 @@ __global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
             if (a.vec2) {
 #pragma unroll
                 for (int j = 0; j < H; ++j) {
-                    xa[j] = *reinterpret_cast<const float2*>(in + base + 2 * (t + T * j));
-                    xb[j] = *reinterpret_cast<const float2*>(in + base2 + 2 * (t + T * j));
+                    xa[j] = *reinterpret_cast<const float2*>(in + fbase + 2 * (t + T * j));
+                    xb[j] = *reinterpret_cast<const float2*>(in + fbase2 + 2 * (t + T * j));
                 }
             } else {
 #pragma unroll
                 for (int j = 0; j < H; ++j) {
                     const int e = 2 * (t + T * j);
-                    xa[j] = make_float2(in[base + e], in[base + e + 1]);
-                    xb[j] = make_float2(in[base2 + e], in[base2 + e + 1]);
+                    xa[j] = make_float2(in[fbase + e], in[fbase + e + 1]);
+                    xb[j] = make_float2(in[fbase2 + e], in[fbase2 + e + 1]);
                 }
             }
 #pragma unroll
@@ -494,16 +518,16 @@ __global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
             const float2 xa = make_float2((float)v[j].y, __shfl_xor((float)v[kE - 1 - j].y, T - 1));
             const float2 xb = make_float2((float)v[j].x, __shfl_xor((float)v[kE - 1 - j].x, T - 1));
             if (a.vec2) {
-                if (live) *reinterpret_cast<float2*>(out + base + e) = xa;
-                if (two) *reinterpret_cast<float2*>(out + base2 + e) = xb;
+                if (live) *reinterpret_cast<float2*>(out + fbase + e) = xa;
+                if (two) *reinterpret_cast<float2*>(out + fbase2 + e) = xb;
             } else {
                 if (live) {
-                    out[base + e] = xa.x;
-                    out[base + e + 1] = xa.y;
+                    out[fbase + e] = xa.x;
+                    out[fbase + e + 1] = xa.y;
                 }
                 if (two) {
-                    out[base2 + e] = xb.x;
-                    out[base2 + e + 1] = xb.y;
+                    out[fbase2 + e] = xb.x;
+                    out[fbase2 + e + 1] = xb.y;
                 }
             }
         }
@@ -544,20 +568,20 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     extern __shared__ double shd[];
     constexpr int TLP = XK ? kTL + 1 : kTL;
     constexpr int CT = SPLIT ? 1 : 2;
-    const int n = a.n, hm = (n + 1) / 2, ho = n / 2, mt = (hm + 15) / 16, rows = 16 * mt;
+    const int n = a.n, hm = a.hm, ho = a.ho, mt = (hm + 15) / 16, rows = 16 * mt;
     double* E = shd;
     double* O = shd + (size_t)rows * TLP;
     if (MODE == 1 && a.last && is_bad(a)) return;
     if (MODE == 0 && a.first) clear_bad(a);
-    const float* __restrict__ in = a.in + (size_t)blockIdx.y * a.cells;
-    float* __restrict__ out = a.out + (size_t)blockIdx.y * a.cells;
+    const float* __restrict__ in = a.in + (size_t)blockIdx.y * (XK && MODE == 0 ? a.fcells : a.cells);
+    float* __restrict__ out = a.out + (size_t)blockIdx.y * (XK && MODE == 1 ? a.fcells : a.cells);
     const int64_t l0 = (int64_t)blockIdx.x * kTL;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int tile = SPLIT ? wave >> 1 : wave, c0 = SPLIT ? (wave & 1) * 16 : 0;
     const bool work = tile < mt;  // (a block of few tiles has waves that only move data)
     const int64_t es = a.estride;
-    auto base_of = [&](int64_t l) -> int64_t {
-        if (XK) return l * n;
+    auto base_of = [&](int64_t l, bool field) -> int64_t {
+        if (XK) return field ? field_row(a, l) : l * n;
         const int64_t o = l / a.inner;
         return o * a.ostride + (l - o * a.inner);
     };
@@ -586,12 +610,12 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     if (XK) {
         for (int line = wave; line < kTL; line += nw) {
             const bool ok = l0 + line < a.lines;
-            fill(in + (ok ? base_of(l0 + line) : 0), 1, lane, 64, line, ok);
+            fill(in + (ok ? base_of(l0 + line, MODE == 0) : (MODE == 0 ? a.off : 0)), 1, lane, 64, line, ok);
         }
     } else {
         const int line = threadIdx.x % kTL;
         const bool ok = l0 + line < a.lines;
-        fill(in + (ok ? base_of(l0 + line) : 0), es, threadIdx.x / kTL, 2 * nw, line, ok);
+        fill(in + (ok ? base_of(l0 + line, false) : 0), es, threadIdx.x / kTL, 2 * nw, line, ok);
     }
     __syncthreads();
     v4d ae[CT], ao[CT];
@@ -611,6 +635,7 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
         }
         for (int k = 0; k < mt; ++k) {
             double ne[4], no[4];
+            const bool odd = ho > 0;
             const size_t nk = (size_t)std::min(k + 1, mt - 1) * 256;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -625,10 +650,10 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
                     const double de = E[o], dd = O[o];
                     if (XK) {
                         ae[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(de, ce[i], ae[c], 0, 0, 0);
-                        ao[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(dd, co[i], ao[c], 0, 0, 0);
+                        if (odd) ao[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(dd, co[i], ao[c], 0, 0, 0);
                     } else {
                         ae[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(ce[i], de, ae[c], 0, 0, 0);
-                        ao[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(co[i], dd, ao[c], 0, 0, 0);
+                        if (odd) ao[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(co[i], dd, ao[c], 0, 0, 0);
                     }
                 }
             }
@@ -648,7 +673,7 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
                 const int k = tile * 16 + (XK ? (lane & 15) : d_row(r, lane));
                 const int line = c0 + c * 16 + (XK ? d_row(r, lane) : (lane & 15));
                 if (l0 + line >= a.lines || k >= hm) continue;
-                float* dst = out + base_of(l0 + line);
+                float* dst = out + base_of(l0 + line, false);
                 dst[es * k] = (float)ae[c][r];
                 if (k < ho) dst[es * (hm + k)] = (float)ao[c][r];
             }
@@ -693,7 +718,7 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
             const int m = tile * 16 + (XK ? (lane & 15) : d_row(r, lane));
             const int line = c0 + c * 16 + (XK ? d_row(r, lane) : (lane & 15));
             if (l0 + line >= a.lines || m >= hm) continue;
-            float* dst = out + base_of(l0 + line);
+            float* dst = out + base_of(l0 + line, true);
             dst[es * m] = (float)(ae[c][r] + ao[c][r]);
             if (m < ho) dst[es * (n - 1 - m)] = (float)(ae[c][r] - ao[c][r]);
         }
@@ -750,8 +775,8 @@ bool fft_length(int n) { return n == 128 || n == 256 || n == 512 || n == 1024; }
 
 // Doubles of one packed half-size matrix: tiles of 16 rows, 4 fragments of 64
 // per 16 reduction rows.
-size_t dense_fragment(int n) {
-    const size_t mt = ((n + 1) / 2 + 15) / 16;
+size_t dense_fragment(int n, bool sym = true) {
+    const size_t mt = ((sym ? (n + 1) / 2 : n) + 15) / 16;
     return mt * 4 * mt * 64;
 }
 
@@ -769,14 +794,14 @@ void launch_fft(const SpecPass& a, int F, hipStream_t s) {
 
 template <int MODE, bool XK>
 cgd_status launch_pass(const SpecPass& a, int F, hipStream_t s) {
-    switch (a.n) {
+    switch (a.tw ? a.n : 0) {
         case 128: launch_fft<128, MODE, XK>(a, F, s); return CGD_OK;
         case 256: launch_fft<256, MODE, XK>(a, F, s); return CGD_OK;
         case 512: launch_fft<512, MODE, XK>(a, F, s); return CGD_OK;
         case 1024: launch_fft<1024, MODE, XK>(a, F, s); return CGD_OK;
         default: break;
     }
-    const int mt = ((a.n + 1) / 2 + 15) / 16;
+    const int mt = (a.hm + 15) / 16;
     const size_t lds = (size_t)2 * mt * 16 * (XK ? kTL + 1 : kTL) * sizeof(double);
     const dim3 grid((unsigned)((a.lines + kTL - 1) / kTL), F);
     auto go = [&](auto kern, int nw) -> cgd_status {
@@ -791,29 +816,195 @@ cgd_status launch_pass(const SpecPass& a, int F, hipStream_t s) {
     return go(k_dense<MODE, XK, false>, std::max(4, mt));
 }
 
-// The axes of more than one cell, contiguous one first.
-int axes_of(const HexGeom& g, int* n, double* h) {
-    const int32_t nn[3] = {g.nx, g.ny, g.nz};
-    int rank = 0;
-    for (int a = 0; a < 3; ++a)
-        if (nn[a] > 1) {
-            n[rank] = nn[a];
-            h[rank++] = g.h[a];
+// Eigenvalues d and eigenvectors (z[k], one array per eigenvalue) of the
+// symmetric tridiagonal matrix with diagonal d and off-diagonal e: QR steps
+// with Wilkinson's shift, each a chase of the bulge that the first rotation
+// makes (the method of Golub and Van Loan, "Matrix Computations", 8.3).  In
+// the basis q1 = c u + s v, q2 = -s u + c v of a rotation the 2 x 2 block
+// (a, b, g) has the diagonal c^2 a + 2 c s b + s^2 g, s^2 a - 2 c s b + c^2 g
+// and the off-diagonal (c^2 - s^2) b + c s (g - a).
+void tridiagonal_modes(std::vector<double>& d, std::vector<double> e, std::vector<std::vector<double>>& z) {
+    const int n = (int)d.size();
+    z.assign(n, std::vector<double>(n, 0.0));
+    for (int k = 0; k < n; ++k) z[k][k] = 1.0;
+    e.resize(n, 0.0);
+    const double eps = 2.3e-16;
+    int hi = n - 1;
+    for (int64_t guard = 0; hi > 0 && guard < 60 * (int64_t)n; ++guard) {
+        auto split = [&](int k) { return std::fabs(e[k]) <= eps * (std::fabs(d[k]) + std::fabs(d[k + 1])); };
+        if (split(hi - 1)) {
+            --hi;
+            continue;
         }
-    return rank;
+        int lo = hi - 1;
+        while (lo > 0 && !split(lo - 1)) --lo;
+        const double half = 0.5 * (d[hi - 1] - d[hi]), b = e[hi - 1];
+        const double mu = d[hi] - b * b / (half + std::copysign(std::hypot(half, b), half));
+        double x = d[lo] - mu, y = e[lo];
+        for (int k = lo; k < hi; ++k) {
+            const double r = std::hypot(x, y);
+            if (r == 0.0) break;
+            const double c = x / r, s = y / r;
+            const double p = d[k], q = e[k], g = d[k + 1];
+            d[k] = c * c * p + 2.0 * c * s * q + s * s * g;
+            d[k + 1] = s * s * p - 2.0 * c * s * q + c * c * g;
+            e[k] = (c * c - s * s) * q + c * s * (g - p);
+            if (k > lo) e[k - 1] = r;
+            if (k + 1 < hi) {
+                y = s * e[k + 1];
+                e[k + 1] *= c;
+            }
+            x = e[k];
+            double* u = z[k].data();
+            double* v = z[k + 1].data();
+            for (int i = 0; i < n; ++i) {
+                const double ui = u[i], vi = v[i];
+                u[i] = c * ui + s * vi;
+                v[i] = c * vi - s * ui;
+            }
+        }
+    }
+}
+
+// The eigenvector axis a of t: eigenvalues in stored order, and the packed
+// matrices (forward even, odd, inverse even, odd).
+void eigen_axis(const SpecTables& t, int a, std::vector<double>& lam, std::vector<double>& mats) {
+    const std::vector<double>& h = t.h[a];
+    const int n = t.n[a];
+    const bool sym = t.sym[a];
+    const int hm = sym ? (n + 1) / 2 : n, ho = sym ? n / 2 : 0, mt = (hm + 15) / 16;
+    std::vector<double> g(n + 1, 0.0), s(n), o(n, 0.0);
+    for (int i = 1; i < n; ++i) g[i] = 2.0 / (h[i - 1] + h[i]);
+    double oper = 0.0;
+    if (t.per[a]) {
+        g[0] = g[n] = 2.0 / (h[0] + h[n - 1]);
+        oper = -g[0] / std::sqrt(h[0] * h[n - 1]);
+    }
+    for (int i = 0; i < n; ++i) s[i] = (g[i] + g[i + 1]) / h[i];
+    for (int i = 0; i + 1 < n; ++i) o[i] = -g[i + 1] / std::sqrt(h[i] * h[i + 1]);
+    lam.assign(n, 0.0);
+    const size_t frag = (size_t)mt * 4 * mt * 64;
+    mats.assign(4 * frag, 0.0);
+    for (int odd = 0; odd < (ho ? 2 : 1); ++odd) {
+        // the half of the modes with x[n-1-m] = +-x[m], in the coordinates of
+        // m < ho (times 1 / sqrt 2 in full) and, even ones of an odd n, the
+        // middle cell; sign * o for the neighbour that is the mirror image
+        const int nn = odd ? ho : hm;
+        std::vector<double> d(s.begin(), s.begin() + nn), e(o.begin(), o.begin() + nn);
+        const double sg = odd ? -1.0 : 1.0;
+        if (sym) {
+            d[0] += n > 1 ? sg * oper : 0.0;
+            if (n % 2 == 0) d[nn - 1] += sg * o[ho - 1];
+            else if (!odd && nn > 1) e[nn - 2] *= std::sqrt(2.0);
+        }
+        std::vector<std::vector<double>> z;
+        tridiagonal_modes(d, e, z);
+        double* f = mats.data() + (odd ? frag : 0);
+        double* inv = mats.data() + (odd ? 3 : 2) * frag;
+        for (int k = 0; k < nn; ++k) {
+            lam[odd ? hm + k : k] = d[k];
+            for (int m = 0; m < nn; ++m) {
+                const double v = z[k][m] * (sym && m < ho ? std::sqrt(0.5) : 1.0);
+                // entry (row, col) of a packed matrix
+                auto at = [&](int row, int col) {
+                    return (((size_t)(row / 16) * 4 * mt + col / 4) * 64) + (size_t)(col % 4) * 16 + row % 16;
+                };
+                f[at(k, m)] = v * std::sqrt(h[m]);
+                inv[at(m, k)] = v / std::sqrt(h[m]);
+            }
+        }
+    }
 }
 
 }  // namespace
 
+// The cells that diffuse, as a box of axes the transforms take.
+static void analyse_grid(const cgd_mesh m, SpecTables* t) {
+    const HexGeom& g = m->hex;
+    const int nn[3] = {g.nx, g.ny, g.nz};
+    int i0[3] = {0, 0, 0}, len[3] = {nn[0], nn[1], nn[2]};
+    double d = 1.0;
+    if (m->kind == 2) {
+        const RectOp* ro = m->rop;
+        for (int a = 0; a < 3; ++a) {
+            const std::vector<double>& f = ro->fac[a];
+            int lo = 0, hi = nn[a];
+            while (lo < hi && !(f[lo] > 0.0)) ++lo;
+            while (hi > lo && !(f[hi - 1] > 0.0)) --hi;
+            if (lo == hi) return;  // nothing diffuses
+            for (int i = lo; i < hi; ++i)
+                if (std::fabs(f[i] - f[lo]) > 1e-12 * f[lo]) return;
+            d *= f[lo];
+            i0[a] = lo;
+            len[a] = hi - lo;
+        }
+    }
+    int64_t st = 1;
+    for (int a = 0; a < 3; ++a) {
+        if (m->kind == 0 || a > 0) {
+            if (len[a] == 1) continue;
+        } else if (len[0] < 2) {
+            return;
+        }
+        const int r = t->rank++, n = len[a];
+        t->n[r] = n;
+        bool even = true, sym = true;
+        double diag = 0.0, mean = g.h[a];
+        if (m->kind == 2) {
+            const RectOp* ro = m->rop;
+            const std::vector<double> h(ro->h[a].begin() + i0[a], ro->h[a].begin() + i0[a] + n);
+            mean = 0.0;
+            for (double w : h) mean += w / n;
+            for (int i = 0; i < n; ++i) {
+                even = even && std::fabs(h[i] - mean) <= 1e-9 * mean;
+                sym = sym && std::fabs(h[i] - h[n - 1 - i]) <= 1e-9 * h[i];
+                const double w0 = h[i > 0 ? i - 1 : n - 1], w1 = h[i + 1 < n ? i + 1 : 0];
+                diag = std::max(diag, (2.0 / (w0 + h[i]) + 2.0 / (h[i] + w1)) / h[i]);
+            }
+            t->per[r] = (ro->per >> a & 1) && n == nn[a];
+            t->eigen[r] = !even || t->per[r];
+            if (t->eigen[r]) t->h[r] = h;
+        } else {
+            diag = 2.0 / (mean * mean);
+        }
+        t->sym[r] = sym;
+        t->scale[r] = t->eigen[r] ? d : d / (mean * mean);
+        t->diag += d * diag;
+        if (!sym && (t->per[r] || n > 256)) return;
+        if (n > 512 && (t->eigen[r] || !fft_length(n))) return;
+        st *= n;
+    }
+    if (t->rank < 2) return;
+    t->cells = st;
+    t->off = i0[0] + (int64_t)nn[0] * (i0[1] + (int64_t)nn[1] * i0[2]);
+    t->pitch = m->kind == 0 ? t->n[0] : nn[0];
+    if (m->kind == 2 && len[1] != nn[1] && len[2] > 1) {
+        t->rows_y = len[1];
+        t->sy = nn[0];
+        t->sz = (int64_t)nn[0] * nn[1];
+    }
+    t->ok = true;
+}
+
+static const SpecTables* grid_of(cgd_mesh m) {
+    if (!m->spec) {
+        SpecTables* t = new (std::nothrow) SpecTables();
+        if (!t) return nullptr;
+        analyse_grid(m, t);
+        m->spec = t;
+    }
+    return m->spec;
+}
+
 // Fields per group: their vector W (with the field itself about 256 MB) stays
 // in the memory-side cache between the passes.
 static int fields_per_group(const cgd_mesh m, int F) {
-    const int64_t most = (int64_t)128 * 1024 * 1024 / (m->cells * (int64_t)sizeof(float));
+    const int64_t most = (int64_t)128 * 1024 * 1024 / (m->spec->cells * (int64_t)sizeof(float));
     return (int)std::max<int64_t>(1, std::min<int64_t>(F, most));
 }
 
 size_t spectral_bytes(const cgd_mesh m, int32_t F) {
-    return (size_t)fields_per_group(m, F) * m->cells * sizeof(float);
+    return (size_t)fields_per_group(m, F) * m->spec->cells * sizeof(float);
 }
 
 // The direct solve stands in for the CG where nothing asks for the CG itself:
@@ -829,24 +1020,21 @@ size_t spectral_bytes(const cgd_mesh m, int32_t F) {
 // 50 at 147, 33 at 93), the CG 25 ps per cell and step at its best
 // (256 x 256 x 512, dtau / h^2 = 1) and 50 us and more per step in launches
 // on the smallest grids, so only one or two steps on lengths of hundreds that
-// are no FFT lengths are left to the CG.
-bool spectral_applies(const cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stats) {
-    if (m->kind != 0 || stats || da.x0_mode != 0 || da.precond != 0 || da.rtol < 5e-7) return false;
+// are no FFT lengths are left to the CG.  Rectilinear grids: the CG takes 136
+// ps per cell and step (128 x 128 x 256, diffusivity 0 in the outer layers).
+bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stats) {
+    if (stats || da.x0_mode != 0 || da.precond != 0 || da.rtol < 5e-7) return false;
+    if (m->kind == 2 ? !m->rop || getenv("CGD_RECT_SLOTS") : m->kind != 0) return false;
     if (getenv("CGD_NO_DIRECT") || getenv("CGD_HEX_PRECOND_DEG")) return false;
-    int n[3];
-    double h[3];
-    const int rank = axes_of(m->hex, n, h);
-    if (rank < 2) return false;
+    const SpecTables* t = grid_of(m);
+    if (!t || !t->ok) return false;
     const double dtau = da.bandwidth * da.bandwidth / 4.0 / da.n_steps * (da.scheme == 1 ? 0.5 : 1.0);
-    double k = 1.0, ps = 0.0;
-    for (int a = 0; a < rank; ++a) {
-        if (n[a] > 512 && !fft_length(n[a])) return false;
-        k += 4.0 * dtau / (h[a] * h[a]);
-        ps += 2.0 * (fft_length(n[a]) ? 2.0 : 2.5 + 0.022 * n[a]);
-    }
+    double ps = 0.0;
+    for (int a = 0; a < t->rank; ++a)
+        ps += 2.0 * (!t->eigen[a] && fft_length(t->n[a]) ? 2.0 : 2.5 + (t->sym[a] ? 0.022 : 0.044) * t->n[a]);
     const double mcells = 1e-6 * (double)m->cells * n_fields;
-    if (25.0 + mcells * ps > da.n_steps * (50.0 + mcells * 25.0)) return false;
-    const double r = sqrt(k);
+    if (25.0 + mcells * ps > da.n_steps * (50.0 + mcells * (m->kind == 0 ? 25.0 : 100.0))) return false;
+    const double r = sqrt(1.0 + 2.0 * dtau * t->diag);
     return 0.5 * r * log(2.0 * r / std::min(da.rtol, 1.0)) + 1.0 <= (double)da.max_iter;
 }
 
@@ -858,52 +1046,64 @@ void destroy_spectral(cgd_mesh m) {
 }
 
 static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
-    if (m->spec) return CGD_OK;
-    int n[3];
-    double h[3];
-    const int rank = axes_of(m->hex, n, h);
-    size_t total = 0;
-    for (int a = 0; a < rank; ++a) total += table_doubles(n[a]);
-    SpecTables* t = new (std::nothrow) SpecTables();
-    if (!t) return CGD_E_NOMEM;
+    SpecTables* t = m->spec;
+    if (t->dev) return CGD_OK;
+    size_t off[3], total = 0;
+    for (int a = 0; a < t->rank; ++a) {
+        off[a] = total;
+        total += t->eigen[a] ? (((size_t)t->n[a] + 1) & ~(size_t)1) + 4 * dense_fragment(t->n[a], t->sym[a])
+                             : table_doubles(t->n[a]);
+    }
     void* dev = nullptr;
     if (hipMalloc(&dev, total * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
-        delete t;
         set_error("allocation of the transform tables failed");
         return CGD_E_NOMEM;
     }
-    t->dev = static_cast<double*>(dev);
-    m->spec = t;
-    double* p = t->dev;
-    for (int a = 0; a < rank; ++a) {
-        for (int b = 0; b < a; ++b)
-            if (n[b] == n[a]) t->axis[a] = t->axis[b];
+    hipError_t e = hipSuccess;
+    for (int a = 0; a < t->rank && e == hipSuccess; ++a) {
         SpecAxis& x = t->axis[a];
-        if (x.n) continue;
-        x.n = n[a];
+        double* p = static_cast<double*>(dev) + off[a];
+        const int n = t->n[a];
+        x = SpecAxis{};
+        x.n = n;
         x.lam = p;
-        const bool fft = fft_length(n[a]);
+        const bool fft = !t->eigen[a] && fft_length(n);
         if (fft) {
-            x.tw = reinterpret_cast<double2*>(p + n[a]);
-            x.pw = x.tw + n[a];
+            x.tw = reinterpret_cast<double2*>(p + n);
+            x.pw = x.tw + n;
         } else {
-            const size_t frag = dense_fragment(n[a]);
-            x.fe = p + ((n[a] + 1) & ~1);
+            const size_t frag = dense_fragment(n, t->sym[a]);
+            x.fe = p + ((n + 1) & ~1);
             x.fo = x.fe + frag;
             x.ie = x.fo + frag;
             x.io = x.ie + frag;
         }
-        hipLaunchKernelGGL(k_spec_tables, dim3(64), dim3(256), 0, s, n[a], (int)fft, x.lam, x.tw, x.pw, x.fe, x.fo,
-                           x.ie, x.io);
-        p += table_doubles(n[a]);
+        if (t->eigen[a]) {
+            try {
+                std::vector<double> lam, mats;
+                eigen_axis(*t, a, lam, mats);
+                e = hipMemcpyAsync(x.lam, lam.data(), lam.size() * sizeof(double), hipMemcpyHostToDevice, s);
+                if (e == hipSuccess)
+                    e = hipMemcpyAsync(x.fe, mats.data(), mats.size() * sizeof(double), hipMemcpyHostToDevice, s);
+                if (e == hipSuccess) e = hipStreamSynchronize(s);  // the vectors go
+            } catch (const std::bad_alloc&) {
+                (void)hipFree(dev);
+                set_error("transform tables: host allocation failed");
+                return CGD_E_NOMEM;
+            }
+        } else {
+            hipLaunchKernelGGL(k_spec_tables, dim3(64), dim3(256), 0, s, n, (int)fft, x.lam, x.tw, x.pw, x.fe, x.fo, x.ie,
+                               x.io);
+            e = hipGetLastError();
+        }
     }
-    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
-        destroy_spectral(m);
+        (void)hipFree(dev);
         set_error(std::string("transform tables: ") + hipGetErrorString(e));
         return CGD_E_HIP;
     }
+    t->dev = static_cast<double*>(dev);
     return CGD_OK;
 }
 
@@ -911,18 +1111,27 @@ cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, flo
                             hipStream_t s) {
     cgd_status rc = spectral_tables(m, s);
     if (rc != CGD_OK) return rc;
-    int n[3];
-    double h[3], c[3];
-    const int rank = axes_of(m->hex, n, h);
+    const SpecTables& tb = *m->spec;
+    const int rank = tb.rank;
+    const int* n = tb.n;
+    double c[3];
     const double dtau = da.bandwidth * da.bandwidth / 4.0 / da.n_steps * (da.scheme == 1 ? 0.5 : 1.0);
-    for (int a = 0; a < rank; ++a) c[a] = dtau / (h[a] * h[a]);
+    for (int a = 0; a < rank; ++a) c[a] = dtau * tb.scale[a];
     SpecPass pass[3];
     for (int ax = 0; ax < rank; ++ax) {
         SpecPass& p = pass[ax];
         p = SpecPass{};
-        const SpecAxis& t = m->spec->axis[ax];
+        const SpecAxis& t = tb.axis[ax];
         const double nn = n[ax];
-        p.cells = m->cells;
+        p.cells = tb.cells;
+        p.fcells = m->cells;
+        p.off = tb.off;
+        p.sy = tb.sy;
+        p.sz = tb.sz;
+        p.pitch = tb.pitch;
+        p.rows_y = tb.rows_y;
+        p.hm = tb.sym[ax] ? (n[ax] + 1) / 2 : n[ax];
+        p.ho = tb.sym[ax] ? n[ax] / 2 : 0;
         p.n_steps = da.n_steps;
         p.cn = da.scheme == 1;
         p.n = n[ax];
@@ -936,7 +1145,7 @@ cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, flo
         p.sf0 = sqrt(1.0 / nn);
         p.si = sqrt(0.5 / nn);
         p.si0 = sqrt(1.0 / nn);
-        p.lines = m->cells / n[ax];
+        p.lines = tb.cells / n[ax];
         int64_t st = 1;
         for (int b = 0; b < ax; ++b) st *= n[b];
         p.estride = st;
@@ -969,7 +1178,8 @@ cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, flo
         SpecPass x = pass[0];
         x.in = field;
         x.first = 1;
-        x.vec2 = reinterpret_cast<uintptr_t>(field) % 8 == 0;  // (FFT lengths are even, so every row is aligned)
+        x.vec2 = reinterpret_cast<uintptr_t>(field) % 8 == 0 && tb.off % 2 == 0 &&
+                 (tb.rows_y ? (tb.sy | tb.sz) % 2 == 0 : tb.pitch % 2 == 0) && (nf == 1 || m->cells % 2 == 0);
         rc = launch_pass<0, true>(x, nf, s);
         if (rc == CGD_OK && rank == 3) rc = launch_pass<0, false>(pass[1], nf, s);
         if (rc == CGD_OK) rc = launch_pass<2, false>(z, nf, s);
@@ -1009,7 +1219,7 @@ cgd_status diffuse_spectral(cgd_mesh m, const DiffuseArgs& da, hipStream_t s) {
         DiffuseArgs d1 = da;
         d1.F = 1;
         d1.field = da.field + (size_t)todo[i] * m->cells;
-        rc = diffuse_hex(m, d1, nullptr, s);
+        rc = m->kind == 0 ? diffuse_hex(m, d1, nullptr, s) : diffuse_tet(m, d1, nullptr, s);
         if (rc < 0 && rc != CGD_E_BREAKDOWN) return rc;
         if (rc == CGD_E_BREAKDOWN || worst == CGD_OK) worst = rc;
     }
