@@ -119,15 +119,17 @@ __device__ __forceinline__ void dft<16>(Cd* v) {
         }
 }
 
-// The gain of a mode whose eigenvalue of A is 1 + mu.
+// The gain of a mode whose eigenvalue of A is 1 + mu.  (Two or four modes
+// side by side overlap these chains but spill: 129 us -> 157 for the gain
+// pass of the dense bed.)
 __device__ __forceinline__ double mode_gain(double mu, int n, int cn) {
     const double d = 1.0 + mu;
     double r = __builtin_amdgcn_rcp(d);  // 4.6e-8 off at most (measured over 1 .. 1e6)
     r = fma(r, fma(-d, r, 1.0), r);      // 2.1e-15
-    double base = cn ? fma(2.0, r, -1.0) : r;
+    if (cn) r = fma(2.0, r, -1.0);
     double g = 1.0;
-    for (int e = n;; base *= base) {
-        if (e & 1) g *= base;
+    for (int e = n;; r *= r) {
+        if (e & 1) g *= r;
         e >>= 1;
         if (!e) break;
     }
@@ -161,22 +163,31 @@ template <int N>
 struct FftCfg;
 template <>
 struct FftCfg<128> {
-    static constexpr int R1 = 16, R2 = 8, R3 = 1, P = 32;
+    static constexpr int R1 = 16, R2 = 8, R3 = 1;
 };
 template <>
 struct FftCfg<256> {
-    static constexpr int R1 = 16, R2 = 16, R3 = 1, P = 16;
+    static constexpr int R1 = 16, R2 = 16, R3 = 1;
 };
 template <>
 struct FftCfg<512> {
-    static constexpr int R1 = 8, R2 = 8, R3 = 8, P = 16;
+    static constexpr int R1 = 8, R2 = 8, R3 = 8;
 };
 template <>
 struct FftCfg<1024> {
-    static constexpr int R1 = 16, R2 = 8, R3 = 8, P = 16;
+    static constexpr int R1 = 16, R2 = 8, R3 = 8;
 };
 
 constexpr int kE = 16;  // points of a line held by a thread
+
+// Pairs of lines per block: small blocks, whose barriers wait for few waves
+// (the gain pass at 512: 131 us with 16 pairs on the dense bed, 120 with 8,
+// 115 with the two blocks that share its cache lines on one XCD; contiguous
+// lines at 128: 60 us with 32 pairs on 16 fields of 128^3, 53 with 16), but
+// whole 128-byte rows where a block is small anyway (strided lines at 128: 14
+// us against 17 on 128 x 115 x 256).
+template <int N, bool XK>
+constexpr int fft_pairs() { return N >= 512 ? 8 : (N == 256 || XK ? 16 : 32); }
 
 // LDS slot of point m of pair p.  Strided lines: the P pairs of a point side
 // by side (a wave's 16 consecutive pairs read 128 bytes).  Contiguous lines:
@@ -188,7 +199,7 @@ __device__ __forceinline__ int slot(int m, int p) {
 }
 template <int N, bool XK>
 constexpr int fft_lds_doubles() {
-    return FftCfg<N>::P * (XK ? N + N / 16 : N);
+    return fft_pairs<N, XK>() * (XK ? N + N / 16 : N);
 }
 
 // One Stockham stage of radix R over what the threads hold (slot j of a
@@ -282,7 +293,7 @@ __device__ __forceinline__ void to_pairs(Cd* v, double* sh, int t, int p) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < H; ++i) {
-        const int k = t + T * i, n = k ? N - k : N / 2;
+        const int n = i == 0 && t == 0 ? N / 2 : N - (t + T * i);
         v[H + i] = {sh[slot<N, P, XK>(n - N / 2, p)], sh[slot<N, P, XK>(n, p)]};
     }
 }
@@ -293,7 +304,7 @@ __device__ __forceinline__ void from_pairs(Cd* v, double* sh, int t, int p) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < H; ++i) {
-        const int k = t + T * i, n = k ? N - k : N / 2;
+        const int n = i == 0 && t == 0 ? N / 2 : N - (t + T * i);
         sh[slot<N, P, XK>(n - N / 2, p)] = v[H + i].x;
         sh[slot<N, P, XK>(n, p)] = v[H + i].y;
     }
@@ -332,16 +343,25 @@ __device__ __forceinline__ void pair_of(v4d m, Cd w, bool k0, double s, double s
 
 // MODE 0 forward, 1 inverse, 2 forward + gain + inverse.  XK: lines
 // contiguous in memory (two rows per pair), else strided (two neighbouring
-// lines per pair, P pairs per block).
+// lines per pair, P pairs per block).  Bound by float64 instructions and the
+// LDS exchanges' barriers together; loads and stores walk one pointer per
+// stream and the special modes (0 and N / 2) are a test on thread 0's first
+// point, where offsets and tests per point took registers and issue slots.
+// 256 x 256 x 512, one field (268 MB in and out, 38 us at 7.0 TB/s): forward
+// and back along x 59 and 54 us (59 and 60 before), y 53 and 49 (56 and 88),
+// the gain pass along z 114 (131).
 template <int N, int MODE, bool XK>
-__global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
-    constexpr int T = N / kE, P = FftCfg<N>::P, H = kE / 2;
+__global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPass a) {
+    constexpr int T = N / kE, P = fft_pairs<N, XK>(), H = kE / 2;
     __shared__ double sh[fft_lds_doubles<N, XK>()];
     if (MODE == 1 && a.last && is_bad(a)) return;
     if (MODE == 0 && a.first) clear_bad(a);
     int t = XK ? threadIdx.x % T : threadIdx.x / P;
     const int p = XK ? threadIdx.x / T : threadIdx.x % P;
-    const int64_t q = (int64_t)blockIdx.x * P + p;
+    // P = 8: the two blocks whose rows share cache lines on one XCD (blocks go to the XCDs in turn)
+    unsigned qb = blockIdx.x;
+    if (P == 8 && !XK && qb < gridDim.x / 16 * 16) qb = qb / 16 * 16 + qb % 8 * 2 + qb / 8 % 2;
+    const int64_t q = (int64_t)qb * P + p;
     const bool live = q < a.pairs;
     const float* __restrict__ in = a.in + (size_t)blockIdx.y * (XK && MODE == 0 ? a.fcells : a.cells);
     float* __restrict__ out = a.out + (size_t)blockIdx.y * (XK && MODE == 1 ? a.fcells : a.cells);
@@ -396,10 +416,15 @@ __global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
             }
         } else if (a.vec2) {
             float2 x[kE];
+            // points t + T j, j < 8: rows 2 t, 2 t + 2 T, ...; the others: N - 1 - 2 t downwards
+            const float* p0 = in + base + es * (2 * t);
+            const float* p1 = in + base + es * (N - 1 - 2 * t);
 #pragma unroll
-            for (int j = 0; j < kE; ++j) {
-                const int m = t + T * j;
-                x[j] = *reinterpret_cast<const float2*>(in + base + es * (j < H ? 2 * m : 2 * N - 1 - 2 * m));
+            for (int j = 0; j < H; ++j) {
+                x[j] = *reinterpret_cast<const float2*>(p0);
+                x[H + j] = *reinterpret_cast<const float2*>(p1);
+                p0 += es * (2 * T);
+                p1 -= es * (2 * T);
             }
 #pragma unroll
             for (int j = 0; j < kE; ++j) v[j] = {x[j].x, x[j].y};
@@ -421,27 +446,28 @@ __global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
     }
     t = again(t);
     if (MODE == 0) {
+        if (!live) return;  // (no barrier follows)
+        const bool pairwise = XK || a.vec2;
+        float* p0 = out + base + es * (2 * t);
 #pragma unroll
         for (int i = 0; i < H; ++i) {
             const int k = t + T * i;
             const double2 c = pw[k];
-            const v4d m = modes_of(v[i], v[H + i], Cd{c.x, c.y}, k == 0, sf, sf0);
+            const v4d m = modes_of(v[i], v[H + i], Cd{c.x, c.y}, i == 0 && t == 0, sf, sf0);
             if (XK) {
-                if (live) *reinterpret_cast<float2*>(out + base + 2 * k) = make_float2((float)m.x, (float)m.y);
+                *reinterpret_cast<float2*>(out + base + 2 * k) = make_float2((float)m.x, (float)m.y);
                 if (two) *reinterpret_cast<float2*>(out + base2 + 2 * k) = make_float2((float)m.z, (float)m.w);
-            } else if (a.vec2) {
-                if (live) {
-                    *reinterpret_cast<float2*>(out + base + es * (2 * k)) = make_float2((float)m.x, (float)m.z);
-                    *reinterpret_cast<float2*>(out + base + es * (2 * k + 1)) = make_float2((float)m.y, (float)m.w);
-                }
+            } else if (pairwise) {
+                *reinterpret_cast<float2*>(p0) = make_float2((float)m.x, (float)m.z);
+                *reinterpret_cast<float2*>(p0 + es) = make_float2((float)m.y, (float)m.w);
+                p0 += es * (2 * T);
             } else {
-                if (live) {
-                    out[base + es * (2 * k)] = (float)m.x;
-                    out[base + es * (2 * k + 1)] = (float)m.y;
-                }
+                const int64_t o = es * (2 * k);
+                out[base + o] = (float)m.x;
+                out[base + o + es] = (float)m.y;
                 if (two) {
-                    out[base2 + es * (2 * k)] = (float)m.z;
-                    out[base2 + es * (2 * k + 1)] = (float)m.w;
+                    out[base2 + o] = (float)m.z;
+                    out[base2 + o + es] = (float)m.w;
                 }
             }
         }
@@ -460,15 +486,16 @@ __global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
             const int k = t + T * i;
             const double2 c = pw[k];
             const Cd w = {c.x, c.y};
-            v4d m = modes_of(v[i], v[H + i], w, k == 0, 1.0, 1.0);
+            const bool k0 = k == 0;
+            v4d m = modes_of(v[i], v[H + i], w, k0, 1.0, 1.0);
             ok = ok && isfinite(m.x) && isfinite(m.y) && isfinite(m.z) && isfinite(m.w);
             // 4 sin^2(pi k / 2N) and 4 cos^2 of the same for N - k (k = 0: modes 0 and N / 2)
-            const double lk = 4.0 * a.cm * c.y * c.y, ln = k ? 4.0 * a.cm * c.x * c.x : 2.0 * a.cm;
+            const double lk = 4.0 * a.cm * c.y * c.y, ln = k0 ? 2.0 * a.cm : 4.0 * a.cm * c.x * c.x;
             m.x *= mode_gain(mua + lk, a.n_steps, a.cn);
             m.y *= mode_gain(mua + ln, a.n_steps, a.cn);
             m.z *= mode_gain(mub + lk, a.n_steps, a.cn);
             m.w *= mode_gain(mub + ln, a.n_steps, a.cn);
-            pair_of(m, w, k == 0, 1.0 / N, 1.0 / N, &v[i], &v[H + i]);
+            pair_of(m, w, k0, 1.0 / N, 1.0 / N, &v[i], &v[H + i]);
         }
         if (!ok && live) mark_bad(a);
     } else {
@@ -481,12 +508,13 @@ __global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
                 x[i] = make_float4(xa.x, xa.y, xb.x, xb.y);
             }
         } else if (a.vec2) {
+            const float* p0 = in + base + es * (2 * t);
 #pragma unroll
             for (int i = 0; i < H; ++i) {
-                const int64_t o = base + es * (2 * (t + T * i));
-                const float2 x0 = *reinterpret_cast<const float2*>(in + o);
-                const float2 x1 = *reinterpret_cast<const float2*>(in + o + es);
+                const float2 x0 = *reinterpret_cast<const float2*>(p0);
+                const float2 x1 = *reinterpret_cast<const float2*>(p0 + es);
                 x[i] = make_float4(x0.x, x1.x, x0.y, x1.y);
+                p0 += es * (2 * T);
             }
         } else {
 #pragma unroll
@@ -500,7 +528,7 @@ __global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
             const int k = t + T * i;
             const double2 c = pw[k];
             const v4d m = {x[i].x, x[i].y, two ? x[i].z : 0.f, two ? x[i].w : 0.f};
-            pair_of(m, Cd{c.x, c.y}, k == 0, si, si0, &v[i], &v[H + i]);
+            pair_of(m, Cd{c.x, c.y}, i == 0 && t == 0, si, si0, &v[i], &v[H + i]);
         }
     }
     t = again(t);
@@ -532,42 +560,51 @@ __global__ __launch_bounds__(FftCfg<N>::P* N / kE, 4) void k_fft(SpecPass a) {
             }
         }
     } else {
+        if (!live) return;  // (no barrier follows)
+        if (a.vec2) {
+            float* p0 = out + base + es * (2 * t);
+            float* p1 = out + base + es * (N - 1 - 2 * t);
+#pragma unroll
+            for (int j = 0; j < H; ++j) {
+                *reinterpret_cast<float2*>(p0) = make_float2((float)v[j].y, (float)v[j].x);
+                *reinterpret_cast<float2*>(p1) = make_float2((float)v[H + j].y, (float)v[H + j].x);
+                p0 += es * (2 * T);
+                p1 -= es * (2 * T);
+            }
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < kE; ++j) {
             const int m = t + T * j;
             const int64_t o = es * (j < H ? 2 * m : 2 * N - 1 - 2 * m);
-            if (a.vec2) {
-                if (live) *reinterpret_cast<float2*>(out + base + o) = make_float2((float)v[j].y, (float)v[j].x);
-            } else {
-                if (live) out[base + o] = (float)v[j].y;
-                if (two) out[base2 + o] = (float)v[j].x;
-            }
+            out[base + o] = (float)v[j].y;
+            if (two) out[base2 + o] = (float)v[j].x;
         }
     }
 }
 
 // ----------------------------------------------------------- dense lengths
 
-constexpr int kTL = 32;  // lines per block
-
 // Row of D element r of v_mfma_f64_16x16x4f64 in a lane (column: lane % 16).
 __device__ __forceinline__ int d_row(int r, int lane) { return 4 * r + (lane >> 4); }
 
 // Even and odd halves in LDS, [m][line].  A wave forms one 16-row tile of
-// the half-size products for the block's 32 lines (SPLIT: for 16 of them):
-// its even and odd products of two column tiles are four independent
-// accumulator chains that share every matrix fragment read from L2 (512
-// bytes for 4 reduction rows).  A block has as many waves as tiles, so none
-// idles in the products, and at least four, for the latency of its loads.
-// Bound by the float64 matrix rate together with a block's load, product and
-// store phases one after the other: 66 us forward or back along n = 275 for
-// 7.5M cells (30 us at 78.6 TFLOP/s), 50 us along 147, 66 us for the gain
-// pass along 93; the CG it replaces took 2.1 ms for the same three steps.
-template <int MODE, bool XK, bool SPLIT>
+// the half-size products for the block's 16 lines: its even and odd products
+// are two independent accumulator chains.  SPLIT, for one or two tiles: 32
+// lines, a wave per tile and half.  A block has as many waves as tiles, so
+// none idles in the products, and at least four, for the latency of its loads.
+// 16 lines rather than 32 with both halves in one wave: twice the blocks, of
+// half the LDS (37 KB at n = 275), so a block's load, product and store
+// phases overlap another's.  Measured, 32 -> 16 lines: 66 us -> 61 forward or
+// back along contiguous n = 275 for 7.5M cells (30 us at the 78.6 TFLOP/s of
+// the float64 matrix cores, which bound it together with the phases), 51 ->
+// 50 along strided 147, gain pass along 93 66 -> 65; 96 x 64 x 80 cells, 2
+// fields: 19.4 -> 15.1 us for the gain pass, 13.6 -> 10.5 and 11.7 -> 8.9 along x.
+template <int MODE, bool XK, bool SPLIT, int kTL>
 __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     extern __shared__ double shd[];
     constexpr int TLP = XK ? kTL + 1 : kTL;
-    constexpr int CT = SPLIT ? 1 : 2;
+    constexpr int CT = SPLIT ? 1 : kTL / 16;
     const int n = a.n, hm = a.hm, ho = a.ho, mt = (hm + 15) / 16, rows = 16 * mt;
     double* E = shd;
     double* O = shd + (size_t)rows * TLP;
@@ -575,7 +612,10 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     if (MODE == 0 && a.first) clear_bad(a);
     const float* __restrict__ in = a.in + (size_t)blockIdx.y * (XK && MODE == 0 ? a.fcells : a.cells);
     float* __restrict__ out = a.out + (size_t)blockIdx.y * (XK && MODE == 1 ? a.fcells : a.cells);
-    const int64_t l0 = (int64_t)blockIdx.x * kTL;
+    // 16 strided lines are half a cache line: the two blocks that share one go to one XCD
+    unsigned lb = blockIdx.x;
+    if (!SPLIT && !XK && lb < gridDim.x / 16 * 16) lb = lb / 16 * 16 + lb % 8 * 2 + lb / 8 % 2;
+    const int64_t l0 = (int64_t)lb * kTL;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int tile = SPLIT ? wave >> 1 : wave, c0 = SPLIT ? (wave & 1) * 16 : 0;
     const bool work = tile < mt;  // (a block of few tiles has waves that only move data)
@@ -615,7 +655,7 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     } else {
         const int line = threadIdx.x % kTL;
         const bool ok = l0 + line < a.lines;
-        fill(in + (ok ? base_of(l0 + line, false) : 0), es, threadIdx.x / kTL, 2 * nw, line, ok);
+        fill(in + (ok ? base_of(l0 + line, false) : 0), es, threadIdx.x / kTL, nw * 64 / kTL, line, ok);
     }
     __syncthreads();
     v4d ae[CT], ao[CT];
@@ -692,15 +732,10 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int k = tile * 16 + d_row(r, lane);
-                double e = 0.0, o = 0.0;
-                if (k < hm) {
-                    ok = ok && isfinite(ae[c][r]);
-                    e = ae[c][r] * mode_gain(fma(a.cm, a.lamm[k], mu), a.n_steps, a.cn);
-                }
-                if (k < ho) {
-                    ok = ok && isfinite(ao[c][r]);
-                    o = ao[c][r] * mode_gain(fma(a.cm, a.lamm[hm + k], mu), a.n_steps, a.cn);
-                }
+                const bool ie = k < hm, io = k < ho;
+                ok = ok && (!ie || isfinite(ae[c][r])) && (!io || isfinite(ao[c][r]));
+                const double e = ie ? ae[c][r] * mode_gain(fma(a.cm, a.lamm[k], mu), a.n_steps, a.cn) : 0.0;
+                const double o = io ? ao[c][r] * mode_gain(fma(a.cm, a.lamm[hm + k], mu), a.n_steps, a.cn) : 0.0;
                 if (work) {
                     E[k * TLP + line] = e;
                     O[k * TLP + line] = o;
@@ -787,7 +822,7 @@ size_t table_doubles(int n) {
 
 template <int N, int MODE, bool XK>
 void launch_fft(const SpecPass& a, int F, hipStream_t s) {
-    constexpr int P = FftCfg<N>::P;
+    constexpr int P = fft_pairs<N, XK>();
     const dim3 grid((unsigned)((a.pairs + P - 1) / P), F);
     hipLaunchKernelGGL((k_fft<N, MODE, XK>), grid, dim3(P * N / kE), 0, s, a);
 }
@@ -802,9 +837,9 @@ cgd_status launch_pass(const SpecPass& a, int F, hipStream_t s) {
         default: break;
     }
     const int mt = (a.hm + 15) / 16;
-    const size_t lds = (size_t)2 * mt * 16 * (XK ? kTL + 1 : kTL) * sizeof(double);
-    const dim3 grid((unsigned)((a.lines + kTL - 1) / kTL), F);
-    auto go = [&](auto kern, int nw) -> cgd_status {
+    auto go = [&](auto kern, int nw, int tl) -> cgd_status {
+        const dim3 grid((unsigned)((a.lines + tl - 1) / tl), F);
+        const size_t lds = (size_t)2 * mt * 16 * (XK ? tl + 1 : tl) * sizeof(double);
         if (lds > 64 * 1024)
             CGD_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -812,8 +847,8 @@ cgd_status launch_pass(const SpecPass& a, int F, hipStream_t s) {
         return CGD_OK;
     };
     // one or two tiles: a wave per tile and column tile, for the latency
-    if (mt <= 2) return go(k_dense<MODE, XK, true>, 4);
-    return go(k_dense<MODE, XK, false>, std::max(4, mt));
+    if (mt <= 2) return go(k_dense<MODE, XK, true, 32>, 4, 32);
+    return go(k_dense<MODE, XK, false, 16>, std::max(4, mt), 16);
 }
 
 // Eigenvalues d and eigenvectors (z[k], one array per eigenvalue) of the
@@ -1016,7 +1051,7 @@ size_t spectral_bytes(const cgd_mesh m, int32_t F) {
 // have converged within max_iter by its bound for the unpreconditioned
 // operator, so that a call that came back not converged still does; and
 // where it is the faster one: a transform takes about 2 ps per cell for an
-// FFT length and 2.5 + 0.022 n for a dense one (7.5M cells: 66 us at n = 275,
+// FFT length and 2.5 + 0.022 n for a dense one (7.5M cells: 61 us at n = 275,
 // 50 at 147, 33 at 93), the CG 25 ps per cell and step at its best
 // (256 x 256 x 512, dtau / h^2 = 1) and 50 us and more per step in launches
 // on the smallest grids, so only one or two steps on lengths of hundreds that
