@@ -92,21 +92,20 @@ struct Src {
     int cb, ldb;
 };
 
-// 8 channels c..c+7 (c a multiple of 8) of voxel (x, y, z) of the virtual input.
-__device__ inline uint4 load_src8(const Src& s, int c, int x, int y, int z, int nx, int ny) {
-    if (c < s.ca) {
-        if (s.upa) {
-            x >>= 1;
-            y >>= 1;
-            z >>= 1;
-            nx >>= 1;
-            ny >>= 1;
-        }
-        const size_t v = ((size_t)z * ny + y) * nx + x;
-        return *reinterpret_cast<const uint4*>(s.a + v * s.lda + c);
-    }
-    const size_t v = ((size_t)z * ny + y) * nx + x;
-    return *reinterpret_cast<const uint4*>(s.b + v * s.ldb + (c - s.ca));
+// A 16-byte load, or zero where !in (p is readable all the same): no branch,
+// so that several loads can be in flight.
+__device__ inline uint4 load8_if(bool in, const bf16* p) {
+    const uint4 w = *reinterpret_cast<const uint4*>(p);
+    return make_uint4(in ? w.x : 0u, in ? w.y : 0u, in ? w.z : 0u, in ? w.w : 0u);
+}
+
+// 8 channels c..c+7 (c a multiple of 8) of voxel (x, y, z) of the virtual
+// input, zero outside the grid (voxel 0 is read there).
+__device__ inline uint4 load_src8(const Src& s, int c, int x, int y, int z, int nx, int ny, bool in) {
+    const bool in_a = c < s.ca;
+    const int up = in_a && s.upa ? 1 : 0;
+    const size_t v = in ? ((size_t)(z >> up) * (ny >> up) + (y >> up)) * (nx >> up) + (x >> up) : 0;
+    return load8_if(in, in_a ? s.a + v * s.lda + c : s.b + v * s.ldb + (c - s.ca));
 }
 
 // Stages channels [pass*CC, pass*CC + CC) of the (BX+2) x (BY+2) x HZ halo
@@ -115,15 +114,24 @@ __device__ inline uint4 load_src8(const Src& s, int c, int x, int y, int z, int 
 template <int CC, int HZ>
 __device__ inline void stage_halo(uint4* lds, const Src& s, int pass, int x0, int y0, int z0, int nx, int ny,
                                   int nz) {
-    constexpr int G8 = CC / 8, RSU = G8 + 1, HV = HX * HY * HZ;
-    for (int i = threadIdx.x; i < HV * G8; i += kThreads) {
-        const int hv = i / G8, j = i - hv * G8;
-        const int hx = hv % HX, t = hv / HX, hy = t % HY, hz = t / HY;
-        const int gx = x0 - 1 + hx, gy = y0 - 1 + hy, gz = z0 - 1 + hz;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if ((unsigned)gx < (unsigned)nx && (unsigned)gy < (unsigned)ny && (unsigned)gz < (unsigned)nz)
-            v = load_src8(s, pass * CC + 8 * j, gx, gy, gz, nx, ny);
-        lds[hv * RSU + j] = v;
+    constexpr int G8 = CC / 8, RSU = G8 + 1, HV = HX * HY * HZ, U = 6;
+#pragma unroll 1
+    for (int i0 = threadIdx.x; i0 < HV * G8; i0 += U * kThreads) {
+        uint4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + u * kThreads, HV * G8 - 1);
+            const int hv = i / G8, j = i - hv * G8;
+            const int hx = hv % HX, t = hv / HX, hy = t % HY, hz = t / HY;
+            const int gx = x0 - 1 + hx, gy = y0 - 1 + hy, gz = z0 - 1 + hz;
+            const bool in = (unsigned)gx < (unsigned)nx && (unsigned)gy < (unsigned)ny && (unsigned)gz < (unsigned)nz;
+            v[u] = load_src8(s, pass * CC + 8 * j, gx, gy, gz, nx, ny, in);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kThreads;
+            if (i < HV * G8) lds[i / G8 * RSU + i % G8] = v[u];
+        }
     }
 }
 
@@ -132,13 +140,13 @@ template <int HZ>
 __device__ inline void stage_halo1(uint16_t* lds, const Src& s, int x0, int y0, int z0, int nx, int ny, int nz) {
     constexpr int HV = HX * HY * HZ;
     const uint16_t* a = reinterpret_cast<const uint16_t*>(s.a);
+#pragma unroll
     for (int hv = threadIdx.x; hv < HV; hv += kThreads) {
         const int hx = hv % HX, t = hv / HX, hy = t % HY, hz = t / HY;
         const int gx = x0 - 1 + hx, gy = y0 - 1 + hy, gz = z0 - 1 + hz;
-        uint16_t v = 0;
-        if ((unsigned)gx < (unsigned)nx && (unsigned)gy < (unsigned)ny && (unsigned)gz < (unsigned)nz)
-            v = a[(((size_t)gz * ny + gy) * nx + gx) * s.lda];
-        lds[hv] = v;
+        const bool in = (unsigned)gx < (unsigned)nx && (unsigned)gy < (unsigned)ny && (unsigned)gz < (unsigned)nz;
+        const uint16_t v = a[(in ? ((size_t)gz * ny + gy) * nx + gx : 0) * s.lda];
+        lds[hv] = in ? v : (uint16_t)0;
     }
 }
 
@@ -160,10 +168,26 @@ struct ConvArgs {
     int nx, ny, nz, bnx, bny;
 };
 
+// Waves per SIMD to leave registers for: what the halo brick's LDS lets in (3
+// blocks of 52 KB, 5 of 31 KB), less where the accumulators and fragments
+// would spill (<32, 32, 2>: 81 us at 3 with 48 bytes spilled, 66 at 2).
+__host__ __device__ constexpr int conv_waves(int cc, int co, int np) {
+    return co == 64 || (cc == 32 && co == 32 && np == 2) ? 2 : (cc == 32 ? 3 : (cc == 16 ? 5 : 8));
+}
+
 // One 3x3x3 convolution (see the file comment).  CC: input channels per LDS
 // pass (1, 16 or 32); CO: output channels; NP: passes (CI = NP * CC).
+// Bound by latency rather than rate: the halo's loads, then the weight
+// fragments out of L2 (1 KB per wave and chunk), and at 16 output channels
+// the LDS reads, 8 cycles of the unit for 16 of one SIMD's matrix core.  So a
+// thread keeps six halo loads in flight and no branch around them, weights
+// are loaded G chunks ahead (behind a scheduling barrier, or the compiler
+// moves them back to their use), and 32-channel passes read each halo row
+// once per dz for its three dy.  One prediction on 128^3, per launch, before
+// and after: <32, 16, 1> 134 -> 112 us, <16, 16, 1> 91 -> 79, <32, 32, 2> 84
+// -> 66, <32, 32, 1> 42 -> 28, <32, 64, 2> 53 -> 39, <32, 64, 1> 37 -> 20.
 template <int CC, int CO, int NP>
-__global__ __launch_bounds__(kThreads) void k_conv(ConvArgs a) {
+__global__ __launch_bounds__(kThreads, conv_waves(CC, CO, NP)) void k_conv(ConvArgs a) {
     constexpr int NT = CO / 16;
     constexpr int KT = kt_of(CC);
     constexpr int NCH = CC == 1 ? 1 : (CC == 16 ? 14 : 27);
@@ -186,7 +210,29 @@ __global__ __launch_bounds__(kThreads) void k_conv(ConvArgs a) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // weight fragments (K = 32 per chunk), G chunks ahead of their use
+    // (9 taps of 32 channels to 16 leave two waves per SIMD: 134 us, 3 taps 112)
+    constexpr int G = NT == 4 ? 1 : (CC == 32 ? 3 : (NT == 1 ? 7 : 2));
+    constexpr int NG = NCH / G;
+    static_assert(CC == 1 || (NG * G == NCH && (CC != 32 || 9 % G == 0)));
+    bf16x8 wc[G][NT], wn[G][NT];
+
     for (int p = 0; p < NP; ++p) {
+        auto load_w = [&](int q, bf16x8(*o)[NT]) {
+            const bf16* wp = a.w + ((size_t)xl * NP + p) * KT * CC + 8 * g;
+#pragma unroll
+            for (int i = 0; i < G; ++i)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    o[i][t] = *reinterpret_cast<const bf16x8*>(wp + (size_t)16 * t * NP * KT * CC + (q * G + i) * 32);
+        };
+        auto next_w = [&] {
+#pragma unroll
+            for (int i = 0; i < G; ++i)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) wc[i][t] = wn[i][t];
+        };
+        if constexpr (CC > 1) load_w(0, wc);
         if (p) __syncthreads();
         if constexpr (CC == 1)
             stage_halo1<BZ + 2>(reinterpret_cast<uint16_t*>(lds), a.src, x0, y0, z0, a.nx, a.ny, a.nz);
@@ -216,34 +262,58 @@ __global__ __launch_bounds__(kThreads) void k_conv(ConvArgs a) {
                 for (int t = 0; t < NT; ++t)
                     acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[t], bfr, acc[r][t], 0, 0, 0);
             }
+        } else if constexpr (CC == 32) {
+            // a wave's rows are one z plane's: per dz, the halo rows' fragments
+            // are read once and serve the three dy
+            static_assert(kRowsPerWave == BY);
+            const bf16x8* lp = reinterpret_cast<const bf16x8*>(lds) + (wave * HY * HX + xl) * RSU + g;
+#pragma unroll
+            for (int dz = 0; dz < 3; ++dz) {
+                bf16x8 rows[HY][3];
+#pragma unroll
+                for (int y = 0; y < HY; ++y)
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx) rows[y][dx] = lp[((dz * HY + y) * HX + dx) * RSU];
+#pragma unroll
+                for (int q = 9 * dz / G; q < 9 * (dz + 1) / G; ++q) {
+                    if (q + 1 < NG) load_w(q + 1, wn);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < G; ++i) {
+                        const int t9 = q * G + i - 9 * dz;
+#pragma unroll
+                        for (int r = 0; r < kRowsPerWave; ++r)
+#pragma unroll
+                            for (int t = 0; t < NT; ++t)
+                                acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    wc[i][t], rows[r + t9 / 3][t9 % 3], acc[r][t], 0, 0, 0);
+                    }
+                    next_w();
+                }
+            }
         } else {
-            const bf16x8* l8 = reinterpret_cast<const bf16x8*>(lds);
-            for (int kc = 0; kc < NCH; ++kc) {
-                int tap, ch;
-                if constexpr (CC == 32) {
-                    tap = kc;
-                    ch = 8 * g;
-                } else {
-                    tap = 2 * kc + (g >> 1);
-                    ch = 8 * (g & 1);
+            // K = 32: two taps of 16 channels, lane groups 0, 1 and 2, 3
+            const bf16x8* l8 = reinterpret_cast<const bf16x8*>(lds) + (wave * HY * HX + xl) * RSU + (g & 1);
+#pragma unroll
+            for (int q = 0; q < NG; ++q) {
+                if (q + 1 < NG) load_w(q + 1, wn);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < G; ++i) {
+                    // (tap 27, the padding, has zero weights)
+                    const int t0 = 2 * (q * G + i), t1 = t0 + 1 < 27 ? t0 + 1 : 26;
+                    const int hv0 = (t0 / 9 * HY + t0 / 3 % 3) * HX + t0 % 3;
+                    const int hv1 = (t1 / 9 * HY + t1 / 3 % 3) * HX + t1 % 3;
+                    const bf16x8* lp = l8 + (g >> 1 ? hv1 : hv0) * RSU;
+#pragma unroll
+                    for (int r = 0; r < kRowsPerWave; ++r) {
+                        const bf16x8 bfr = lp[r * HX * RSU];
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+                            acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wc[i][t], bfr, acc[r][t], 0, 0, 0);
+                    }
                 }
-                bf16x8 af[NT];
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    af[t] = *reinterpret_cast<const bf16x8*>(a.w + ((size_t)(16 * t + xl) * NP + p) * KT * CC +
-                                                             tap * CC + ch);
-                const int tp = min(tap, 26);  // tap 27 (CC = 16 padding) has zero weights
-                const int dz = tap_dz(tp), dy = tap_dy(tp), dx = tap_dx(tp);
-#pragma unroll
-                for (int r = 0; r < kRowsPerWave; ++r) {
-                    const int row = wave * kRowsPerWave + r;
-                    const int ty = row % BY, tz = row / BY;
-                    const int hv = ((tz + 1 + dz) * HY + ty + 1 + dy) * HX + xl + 1 + dx;
-                    const bf16x8 bfr = l8[hv * RSU + (ch >> 3)];
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-                        acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[t], bfr, acc[r][t], 0, 0, 0);
-                }
+                next_w();
             }
         }
     }
@@ -448,10 +518,9 @@ __global__ __launch_bounds__(kThreads) void k_wgrad2(WgArgs a) {
             for (int k = 0; k < 4; ++k) {
                 const int hx = 4 * q + k - 7;
                 const int gx = x0 - 1 + hx, gy = y0 - 1 + hy, gz = z0 - 1 + hz;
-                uint4 v = make_uint4(0u, 0u, 0u, 0u);
-                if (hx >= 0 && hx < HX && (unsigned)gx < (unsigned)a.nx && (unsigned)gy < (unsigned)a.ny &&
-                    (unsigned)gz < (unsigned)a.nz)
-                    v = load_src8(a.src, pass * CC + 8 * j, gx, gy, gz, a.nx, a.ny);
+                const bool in = hx >= 0 && hx < HX && (unsigned)gx < (unsigned)a.nx &&
+                                (unsigned)gy < (unsigned)a.ny && (unsigned)gz < (unsigned)a.nz;
+                const uint4 v = load_src8(a.src, pass * CC + 8 * j, gx, gy, gz, a.nx, a.ny, in);
                 w[k][0] = v.x;
                 w[k][1] = v.y;
                 w[k][2] = v.z;
@@ -475,9 +544,8 @@ __global__ __launch_bounds__(kThreads) void k_wgrad2(WgArgs a) {
             for (int k = 0; k < 4; ++k) {
                 const int vi = 4 * vq + k;
                 const int x = x0 + (vi & 15), y = y0 + ((vi >> 4) & 3), z = z0 + (vi >> 6);
-                uint4 v = make_uint4(0u, 0u, 0u, 0u);
-                if (x < a.nx && y < a.ny && z < a.nz)
-                    v = *reinterpret_cast<const uint4*>(a.g + (((size_t)z * a.ny + y) * a.nx + x) * a.ldg + 8 * j);
+                const bool in = x < a.nx && y < a.ny && z < a.nz;
+                const uint4 v = load8_if(in, a.g + (in ? ((size_t)z * a.ny + y) * a.nx + x : 0) * a.ldg + 8 * j);
                 w[k][0] = v.x;
                 w[k][1] = v.y;
                 w[k][2] = v.z;
