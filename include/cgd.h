@@ -283,9 +283,13 @@ cgd_status cgd_deposit_noalloc(cgd_mesh m, int64_t n, const float* pos, int32_t 
  * diffusivity is one value on a box of cells and 0 elsewhere, is solved
  * directly where that is the faster way: the operator is diagonal in the
  * axes' modes (cosines where the cells are even), so all n_steps are one
- * multiplication between a forward and an inverse transform
- * (float64 arithmetic on float32 vectors; within 1e-7 of the exact solution
- * in relative L2, closer than the CG at its default tolerance).  Statistics,
+ * multiplication between a forward and an inverse transform in
+ * float64: every result is the discrete solution rounded to float32 once, to
+ * within 2^-53 sqrt(cells of an x-y plane) of the largest plane mean (a
+ * small factor).  From a field without negative values, results below a cut
+ * between 2^-32 of the largest plane mean and 2^-32 of the largest result are
+ * returned as 0, so that no backward Euler result is negative and quotients
+ * of two fields hold wherever the divisor is not 0.  Statistics,
  * x0_mode != 0, precond = 1, rtol < 5e-7, axes of more than 512 cells other
  * than 1024, one or two steps on long axes that are no power of two, and a
  * max_iter below the CG's own bound are solved by CG, as are axes of uneven

@@ -40,12 +40,17 @@ struct SpecTables {
     int64_t cells = 0;        // of the box
     double* dev = nullptr;
     SpecAxis axis[3];
+    uint32_t* neg = nullptr;  // device, [kSpecFields] (SpecPass)
+    uint32_t calls = 0;       // calls so far
 };
+constexpr int kSpecFields = 4096;  // fields of a call at most
+constexpr int kTopSlots = 8, kTopStride = 32;  // SpecPass::top: words per field, each in a cache line of its own
 
 // One pass of transforms along one axis of all fields.
 struct SpecPass {
-    const float* in;
-    float* out;
+    const float* in;      // the caller's fields: the first pass's input
+    float* out;           //    and the last one's output
+    double* W;            // the modes between the passes, worked on in place
     int64_t cells;        // per field of W
     int64_t fcells;       // per field of the caller's array (the first pass's input, the last one's output)
     int64_t off, sy, sz, pitch;  // ... where its row r begins: off + r pitch, or (rows_y) off + (r % rows_y) sy + (r / rows_y) sz
@@ -58,8 +63,7 @@ struct SpecPass {
     int64_t inner_pairs;  //    their pairs, the stride between points of a line
     int64_t estride;      //    and between groups of neighbouring lines
     int64_t ostride;
-    int32_t vec2;         // both lines of a pair (contiguous lines: two points) in one aligned 8-byte access
-    int32_t first, last;  // first: clears *bad; last: writes nothing where *bad is set
+    int32_t vec2;         // both lines of a pair in one aligned 16-byte access (contiguous lines: two points in 8 bytes)
     const double2* tw;
     const double2* pw;
     const double* fe;
@@ -74,20 +78,24 @@ struct SpecPass {
     const double* lam1;
     int64_t n0;
     int32_t n_steps, cn;
-    int* bad;       // device, per field: set when a mode is not finite
+    int* bad;       // device, per field: set by the gain pass where a value of W is beyond float32 or not finite
     int* bad_host;  // nullable: the same in pinned host memory
+    uint32_t* top;  // device, kTopSlots per field: the largest |value| in W after the gain pass (float32 bits)
+    uint32_t* neg;  // device, per field: `call` where the input holds a negative value
+    uint32_t call;
+    double cut;     // results below cut * (the largest of top) of a field without negative values are 0
 };
 
 // Whether a call on n_fields fields is answered by the direct solve (stats:
 // its statistics are asked for).
 bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stats);
-// Bytes of the scratch vector W for F fields, where spectral_applies.
+// Bytes of scratch (W) for F fields, where spectral_applies.
 size_t spectral_bytes(const cgd_mesh m, int32_t F);
 // Enqueues all steps of `da` on n_fields fields at da.field [n_fields][cells]
-// (da.F is not used), with W as scratch.  Where a field has a mode that is
-// not finite, its entries of bad and bad_host (nullable, cleared by the
-// caller) are set and the field is left as it was.
-cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, float* W, int* bad, int* bad_host,
+// (da.F is not used), with W as scratch; at most kSpecFields.  Where a field
+// has a mode beyond float32 or not finite, its entries of bad and bad_host
+// (nullable, cleared by the caller) are set and the field is left as it was.
+cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, double* W, int* bad, int* bad_host,
                             hipStream_t s);
 // The diffusion of cgd_diffuse by the direct solve; waits for the stream.
 cgd_status diffuse_spectral(cgd_mesh m, const DiffuseArgs& da, hipStream_t s);

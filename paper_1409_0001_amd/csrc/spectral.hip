@@ -10,12 +10,16 @@
 // and an inverse transform.
 //
 // Passes over memory (three axes): x forward, y forward, z forward + gain +
-// z inverse in one kernel, y inverse, x inverse; 8 bytes per cell each, the
-// four inner ones in place on one workspace vector.  Arithmetic is float64 in
-// registers and LDS throughout (gfx950 issues float64 and unpacked float32
-// multiply-adds at the same rate), and only the vectors between passes are
-// float32: what an iterate of the CG holds, rounded four times instead of
-// twice per iteration.
+// z inverse in one kernel, y inverse, x inverse; 12 bytes per cell along x,
+// 16 for the inner ones, in place on one float64 workspace vector.  All is
+// float64 (gfx950 issues float64 and unpacked float32 multiply-adds at the
+// same rate) but the field itself, rounded once.  The vectors between the
+// passes have to be float64 as well: a mode's rounding error reaches every
+// cell of its line, and in float32 it put noise of 1e-8 of a line's largest
+// values, of either sign, into cells that no particle is near (a bed in half
+// of 64 x 64 x 128 cells: 29,994 negative cells, and velocities from momentum
+// 20 % off where eps is 1e-7 of its maximum).  It costs 38 % of the dense
+// bed's transforms (256 x 256 x 512: 340 -> 500 us).
 //
 // Rectilinear grids: with one diffusivity d on the cells that diffuse at all
 // (the product of per-axis factors that are constant on one range of the axis
@@ -37,9 +41,11 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <new>
 #include <string>
+#include <type_traits>
 
 #include "cg_common.h"
 #include "spectral.h"
@@ -136,18 +142,60 @@ __device__ __forceinline__ double mode_gain(double mu, int n, int cn) {
     return g;
 }
 
-// A field with a mode that is not finite: the last pass leaves it alone, and
-// the host solves it by CG.
+// A field with a value beyond float32 in W: the last pass leaves it alone,
+// and the host solves it by CG.
 __device__ __forceinline__ void mark_bad(const SpecPass& a) {
     __hip_atomic_store(a.bad + blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (a.bad_host) a.bad_host[blockIdx.y] = 1;
 }
-__device__ __forceinline__ void clear_bad(const SpecPass& a) {
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        __hip_atomic_store(a.bad + blockIdx.y, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ bool carried(double x) { return fabs(x) <= (double)FLT_MAX; }
+// The first pass (x forward) clears what the gain pass notes per field.
+__device__ __forceinline__ void clear_notes(const SpecPass& a) {
+    if (blockIdx.x) return;
+    if (threadIdx.x == 0) __hip_atomic_store(a.bad + blockIdx.y, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x < kTopSlots) a.top[(size_t)(blockIdx.y * kTopSlots + threadIdx.x) * kTopStride] = 0u;
 }
 __device__ __forceinline__ bool is_bad(const SpecPass& a) {
     return __hip_atomic_load(a.bad + blockIdx.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
+// A negative value anywhere in a field: noted as this call's number, which
+// no earlier call has left there, so nothing has to be cleared first.  A
+// plain store (every wave stores the same, and only later kernels read it):
+// one that goes past the XCD's L2 took x forward of 4 x 128^3 from 17 to 53
+// us.  (All threads of a wave.)
+__device__ __forceinline__ void mark_negative(const SpecPass& a, bool negative) {
+    if (__ballot(negative) && (threadIdx.x & 63) == 0) a.neg[blockIdx.y] = a.call;
+}
+// The largest |value| the gain pass leaves in W, in one of a field's
+// kTopSlots cache lines (one word per field took the gain pass of 4 x 128^3
+// from 29 to 60 us).  (All threads of a wave.)
+__device__ __forceinline__ void note_top(const SpecPass& a, double big) {
+    float b = (float)fmin(big, (double)FLT_MAX);
+    for (int o = 32; o > 0; o >>= 1) b = fmaxf(b, __shfl_xor(b, o));
+    const unsigned wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if ((threadIdx.x & 63) == 0)
+        atomic_max_if_larger(a.top + (size_t)(blockIdx.y * kTopSlots + wave % kTopSlots) * kTopStride, __float_as_uint(b));
+}
+// Results of a field without negative values are right to about 2^-53 of the
+// largest plane mean times the square root of a plane's cells, whatever
+// their own size.  Below a.cut times the largest value between the gain pass
+// and the inverse ones, which is 2^-32 of something between that mean (the
+// plane's mode 0) and the largest result (the transforms keep the norm), they
+// are returned as 0: no backward Euler result is negative, and the quotient
+// of two fields is right wherever the divisor is not 0 (in a float64 model to
+// 2e-5 for beds in half or a corner of 512 x 512 x 8 cells and smaller
+// boxes, 3e-3 for a single particle in the first).
+__device__ __forceinline__ float cut_of(const SpecPass& a) {
+    uint32_t top = 0u;
+#pragma unroll
+    for (int i = 0; i < kTopSlots; ++i) top = max(top, a.top[(size_t)(blockIdx.y * kTopSlots + i) * kTopStride]);
+    const float c = a.neg[blockIdx.y] == a.call ? 0.f : (float)(a.cut * (double)__uint_as_float(top));
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(c)));  // (the same in all lanes: a scalar register)
+}
+__device__ __forceinline__ float result(double x, float cut) {
+    const float r = (float)x;
+    return fabsf(r) < cut ? 0.f : r;
 }
 
 // Where row r of the caller's array begins.
@@ -181,11 +229,10 @@ struct FftCfg<1024> {
 constexpr int kE = 16;  // points of a line held by a thread
 
 // Pairs of lines per block: small blocks, whose barriers wait for few waves
-// (the gain pass at 512: 131 us with 16 pairs on the dense bed, 120 with 8,
-// 115 with the two blocks that share its cache lines on one XCD; contiguous
-// lines at 128: 60 us with 32 pairs on 16 fields of 128^3, 53 with 16), but
-// whole 128-byte rows where a block is small anyway (strided lines at 128: 14
-// us against 17 on 128 x 115 x 256).
+// (with float32 vectors, the gain pass at 512: 131 us with 16 pairs on the
+// dense bed, 120 with 8; contiguous lines at 128: 60 us with 32 pairs on 16
+// fields of 128^3, 53 with 16), but longer rows where a block is small anyway
+// (strided lines at 128: 14 us with 32 pairs against 17 on 128 x 115 x 256).
 template <int N, bool XK>
 constexpr int fft_pairs() { return N >= 512 ? 8 : (N == 256 || XK ? 16 : 32); }
 
@@ -347,24 +394,28 @@ __device__ __forceinline__ void pair_of(v4d m, Cd w, bool k0, double s, double s
 // LDS exchanges' barriers together; loads and stores walk one pointer per
 // stream and the special modes (0 and N / 2) are a test on thread 0's first
 // point, where offsets and tests per point took registers and issue slots.
-// 256 x 256 x 512, one field (268 MB in and out, 38 us at 7.0 TB/s): forward
-// and back along x 59 and 54 us (59 and 60 before), y 53 and 49 (56 and 88),
-// the gain pass along z 114 (131).
+// Large fields are bound by memory: 256 x 256 x 512, one field, whose W of
+// 268 MB the memory-side cache does not hold: forward and back along x 70 and
+// 82 us (403 MB in and out; 61 and 57 with float32 W), y 98 and 87 (537 MB,
+// 5.5 to 6.2 TB/s; 53 and 50), the gain pass along z 160 (118).  4 fields of
+// 128^3 (67 MB): 19, 22, 21, 21 and 39 us (17, 18, 15, 16, 29).
 template <int N, int MODE, bool XK>
 __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPass a) {
     constexpr int T = N / kE, P = fft_pairs<N, XK>(), H = kE / 2;
     __shared__ double sh[fft_lds_doubles<N, XK>()];
-    if (MODE == 1 && a.last && is_bad(a)) return;
-    if (MODE == 0 && a.first) clear_bad(a);
+    if (MODE == 1 && XK && is_bad(a)) return;
+    if (MODE == 0 && XK) clear_notes(a);
     int t = XK ? threadIdx.x % T : threadIdx.x / P;
     const int p = XK ? threadIdx.x / T : threadIdx.x % P;
-    // P = 8: the two blocks whose rows share cache lines on one XCD (blocks go to the XCDs in turn)
+    // P = 8: the two blocks whose rows share cache lines (rows not a multiple
+    // of 16 long) on one XCD (blocks go to the XCDs in turn)
     unsigned qb = blockIdx.x;
     if (P == 8 && !XK && qb < gridDim.x / 16 * 16) qb = qb / 16 * 16 + qb % 8 * 2 + qb / 8 % 2;
     const int64_t q = (int64_t)qb * P + p;
     const bool live = q < a.pairs;
-    const float* __restrict__ in = a.in + (size_t)blockIdx.y * (XK && MODE == 0 ? a.fcells : a.cells);
-    float* __restrict__ out = a.out + (size_t)blockIdx.y * (XK && MODE == 1 ? a.fcells : a.cells);
+    const float* __restrict__ in = a.in + (size_t)blockIdx.y * a.fcells;
+    float* __restrict__ out = a.out + (size_t)blockIdx.y * a.fcells;
+    double* __restrict__ W = a.W + (size_t)blockIdx.y * a.cells;
     const double2* __restrict__ tw = a.tw;
     const double2* __restrict__ pw = a.pw;
     const double sf = a.sf, sf0 = a.sf0, si = a.si, si0 = a.si0;
@@ -408,6 +459,11 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
                     xb[j] = make_float2(in[fbase2 + e], in[fbase2 + e + 1]);
                 }
             }
+            bool negative = false;
+#pragma unroll
+            for (int j = 0; j < H; ++j)
+                negative = negative || xa[j].x < 0.f || xa[j].y < 0.f || xb[j].x < 0.f || xb[j].y < 0.f;
+            mark_negative(a, negative);
 #pragma unroll
             for (int j = 0; j < H; ++j) {
                 v[j] = {xa[j].x, two ? xb[j].x : 0.f};
@@ -415,30 +471,33 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
                 v[kE - 1 - j] = {ya, two ? yb : 0.f};
             }
         } else if (a.vec2) {
-            float2 x[kE];
             // points t + T j, j < 8: rows 2 t, 2 t + 2 T, ...; the others: N - 1 - 2 t downwards
-            const float* p0 = in + base + es * (2 * t);
-            const float* p1 = in + base + es * (N - 1 - 2 * t);
+            const double* p0 = W + base + es * (2 * t);
+            const double* p1 = W + base + es * (N - 1 - 2 * t);
 #pragma unroll
             for (int j = 0; j < H; ++j) {
-                x[j] = *reinterpret_cast<const float2*>(p0);
-                x[H + j] = *reinterpret_cast<const float2*>(p1);
+                const double2 x0 = *reinterpret_cast<const double2*>(p0);
+                const double2 x1 = *reinterpret_cast<const double2*>(p1);
+                v[j] = {x0.x, x0.y};
+                v[H + j] = {x1.x, x1.y};
                 p0 += es * (2 * T);
                 p1 -= es * (2 * T);
             }
-#pragma unroll
-            for (int j = 0; j < kE; ++j) v[j] = {x[j].x, x[j].y};
         } else {
-            float x[kE], y[kE];
 #pragma unroll
             for (int j = 0; j < kE; ++j) {
                 const int m = t + T * j;
                 const int64_t o = es * (j < H ? 2 * m : 2 * N - 1 - 2 * m);
-                x[j] = in[base + o];
-                y[j] = in[base2 + o];
+                v[j] = {W[base + o], W[base2 + o]};
             }
 #pragma unroll
-            for (int j = 0; j < kE; ++j) v[j] = {x[j], two ? y[j] : 0.f};
+            for (int j = 0; j < kE; ++j) v[j].y = two ? v[j].y : 0.0;
+        }
+        if (MODE == 2) {
+            bool ok = true;
+#pragma unroll
+            for (int j = 0; j < kE; ++j) ok = ok && carried(v[j].x) && carried(v[j].y);
+            if (!ok && live) mark_bad(a);
         }
         fft_line<N, P, XK>(v, sh, t, p, tw);
         t = again(t);
@@ -447,27 +506,26 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
     t = again(t);
     if (MODE == 0) {
         if (!live) return;  // (no barrier follows)
-        const bool pairwise = XK || a.vec2;
-        float* p0 = out + base + es * (2 * t);
+        double* p0 = W + base + es * (2 * t);
 #pragma unroll
         for (int i = 0; i < H; ++i) {
             const int k = t + T * i;
             const double2 c = pw[k];
             const v4d m = modes_of(v[i], v[H + i], Cd{c.x, c.y}, i == 0 && t == 0, sf, sf0);
             if (XK) {
-                *reinterpret_cast<float2*>(out + base + 2 * k) = make_float2((float)m.x, (float)m.y);
-                if (two) *reinterpret_cast<float2*>(out + base2 + 2 * k) = make_float2((float)m.z, (float)m.w);
-            } else if (pairwise) {
-                *reinterpret_cast<float2*>(p0) = make_float2((float)m.x, (float)m.z);
-                *reinterpret_cast<float2*>(p0 + es) = make_float2((float)m.y, (float)m.w);
+                *reinterpret_cast<double2*>(W + base + 2 * k) = make_double2(m.x, m.y);
+                if (two) *reinterpret_cast<double2*>(W + base2 + 2 * k) = make_double2(m.z, m.w);
+            } else if (a.vec2) {
+                *reinterpret_cast<double2*>(p0) = make_double2(m.x, m.z);
+                *reinterpret_cast<double2*>(p0 + es) = make_double2(m.y, m.w);
                 p0 += es * (2 * T);
             } else {
                 const int64_t o = es * (2 * k);
-                out[base + o] = (float)m.x;
-                out[base + o + es] = (float)m.y;
+                W[base + o] = m.x;
+                W[base + o + es] = m.y;
                 if (two) {
-                    out[base2 + o] = (float)m.z;
-                    out[base2 + o + es] = (float)m.w;
+                    W[base2 + o] = m.z;
+                    W[base2 + o + es] = m.w;
                 }
             }
         }
@@ -480,7 +538,6 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
         const int64_t y0 = line / a.n0, y1 = l1 / a.n0;
         const double mua = a.c0 * a.lam0[line - y0 * a.n0] + (a.lam1 ? a.c1 * a.lam1[y0] : 0.0);
         const double mub = a.c0 * a.lam0[l1 - y1 * a.n0] + (a.lam1 ? a.c1 * a.lam1[y1] : 0.0);
-        bool ok = true;
 #pragma unroll
         for (int i = 0; i < H; ++i) {
             const int k = t + T * i;
@@ -488,7 +545,6 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
             const Cd w = {c.x, c.y};
             const bool k0 = k == 0;
             v4d m = modes_of(v[i], v[H + i], w, k0, 1.0, 1.0);
-            ok = ok && isfinite(m.x) && isfinite(m.y) && isfinite(m.z) && isfinite(m.w);
             // 4 sin^2(pi k / 2N) and 4 cos^2 of the same for N - k (k = 0: modes 0 and N / 2)
             const double lk = 4.0 * a.cm * c.y * c.y, ln = k0 ? 2.0 * a.cm : 4.0 * a.cm * c.x * c.x;
             m.x *= mode_gain(mua + lk, a.n_steps, a.cn);
@@ -497,37 +553,36 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
             m.w *= mode_gain(mub + ln, a.n_steps, a.cn);
             pair_of(m, w, k0, 1.0 / N, 1.0 / N, &v[i], &v[H + i]);
         }
-        if (!ok && live) mark_bad(a);
     } else {
-        float4 x[H];  // modes of line a (k, N - k), then of line b
+        v4d x[H];  // modes of line a (k, N - k), then of line b
         if (XK) {
 #pragma unroll
             for (int i = 0; i < H; ++i) {
-                const float2 xa = *reinterpret_cast<const float2*>(in + base + 2 * (t + T * i));
-                const float2 xb = *reinterpret_cast<const float2*>(in + base2 + 2 * (t + T * i));
-                x[i] = make_float4(xa.x, xa.y, xb.x, xb.y);
+                const double2 xa = *reinterpret_cast<const double2*>(W + base + 2 * (t + T * i));
+                const double2 xb = *reinterpret_cast<const double2*>(W + base2 + 2 * (t + T * i));
+                x[i] = v4d{xa.x, xa.y, xb.x, xb.y};
             }
         } else if (a.vec2) {
-            const float* p0 = in + base + es * (2 * t);
+            const double* p0 = W + base + es * (2 * t);
 #pragma unroll
             for (int i = 0; i < H; ++i) {
-                const float2 x0 = *reinterpret_cast<const float2*>(p0);
-                const float2 x1 = *reinterpret_cast<const float2*>(p0 + es);
-                x[i] = make_float4(x0.x, x1.x, x0.y, x1.y);
+                const double2 x0 = *reinterpret_cast<const double2*>(p0);
+                const double2 x1 = *reinterpret_cast<const double2*>(p0 + es);
+                x[i] = v4d{x0.x, x1.x, x0.y, x1.y};
                 p0 += es * (2 * T);
             }
         } else {
 #pragma unroll
             for (int i = 0; i < H; ++i) {
                 const int64_t o = es * (2 * (t + T * i));
-                x[i] = make_float4(in[base + o], in[base + o + es], in[base2 + o], in[base2 + o + es]);
+                x[i] = v4d{W[base + o], W[base + o + es], W[base2 + o], W[base2 + o + es]};
             }
         }
 #pragma unroll
         for (int i = 0; i < H; ++i) {
             const int k = t + T * i;
             const double2 c = pw[k];
-            const v4d m = {x[i].x, x[i].y, two ? x[i].z : 0.f, two ? x[i].w : 0.f};
+            const v4d m = {x[i].x, x[i].y, two ? x[i].z : 0.0, two ? x[i].w : 0.0};
             pair_of(m, Cd{c.x, c.y}, i == 0 && t == 0, si, si0, &v[i], &v[H + i]);
         }
     }
@@ -539,12 +594,19 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
     for (int j = 0; j < kE; ++j) v[j] = {v[j].y, v[j].x};
     fft_line<N, P, XK>(v, sh, t, p, tw);
     t = again(t);
+    if (MODE == 2) {
+        double big = 0.0;
+#pragma unroll
+        for (int j = 0; j < kE; ++j) big = fmax(big, fmax(fabs(v[j].x), fabs(v[j].y)));
+        note_top(a, live ? big : 0.0);
+    }
     if (XK) {
+        const float cut = cut_of(a);
 #pragma unroll
         for (int j = 0; j < H; ++j) {
             const int e = 2 * (t + T * j);
-            const float2 xa = make_float2((float)v[j].y, __shfl_xor((float)v[kE - 1 - j].y, T - 1));
-            const float2 xb = make_float2((float)v[j].x, __shfl_xor((float)v[kE - 1 - j].x, T - 1));
+            const float2 xa = make_float2(result(v[j].y, cut), __shfl_xor(result(v[kE - 1 - j].y, cut), T - 1));
+            const float2 xb = make_float2(result(v[j].x, cut), __shfl_xor(result(v[kE - 1 - j].x, cut), T - 1));
             if (a.vec2) {
                 if (live) *reinterpret_cast<float2*>(out + fbase + e) = xa;
                 if (two) *reinterpret_cast<float2*>(out + fbase2 + e) = xb;
@@ -562,12 +624,12 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
     } else {
         if (!live) return;  // (no barrier follows)
         if (a.vec2) {
-            float* p0 = out + base + es * (2 * t);
-            float* p1 = out + base + es * (N - 1 - 2 * t);
+            double* p0 = W + base + es * (2 * t);
+            double* p1 = W + base + es * (N - 1 - 2 * t);
 #pragma unroll
             for (int j = 0; j < H; ++j) {
-                *reinterpret_cast<float2*>(p0) = make_float2((float)v[j].y, (float)v[j].x);
-                *reinterpret_cast<float2*>(p1) = make_float2((float)v[H + j].y, (float)v[H + j].x);
+                *reinterpret_cast<double2*>(p0) = make_double2(v[j].y, v[j].x);
+                *reinterpret_cast<double2*>(p1) = make_double2(v[H + j].y, v[H + j].x);
                 p0 += es * (2 * T);
                 p1 -= es * (2 * T);
             }
@@ -577,8 +639,8 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
         for (int j = 0; j < kE; ++j) {
             const int m = t + T * j;
             const int64_t o = es * (j < H ? 2 * m : 2 * N - 1 - 2 * m);
-            out[base + o] = (float)v[j].y;
-            if (two) out[base2 + o] = (float)v[j].x;
+            W[base + o] = v[j].y;
+            if (two) W[base2 + o] = v[j].x;
         }
     }
 }
@@ -598,8 +660,10 @@ __device__ __forceinline__ int d_row(int r, int lane) { return 4 * r + (lane >> 
 // phases overlap another's.  Measured, 32 -> 16 lines: 66 us -> 61 forward or
 // back along contiguous n = 275 for 7.5M cells (30 us at the 78.6 TFLOP/s of
 // the float64 matrix cores, which bound it together with the phases), 51 ->
-// 50 along strided 147, gain pass along 93 66 -> 65; 96 x 64 x 80 cells, 2
-// fields: 19.4 -> 15.1 us for the gain pass, 13.6 -> 10.5 and 11.7 -> 8.9 along x.
+// 50 along strided 147, gain pass along 93 66 -> 65 (with float32 vectors
+// between the passes; with float64 ones 62 and 65, 54 and 48, 70); 96 x 64 x
+// 80 cells, 2 fields: 19.4 -> 15.1 us for the gain pass (now 19.7), 13.6 ->
+// 10.5 and 11.7 -> 8.9 along x (now 12.6 and 9.7).
 template <int MODE, bool XK, bool SPLIT, int kTL>
 __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     extern __shared__ double shd[];
@@ -608,11 +672,14 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     const int n = a.n, hm = a.hm, ho = a.ho, mt = (hm + 15) / 16, rows = 16 * mt;
     double* E = shd;
     double* O = shd + (size_t)rows * TLP;
-    if (MODE == 1 && a.last && is_bad(a)) return;
-    if (MODE == 0 && a.first) clear_bad(a);
-    const float* __restrict__ in = a.in + (size_t)blockIdx.y * (XK && MODE == 0 ? a.fcells : a.cells);
-    float* __restrict__ out = a.out + (size_t)blockIdx.y * (XK && MODE == 1 ? a.fcells : a.cells);
-    // 16 strided lines are half a cache line: the two blocks that share one go to one XCD
+    if (MODE == 1 && XK && is_bad(a)) return;
+    if (MODE == 0 && XK) clear_notes(a);
+    const float* __restrict__ in = a.in + (size_t)blockIdx.y * a.fcells;
+    float* __restrict__ out = a.out + (size_t)blockIdx.y * a.fcells;
+    double* __restrict__ W = a.W + (size_t)blockIdx.y * a.cells;
+    // 16 strided lines share cache lines with the next block's (unless rows
+    // are a multiple of 16 long): the two blocks go to one XCD (y at 275 x 147
+    // x 93, 2 fields: 54 us against 59)
     unsigned lb = blockIdx.x;
     if (!SPLIT && !XK && lb < gridDim.x / 16 * 16) lb = lb / 16 * 16 + lb % 8 * 2 + lb / 8 % 2;
     const int64_t l0 = (int64_t)lb * kTL;
@@ -627,14 +694,23 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     };
     // E and O: x[m] +- x[N-1-m], or (inverse) the even and odd modes.  Loads
     // at clamped places, four pairs in flight per thread.
-    auto fill = [&](const float* __restrict__ src, int64_t step, int m0, int dm, int line, bool ok) {
+    bool negative = false, within = true;
+    auto fill = [&](const auto* __restrict__ src, int64_t step, int m0, int dm, int line, bool ok) {
         for (int m = m0; m < rows; m += 4 * dm) {
-            float u[4], w[4];
+            std::remove_cv_t<std::remove_reference_t<decltype(*src)>> u[4], w[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int mc = std::min(m + i * dm, hm - 1);
                 u[i] = src[step * mc];
                 w[i] = src[step * (MODE == 1 ? std::min(hm + mc, n - 1) : n - 1 - mc)];
+            }
+            if (MODE == 0 && XK) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) negative = negative || (ok && (u[i] < 0 || w[i] < 0));
+            }
+            if (MODE == 2) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) within = within && (!ok || (carried(u[i]) && carried(w[i])));
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -650,12 +726,15 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     if (XK) {
         for (int line = wave; line < kTL; line += nw) {
             const bool ok = l0 + line < a.lines;
-            fill(in + (ok ? base_of(l0 + line, MODE == 0) : (MODE == 0 ? a.off : 0)), 1, lane, 64, line, ok);
+            if constexpr (MODE == 0) fill(in + (ok ? base_of(l0 + line, true) : a.off), 1, lane, 64, line, ok);
+            else fill(W + (ok ? base_of(l0 + line, false) : 0), 1, lane, 64, line, ok);
         }
+        if (MODE == 0) mark_negative(a, negative);
     } else {
         const int line = threadIdx.x % kTL;
         const bool ok = l0 + line < a.lines;
-        fill(in + (ok ? base_of(l0 + line, false) : 0), es, threadIdx.x / kTL, nw * 64 / kTL, line, ok);
+        fill(W + (ok ? base_of(l0 + line, false) : 0), es, threadIdx.x / kTL, nw * 64 / kTL, line, ok);
+        if (MODE == 2 && !within) mark_bad(a);
     }
     __syncthreads();
     v4d ae[CT], ao[CT];
@@ -713,16 +792,15 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
                 const int k = tile * 16 + (XK ? (lane & 15) : d_row(r, lane));
                 const int line = c0 + c * 16 + (XK ? d_row(r, lane) : (lane & 15));
                 if (l0 + line >= a.lines || k >= hm) continue;
-                float* dst = out + base_of(l0 + line, false);
-                dst[es * k] = (float)ae[c][r];
-                if (k < ho) dst[es * (hm + k)] = (float)ao[c][r];
+                double* dst = W + base_of(l0 + line, false);
+                dst[es * k] = ae[c][r];
+                if (k < ho) dst[es * (hm + k)] = ao[c][r];
             }
         }
         return;
     }
     if (MODE == 2) {
         __syncthreads();
-        bool ok = true;
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const int line = c0 + c * 16 + (lane & 15);
@@ -733,7 +811,6 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
             for (int r = 0; r < 4; ++r) {
                 const int k = tile * 16 + d_row(r, lane);
                 const bool ie = k < hm, io = k < ho;
-                ok = ok && (!ie || isfinite(ae[c][r])) && (!io || isfinite(ao[c][r]));
                 const double e = ie ? ae[c][r] * mode_gain(fma(a.cm, a.lamm[k], mu), a.n_steps, a.cn) : 0.0;
                 const double o = io ? ao[c][r] * mode_gain(fma(a.cm, a.lamm[hm + k], mu), a.n_steps, a.cn) : 0.0;
                 if (work) {
@@ -742,10 +819,11 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
                 }
             }
         }
-        if (!ok) mark_bad(a);
         __syncthreads();
     }
     multiply(a.ie, a.io);
+    const float cut = XK ? cut_of(a) : 0.f;
+    double big = 0.0;
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
 #pragma unroll
@@ -753,11 +831,20 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
             const int m = tile * 16 + (XK ? (lane & 15) : d_row(r, lane));
             const int line = c0 + c * 16 + (XK ? d_row(r, lane) : (lane & 15));
             if (l0 + line >= a.lines || m >= hm) continue;
-            float* dst = out + base_of(l0 + line, true);
-            dst[es * m] = (float)(ae[c][r] + ao[c][r]);
-            if (m < ho) dst[es * (n - 1 - m)] = (float)(ae[c][r] - ao[c][r]);
+            const double p = ae[c][r] + ao[c][r], q = ae[c][r] - ao[c][r];
+            if (XK) {
+                float* dst = out + base_of(l0 + line, true);
+                dst[m] = result(p, cut);
+                if (m < ho) dst[n - 1 - m] = result(q, cut);
+            } else {
+                double* dst = W + base_of(l0 + line, false);
+                dst[es * m] = p;
+                if (m < ho) dst[es * (n - 1 - m)] = q;
+                big = fmax(big, fmax(fabs(p), m < ho ? fabs(q) : 0.0));
+            }
         }
     }
+    if (MODE == 2) note_top(a, big);
 }
 
 // ------------------------------------------------------------------ tables
@@ -804,6 +891,10 @@ __global__ __launch_bounds__(256) void k_spec_tables(int n, int fft, double* lam
         ie[i] = row < hm && col < hm ? entry(2 * col, row) : 0.0;
         io[i] = row < ho && col < ho ? entry(2 * col + 1, row) : 0.0;
     }
+}
+
+__global__ void k_spec_clear(uint32_t* p, int n) {
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0u;
 }
 
 bool fft_length(int n) { return n == 128 || n == 256 || n == 512 || n == 1024; }
@@ -1031,15 +1122,15 @@ static const SpecTables* grid_of(cgd_mesh m) {
     return m->spec;
 }
 
-// Fields per group: their vector W (with the field itself about 256 MB) stays
+// Fields per group: their vector W (with the field itself about 192 MB) stays
 // in the memory-side cache between the passes.
 static int fields_per_group(const cgd_mesh m, int F) {
-    const int64_t most = (int64_t)128 * 1024 * 1024 / (m->spec->cells * (int64_t)sizeof(float));
+    const int64_t most = (int64_t)128 * 1024 * 1024 / (m->spec->cells * (int64_t)sizeof(double));
     return (int)std::max<int64_t>(1, std::min<int64_t>(F, most));
 }
 
 size_t spectral_bytes(const cgd_mesh m, int32_t F) {
-    return (size_t)fields_per_group(m, F) * m->spec->cells * sizeof(float);
+    return (size_t)fields_per_group(m, F) * (m->spec->cells * sizeof(double) + kTopSlots * kTopStride * sizeof(uint32_t));
 }
 
 // The direct solve stands in for the CG where nothing asks for the CG itself:
@@ -1089,13 +1180,17 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
         total += t->eigen[a] ? (((size_t)t->n[a] + 1) & ~(size_t)1) + 4 * dense_fragment(t->n[a], t->sym[a])
                              : table_doubles(t->n[a]);
     }
+    const size_t neg = total;  // after the tables: a 32-bit word per field
+    total += kSpecFields / 2;
     void* dev = nullptr;
     if (hipMalloc(&dev, total * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
         set_error("allocation of the transform tables failed");
         return CGD_E_NOMEM;
     }
-    hipError_t e = hipSuccess;
+    t->neg = reinterpret_cast<uint32_t*>(static_cast<double*>(dev) + neg);
+    hipLaunchKernelGGL(k_spec_clear, dim3(8), dim3(256), 0, s, t->neg, kSpecFields);
+    hipError_t e = hipGetLastError();
     for (int a = 0; a < t->rank && e == hipSuccess; ++a) {
         SpecAxis& x = t->axis[a];
         double* p = static_cast<double*>(dev) + off[a];
@@ -1142,16 +1237,27 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
     return CGD_OK;
 }
 
-cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, float* W, int* bad, int* bad_host,
+cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, double* W, int* bad, int* bad_host,
                             hipStream_t s) {
     cgd_status rc = spectral_tables(m, s);
     if (rc != CGD_OK) return rc;
+    if (++m->spec->calls == 0) ++m->spec->calls;  // (0 is what the notes start from)
     const SpecTables& tb = *m->spec;
     const int rank = tb.rank;
     const int* n = tb.n;
     double c[3];
     const double dtau = da.bandwidth * da.bandwidth / 4.0 / da.n_steps * (da.scheme == 1 ? 0.5 : 1.0);
     for (int a = 0; a < rank; ++a) c[a] = dtau * tb.scale[a];
+    // the mode that holds a plane's sum, over its mean (a weighted one on an eigenvector axis)
+    double plane = 1.0;
+    for (int a = 0; a + 1 < rank; ++a) {
+        double len = n[a];
+        if (tb.eigen[a]) {
+            len = 0.0;
+            for (double w : tb.h[a]) len += w;
+        }
+        plane *= len;
+    }
     SpecPass pass[3];
     for (int ax = 0; ax < rank; ++ax) {
         SpecPass& p = pass[ax];
@@ -1189,8 +1295,9 @@ cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, flo
         p.ostride = st * n[ax];
         p.pairs = ax == 0 ? (p.lines + 1) / 2 : p.inner_pairs * (p.lines / st);
         p.vec2 = ax > 0 && st % 2 == 0;
-        p.in = W;
-        p.out = W;
+        p.W = W;
+        p.call = tb.calls;
+        p.cut = 0x1p-32 / sqrt(plane);
     }
     SpecPass& z = pass[rank - 1];
     z.cm = c[rank - 1];
@@ -1203,16 +1310,19 @@ cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, flo
         z.lam1 = m->spec->axis[1].lam;
     }
     const int group = fields_per_group(m, n_fields);
+    uint32_t* top = reinterpret_cast<uint32_t*>(W + (size_t)group * tb.cells);
     for (int f0 = 0; f0 < n_fields; f0 += group) {
         const int nf = std::min(group, n_fields - f0);
         float* field = da.field + (size_t)f0 * m->cells;
         for (int ax = 0; ax < rank; ++ax) {
             pass[ax].bad = bad + f0;
             pass[ax].bad_host = bad_host ? bad_host + f0 : nullptr;
+            pass[ax].top = top;
+            pass[ax].neg = tb.neg + f0;
         }
         SpecPass x = pass[0];
         x.in = field;
-        x.first = 1;
+        x.out = field;
         x.vec2 = reinterpret_cast<uintptr_t>(field) % 8 == 0 && tb.off % 2 == 0 &&
                  (tb.rows_y ? (tb.sy | tb.sz) % 2 == 0 : tb.pitch % 2 == 0) && (nf == 1 || m->cells % 2 == 0);
         rc = launch_pass<0, true>(x, nf, s);
@@ -1220,10 +1330,6 @@ cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, flo
         if (rc == CGD_OK) rc = launch_pass<2, false>(z, nf, s);
         if (rc == CGD_OK && rank == 3) rc = launch_pass<1, false>(pass[1], nf, s);
         if (rc != CGD_OK) return rc;
-        x.in = W;
-        x.out = field;
-        x.first = 0;
-        x.last = 1;
         rc = launch_pass<1, true>(x, nf, s);
         if (rc != CGD_OK) return rc;
     }
@@ -1239,7 +1345,7 @@ cgd_status diffuse_spectral(cgd_mesh m, const DiffuseArgs& da, hipStream_t s) {
     char* base = static_cast<char*>(m->ws.ptr);
     int* bad_host = reinterpret_cast<int*>(static_cast<char*>(m->pinned) + kPinStatus);
     for (int f = 0; f < da.F; ++f) bad_host[f] = 0;
-    rc = spectral_enqueue(m, da, da.F, reinterpret_cast<float*>(base + kSmallFixed),
+    rc = spectral_enqueue(m, da, da.F, reinterpret_cast<double*>(base + kSmallFixed),
                           reinterpret_cast<int*>(base + kOffStatus), bad_host, s);
     if (rc != CGD_OK) return rc;
     CGD_HIP_TRY(hipStreamSynchronize(s));
