@@ -19,6 +19,11 @@ struct SpecAxis {
     double* io = nullptr;
 };
 
+// The cells that diffuse, lo .. lo + len of a grid of nn per axis.
+struct SpecBox {
+    int nn[3], lo[3], len[3];
+};
+
 // What the transforms need to know of a mesh: the box of cells that diffuse
 // (a uniform grid: all of them; a rectilinear one: those with a diffusivity),
 // its axes of more than one cell, the contiguous one first.  Owned by the
@@ -38,6 +43,7 @@ struct SpecTables {
     int64_t sy = 0, sz = 0;   //    and the strides between rows and planes in a field
     int64_t pitch = 0;        // else the stride between rows
     int64_t cells = 0;        // of the box
+    SpecBox box = {};
     double* dev = nullptr;
     SpecAxis axis[3];
     uint32_t* neg = nullptr;  // device, [kSpecFields] (SpecPass)

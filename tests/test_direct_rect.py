@@ -117,3 +117,32 @@ def test_rect_not_finite(gpu_lib):
         cgd.diffuse(mesh, f, 0.2, 2)
     assert err.value.status == -5
     assert torch.allclose(f[0], torch.ones_like(f[0]), rtol=1e-6)
+
+
+@pytest.mark.parametrize("where", [(0, 0, 0), (19, 5, 4), (5, 0, 4), (5, 5, 9), (2, 5, 4)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_rect_not_finite_outside_the_box(gpu_lib, where, bad, monkeypatch):
+    """A value that is not finite in a cell without diffusivity: the CG's
+    status, for its field alone."""
+    import torch
+    cgd = gpu_lib
+    shape, cut = (20, 12, 10), ((3, 2), (1, 2), (1, 1))
+    e = [_edges(n, 0.0, 1.0, "mirror", 1) for n in shape]
+    D = np.zeros(shape[::-1], np.float32)
+    D[tuple(slice(cut[a][0], shape[a] - cut[a][1]) for a in (2, 1, 0))] = 1.0
+    mesh = cgd.RectMesh(*e, diffusivity=D.ravel())
+    f = np.ones((2, mesh.cells), np.float32)
+    f[1, where[0] + 20 * (where[1] + 12 * where[2])] = bad
+    assert D[where[::-1]] == 0
+    print(f"case: direct rect {bad} at {where}", flush=True)
+    status = []
+    for env in (None, "1"):
+        if env:
+            monkeypatch.setenv("CGD_NO_DIRECT", env)
+        t = torch.from_numpy(f).cuda()
+        with pytest.raises(cgd.CgdError) as err:
+            cgd.diffuse(mesh, t, 0.2, 2)
+        status.append(err.value.status)
+        if not env:  # (the CG leaves the field beside it to its own tolerance)
+            assert torch.allclose(t[0], torch.ones_like(t[0]), rtol=1e-6)
+    assert status == [-5, -5]
