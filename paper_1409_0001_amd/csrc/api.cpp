@@ -440,7 +440,7 @@ static cgd_status do_diffuse(cgd_mesh m, const DiffuseArgs& a, cgd_solve_stats* 
         set_error("x0_mode 3: the network must be created for this hex mesh's grid, on its device");
         return CGD_E_INVALID;
     }
-    if (spectral_applies(m, a, a.F, st != nullptr)) return diffuse_spectral(m, a, s);
+    if (spectral_applies(m, a, st != nullptr)) return diffuse_spectral(m, a, s);
     if (m->kind == 0) return diffuse_hex(m, a, st, s);
     return diffuse_tet(m, a, st, s);
 }
@@ -484,7 +484,7 @@ cgd_status cgd_coarse_grain(cgd_mesh m, int64_t n, const float* pos, int32_t F, 
     }
     if (st) memset(st, 0, sizeof(*st));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (spectral_applies(m, a, a.F, st != nullptr)) {
+    if (spectral_applies(m, a, st != nullptr)) {
         rc = do_deposit(m, n, pos, F, values, field, nullptr, nullptr, nullptr, s, kSmallFixed + spectral_bytes(m, F));
         return rc < 0 ? rc : diffuse_spectral(m, a, s);
     }

@@ -777,7 +777,7 @@ cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offse
     const int64_t total = offsets[n_snap];
     const size_t cells = (size_t)m->cells;
     // a forced candidate (CGD_BATCHED_CFG) is one of the CG solvers below
-    const bool direct = !cg_only && spectral_applies(m, da, n_rhs, st_out != nullptr) && !getenv("CGD_BATCHED_CFG");
+    const bool direct = !cg_only && spectral_applies(m, da, st_out != nullptr) && !getenv("CGD_BATCHED_CFG");
     int ci = 0;
     cgd_status rc = direct ? CGD_OK : autotune_batched(m, n_rhs, &ci, nullptr, nullptr);
     if (rc != CGD_OK) return rc;

@@ -92,9 +92,9 @@ struct SpecPass {
     double cut;     // results below cut * (the largest of top) of a field without negative values are 0
 };
 
-// Whether a call on n_fields fields is answered by the direct solve (stats:
-// its statistics are asked for).
-bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stats);
+// Whether a call is answered by the direct solve (stats: its statistics are
+// asked for); the same for any number of fields.
+bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, bool stats);
 // Bytes of scratch (W) for F fields, where spectral_applies.
 size_t spectral_bytes(const cgd_mesh m, int32_t F);
 // Enqueues all steps of `da` on n_fields fields at da.field [n_fields][cells]

@@ -1164,14 +1164,18 @@ size_t spectral_bytes(const cgd_mesh m, int32_t F) {
 // the default stay with the CG's recursive residual); where the CG would
 // have converged within max_iter by its bound for the unpreconditioned
 // operator, so that a call that came back not converged still does; and
-// where it is the faster one: a transform takes about 2 ps per cell for an
-// FFT length and 2.5 + 0.022 n for a dense one (7.5M cells: 61 us at n = 275,
-// 50 at 147, 33 at 93), the CG 25 ps per cell and step at its best
-// (256 x 256 x 512, dtau / h^2 = 1) and 50 us and more per step in launches
-// on the smallest grids, so only one or two steps on lengths of hundreds that
-// are no FFT lengths are left to the CG.  Rectilinear grids: the CG takes 136
-// ps per cell and step (128 x 128 x 256, diffusivity 0 in the outer layers).
-bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stats) {
+// where it is the faster one: a transform takes about 2.45 ps per cell for an
+// FFT length and 3.3 + 0.021 n for a dense one (7.5M cells: 62 and 65 us at n
+// = 275, 54 and 48 at 147, 35 at 93), the CG 25 ps per cell and step at its
+// best (256 x 256 x 512, dtau / h^2 = 1) and 50 us and more per step in
+// launches on the smallest grids, so only one or two steps on lengths of
+// hundreds that are no FFT lengths are left to the CG (1 step at b = 2h and 4h,
+// 275 x 147 x 93: direct 189 us, CG 160 and 360; 400 x 300 x 64: 381, 214 and
+// 538; 120^3: 109, 201 and 203).  Rectilinear grids: the CG takes 136 ps per
+// cell and step (128 x 128 x 256, diffusivity 0 in the outer layers).  The
+// times are one field's, whatever their number, so that a field comes out as
+// the same bits alone, among others and in a batch.
+bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, bool stats) {
     if (stats || da.x0_mode != 0 || da.precond != 0 || da.rtol < 5e-7) return false;
     if (m->kind == 2 ? !m->rop || getenv("CGD_RECT_SLOTS") : m->kind != 0) return false;
     if (getenv("CGD_NO_DIRECT") || getenv("CGD_HEX_PRECOND_DEG")) return false;
@@ -1180,8 +1184,8 @@ bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, int n_fields, bool stat
     const double dtau = da.bandwidth * da.bandwidth / 4.0 / da.n_steps * (da.scheme == 1 ? 0.5 : 1.0);
     double ps = 0.0;
     for (int a = 0; a < t->rank; ++a)
-        ps += 2.0 * (!t->eigen[a] && fft_length(t->n[a]) ? 2.0 : 2.5 + (t->sym[a] ? 0.022 : 0.044) * t->n[a]);
-    const double mcells = 1e-6 * (double)m->cells * n_fields;
+        ps += 2.0 * (!t->eigen[a] && fft_length(t->n[a]) ? 2.45 : 3.3 + (t->sym[a] ? 0.021 : 0.042) * t->n[a]);
+    const double mcells = 1e-6 * (double)m->cells;
     if (25.0 + mcells * ps > da.n_steps * (50.0 + mcells * (m->kind == 0 ? 25.0 : 100.0))) return false;
     const double r = sqrt(1.0 + 2.0 * dtau * t->diag);
     return 0.5 * r * log(2.0 * r / std::min(da.rtol, 1.0)) + 1.0 <= (double)da.max_iter;

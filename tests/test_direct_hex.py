@@ -159,3 +159,24 @@ def test_direct_batched(gpu_lib, F, counts):
     with pytest.raises(cgd.CgdError) as e:
         cgd.coarse_grain_batched(mesh, off, pos, vals, 0.08, 3)
     assert e.value.status == -2
+
+
+# near the line of the cost rule, one step: FFT and matrix lengths, and one that stays with the CG
+@pytest.mark.parametrize("shape", [(120, 120, 120), (128, 100, 90), (300, 100, 60)])
+def test_route_does_not_depend_on_the_number_of_fields(gpu_lib, shape):
+    """A field alone, among four and in a batch: the same bits."""
+    import torch
+    cgd = gpu_lib
+    mesh = cgd.HexMesh(shape)
+    p = inputs.uniform_bed(inputs.HexBox((0, 0, 0), (1, 1, 1), shape), 60_000, 4, seed=8, diam=0.01)
+    pos, vals = torch.from_numpy(p.pos).cuda(), torch.from_numpy(p.values).cuda()
+    print(f"case: route {shape}", flush=True)
+    four = cgd.coarse_grain(mesh, pos, vals, 0.03, 1)[0]
+    off = np.array([0, 60_000, 120_000], np.int64)
+    batch = cgd.coarse_grain_batched(mesh, off, torch.cat([pos, pos]), torch.cat([vals, vals], dim=1).contiguous(), 0.03, 1)
+    for f in range(4):
+        one = cgd.coarse_grain(mesh, pos, vals[f:f + 1].contiguous(), 0.03, 1)[0]
+        assert torch.equal(one[0].view(torch.int32), four[f].view(torch.int32)), f
+    if shape[0] != 300:  # (the batched CG's sums differ from the single call's, as before)
+        assert torch.equal(batch[0].view(torch.int32), four.view(torch.int32))
+        assert torch.equal(batch[1].view(torch.int32), four.view(torch.int32))
