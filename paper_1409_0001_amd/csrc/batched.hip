@@ -771,13 +771,13 @@ cgd_status autotune_batched(cgd_mesh m, int n_rhs, int* chosen, double* ms_out, 
 
 cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offsets, const float* pos, int32_t F,
                                 const float* values, const DiffuseArgs& da, float* fields, cgd_solve_stats* st_out,
-                                hipStream_t s, bool cg_only) {
+                                hipStream_t s) {
     const HexGeom& g = m->hex;
     const int n_rhs = n_snap * F;
     const int64_t total = offsets[n_snap];
     const size_t cells = (size_t)m->cells;
     // a forced candidate (CGD_BATCHED_CFG) is one of the CG solvers below
-    const bool direct = !cg_only && spectral_applies(m, da, st_out != nullptr) && !getenv("CGD_BATCHED_CFG");
+    const bool direct = spectral_applies(m, da, st_out != nullptr) && !getenv("CGD_BATCHED_CFG");
     int ci = 0;
     cgd_status rc = direct ? CGD_OK : autotune_batched(m, n_rhs, &ci, nullptr, nullptr);
     if (rc != CGD_OK) return rc;
@@ -937,24 +937,34 @@ cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offse
     if (direct) {
         // The direct solve needs no iteration counts, so nothing is learned,
         // tuned or captured: five launches per group of right-hand sides.
-        // Per right-hand side the status array holds whether a mode was not
-        // finite; then the whole call goes round again by CG, which says
-        // what it makes of such values.
+        // Per right-hand side the status array holds whether the transforms
+        // could not carry it; it is as it was then, and solved by CG alone,
+        // as in its own cgd_coarse_grain.
         rc = enqueue_deposit(s);
         if (rc != CGD_OK) return rc;
         rc = spectral_enqueue(m, da, n_rhs, static_cast<double*>(big), d_status, nullptr, s);
         if (rc != CGD_OK) return rc;
         CGD_HIP_TRY(hipMemcpyAsync(pin + P.status, base + L.status, L.maxbits - L.status, hipMemcpyDeviceToHost, s));
         CGD_HIP_TRY(hipStreamSynchronize(s));
-        for (int r = 0; r < n_rhs; ++r)
-            if (h_status[r])
-                return coarse_grain_batched(m, n_snap, offsets, pos, F, values, da, fields, st_out, s, true);
-        for (int j = 0; j < n_snap; ++j)
-            if (h_counters[2 * j + 1]) {
-                set_error("non-finite particle positions or values were skipped");
-                return CGD_E_NONFINITE;
-            }
-        return CGD_OK;
+        bool nonfinite = false;
+        for (int j = 0; j < n_snap; ++j) nonfinite = nonfinite || h_counters[2 * j + 1];
+        const std::vector<int> bad(h_status, h_status + n_rhs);
+        cgd_status worst = CGD_OK;
+        for (int r = 0; r < n_rhs; ++r) {
+            if (!bad[r]) continue;
+            DiffuseArgs d1 = da;
+            d1.F = 1;
+            d1.field = fields + (size_t)r * cells;
+            rc = diffuse_hex(m, d1, nullptr, s);
+            if (rc < 0 && rc != CGD_E_BREAKDOWN) return rc;
+            if (rc == CGD_E_BREAKDOWN) set_error("CG breakdown in right-hand side " + std::to_string(r));
+            if (rc == CGD_E_BREAKDOWN || worst == CGD_OK) worst = rc;
+        }
+        if (worst == CGD_OK && nonfinite) {
+            set_error("non-finite particle positions or values were skipped");
+            worst = CGD_E_NONFINITE;
+        }
+        return worst;
     }
 
     // everything the call does, in stream order; budget: the per-launch

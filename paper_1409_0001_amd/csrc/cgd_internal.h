@@ -302,7 +302,7 @@ bool unet_matches(cgd_unet u, int nx, int ny, int nz, int device);
 // batched.hip
 cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offsets, const float* pos, int32_t F,
                                 const float* values, const DiffuseArgs& da, float* fields, cgd_solve_stats* st_out,
-                                hipStream_t s, bool cg_only = false);
+                                hipStream_t s);
 cgd_status autotune_batched(cgd_mesh m, int n_rhs, int* chosen, double* ms_out, int* n_cand);
 void destroy_batched(cgd_mesh m);
 

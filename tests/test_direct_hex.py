@@ -180,3 +180,46 @@ def test_route_does_not_depend_on_the_number_of_fields(gpu_lib, shape):
     if shape[0] != 300:  # (the batched CG's sums differ from the single call's, as before)
         assert torch.equal(batch[0].view(torch.int32), four.view(torch.int32))
         assert torch.equal(batch[1].view(torch.int32), four.view(torch.int32))
+
+
+@pytest.mark.parametrize("kind", ["overflow", "infinite"])
+def test_batched_hands_over_single_right_hand_sides(gpu_lib, kind):
+    """A snapshot with one field that the transforms cannot carry: every field
+    of the batch, that one and the healthy ones, is the bits of its own
+    cgd_coarse_grain, and the status is its status."""
+    import torch
+    cgd = gpu_lib
+    shape, n = (128, 16, 12), 40_000
+    mesh = cgd.HexMesh(shape)
+    box = inputs.HexBox((0, 0, 0), (1, 1, 1), shape)
+    parts = [inputs.uniform_bed(box, n, 2, seed=20 + j, diam=0.01) for j in range(3)]
+    pos = torch.from_numpy(np.concatenate([p.pos for p in parts])).cuda()
+    vals = np.ascontiguousarray(np.concatenate([p.values for p in parts], axis=1))
+    # mean density 1.2e37: finite, its x-y modes are not (1.2e37 * sqrt(128 * 16)); or an infinite density
+    vals[1, n:2 * n] = np.float32(1.2e37 / n if kind == "overflow" else 3e38)
+    vals = torch.from_numpy(vals).cuda()
+    off = np.array([0, n, 2 * n, 3 * n], np.int64)
+    print(f"case: batched hand-over {kind}", flush=True)
+
+    def call(f):
+        try:
+            f()
+            return 0, ""
+        except cgd.CgdError as e:
+            return e.status, str(e)
+
+    out = torch.full((3, 2, mesh.cells), -1.0, device="cuda")
+    status, message = call(lambda: cgd.coarse_grain_batched(mesh, off, pos, vals, 0.01, 3, fields=out))
+    want = 0
+    for j in range(3):
+        s = slice(j * n, (j + 1) * n)
+        one = torch.full((2, mesh.cells), -1.0, device="cuda")
+        st, _ = call(lambda: cgd.coarse_grain(mesh, pos[s].contiguous(), vals[:, s].contiguous(), 0.01, 3, field=one))
+        want = want or st
+        if kind == "overflow" or j != 1:
+            assert torch.equal(one.view(torch.int32), out[j].view(torch.int32)), j
+        else:
+            assert torch.equal(one[0].view(torch.int32), out[j][0].view(torch.int32))
+    assert status == want == (0 if kind == "overflow" else -5)
+    if kind == "infinite":
+        assert "right-hand side 3" in message
