@@ -1394,6 +1394,11 @@ cgd_status diffuse_spectral(cgd_mesh m, const DiffuseArgs& da, hipStream_t s) {
         d1.field = da.field + (size_t)todo[i] * m->cells;
         rc = m->kind == 0 ? diffuse_hex(m, d1, nullptr, s) : diffuse_tet(m, d1, nullptr, s);
         if (rc < 0 && rc != CGD_E_BREAKDOWN) return rc;
+        if (rc == CGD_E_BREAKDOWN) {  // (solved as the only field of its call: give its own number)
+            std::string e = cgd_last_error();
+            const size_t at = e.rfind(", field ");
+            if (at != std::string::npos) set_error(e.substr(0, at) + ", field " + std::to_string(todo[i]));
+        }
         if (rc == CGD_E_BREAKDOWN || worst == CGD_OK) worst = rc;
     }
     return worst;

@@ -143,6 +143,7 @@ def test_rect_not_finite_outside_the_box(gpu_lib, where, bad, monkeypatch):
         with pytest.raises(cgd.CgdError) as err:
             cgd.diffuse(mesh, t, 0.2, 2)
         status.append(err.value.status)
+        assert str(err.value).endswith(", field 1")
         if not env:  # (the CG leaves the field beside it to its own tolerance)
             assert torch.allclose(t[0], torch.ones_like(t[0]), rtol=1e-6)
     assert status == [-5, -5]
