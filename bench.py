@@ -85,26 +85,28 @@ def traffic_from_profiles():
 
 # Timed kernels (cgd_timing_read kinds) that are one kernel each; "deposit"
 # spans several and is split into its stages.
-DIRECT = "direct_transform_passes"
-SOLVE_KERNELS = (DIRECT, "cg_sweep1", "cg_sweep2", "cg_precond_pass1", "cg_precond_pass_mid", "cg_precond_pass_last",
+SOLVE_KERNELS = ("cg_sweep1", "cg_sweep2", "cg_precond_pass1", "cg_precond_pass_mid", "cg_precond_pass_last",
                  "cg_first_sweep1", "cg_first_sweep2", "cg_first_precond_pass1", "cg_first_precond_pass_mid",
                  "cg_first_precond_pass_last")
+# What the first two hold where the call was solved directly (no first
+# iteration of a CG was timed).
+DIRECT = {"cg_sweep1": "direct_passes_x", "cg_sweep2": "direct_passes_yz"}
 DEPOSIT_KERNELS = ("deposit_bin", "deposit_scatter", "deposit_accum")
 
 
-def roofline_of(tim, ms_per_field, solve):
+def roofline_of(tim, ms_per_field):
     """Every timed kernel ranked by its total time on the last timed step;
     the dominant one (most total time) gives the roofline line: its
     algorithmic bytes per launch over its mean launch time, against 8 TB/s.
-    solve: the direct solve's (passes, ms of all of them, bytes per pass),
-    timed as cgd.diffuse calls of their own; its five transform passes count
-    as launches of one kernel.  Also the whole solve's and the whole call's
-    algorithmic bytes over their time."""
+    Also the whole solve's and the whole call's algorithmic bytes over their
+    time."""
     rows = []
-    for k in SOLVE_KERNELS + DEPOSIT_KERNELS:
-        n, ms, bpl = solve if k == DIRECT and solve else tim.get(k, (0, 0.0, 0.0))
+    direct = not any(tim[k][0] for k in SOLVE_KERNELS[2:])
+    solve_names = tuple(DIRECT.get(k, k) if direct else k for k in SOLVE_KERNELS)
+    for k, name in zip(SOLVE_KERNELS + DEPOSIT_KERNELS, solve_names + DEPOSIT_KERNELS):
+        n, ms, bpl = tim.get(k, (0, 0.0, 0.0))
         if n:
-            rows.append((k, n, ms, bpl))
+            rows.append((name, n, ms, bpl))
     rows.sort(key=lambda r: -r[2])
     dom, launches, total_ms, bpl = rows[0]
     avg_ms = total_ms / launches
@@ -116,8 +118,8 @@ def roofline_of(tim, ms_per_field, solve):
     ranked = [{"kernel": k, "launches": n, "total_us": round(ms * 1e3, 1), "avg_us": round(ms / n * 1e3, 2),
                "algorithmic_bytes_per_launch": b, "achieved_GBs": round(b / (ms / n * 1e-3) / 1e9, 1),
                "frac": round(b / (ms / n * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)} for k, n, ms, b in rows]
-    sb = sum(b * n for k, n, ms, b in rows if k in SOLVE_KERNELS)
-    st = sum(ms for k, n, ms, b in rows if k in SOLVE_KERNELS)
+    sb = sum(b * n for k, n, ms, b in rows if k in solve_names)
+    st = sum(ms for k, n, ms, b in rows if k in solve_names)
     db = sum(b * n for k, n, ms, b in rows if k in DEPOSIT_KERNELS)
     return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
@@ -227,8 +229,8 @@ def bench_batched(args):
     torch.cuda.synchronize()
     dt_loop = time.perf_counter() - t
     it_total = int(iters.sum())
-    # direct solve: five transform passes of 8 bytes per cell
-    alg_bytes = 40.0 * mesh.cells * n_rhs
+    # direct solve: two transform passes of 12 bytes per cell, three of 16
+    alg_bytes = 72.0 * mesh.cells * n_rhs
     rel = None
     if not args.no_check:
         from oracle import cgd_oracle as O
@@ -553,24 +555,8 @@ def run_dense(args, w, mesh, pos, vals, scheme, steps, warmup, check=True):
     value = F * steps / dt
     print(f"[bench] {w.name} {scheme}: {ms_per_field:.2f} ms per field, {value:.2f} fields/s",
           file=sys.stderr, flush=True)
-    solve = None
-    if not any(tim[k][0] for k in SOLVE_KERNELS if k != DIRECT):
-        # no CG kernel ran in the timed step: the direct solve, timed on its own
-        # on the deposited fields (five passes of 8 bytes per cell)
-        dep = cgd.deposit(mesh, pos, vals)
-        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-        total = 0.0
-        for i in range(4):
-            work = dep.clone()
-            ev[0].record()
-            cgd.diffuse(mesh, work, w.bandwidth, w.n_steps, rtol=args.rtol, scheme=scheme)
-            ev[1].record()
-            torch.cuda.synchronize()
-            total += ev[0].elapsed_time(ev[1]) if i else 0.0
-        solve = (5, total / 3, 8.0 * F * mesh.cells)
-        del dep, work
     res = {"value": value, "ms_per_field": ms_per_field, "iters": iters,
-           "roofline": roofline_of(tim, ms_per_field, solve),
+           "roofline": roofline_of(tim, ms_per_field),
            "rel_l2": None, "deposit_bit_exact": None}
     if check:
         from oracle import cgd_oracle as O

@@ -474,8 +474,10 @@ cgd_status cgd_conv3_wgrad(int32_t nx, int32_t ny, int32_t nz, int32_t ci, int32
  * queue as little as possible); the elapsed times are collected when the
  * call synchronises (every cgd_diffuse / cgd_coarse_grain does at its end).
  * Kinds (one kernel each unless stated):
- *   0  CG sweep 1 (p = z + beta p_old, A p, p.Ap), hex stencil
- *   1  CG sweep 2 (x += alpha p, r -= alpha A p, r.r), hex stencil
+ *   0  CG sweep 1 (p = z + beta p_old, A p, p.Ap), hex stencil; in a call
+ *      that is solved directly, the transform passes along x
+ *   1  CG sweep 2 (x += alpha p, r -= alpha A p, r.r), hex stencil; in a call
+ *      that is solved directly, the transform passes along the other axes
  *   2  whole deposit: centroid binning, bucketing and fixed-point sums
  *      (all kernels of a call; kinds 13..15 split the tiled hex path)
  *   3  matrix sweep of the CG on face slots (p, A p, p.Ap)

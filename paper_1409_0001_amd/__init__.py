@@ -362,7 +362,9 @@ def timing_enable(mesh: Mesh, on: bool = True):
 
 
 def timing_read(mesh: Mesh, reset: bool = False) -> dict:
-    """{kind name: (launches, total_ms, algorithmic bytes per launch)}."""
+    """{kind name: (launches, total_ms, algorithmic bytes per launch)}.  In a
+    call that is solved directly, "cg_sweep1" holds the transform passes along
+    x and "cg_sweep2" those along the other axes."""
     t = _abi.KernelTiming()
     _check(_abi.load().cgd_timing_read(mesh.handle, ctypes.byref(t), int(bool(reset))),
            "cgd_timing_read", allow=(0,))

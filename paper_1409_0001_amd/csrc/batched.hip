@@ -942,7 +942,7 @@ cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offse
         // as in its own cgd_coarse_grain.
         rc = enqueue_deposit(s);
         if (rc != CGD_OK) return rc;
-        rc = spectral_enqueue(m, da, n_rhs, static_cast<double*>(big), d_status, nullptr, s);
+        rc = spectral_enqueue(m, da, n_rhs, static_cast<double*>(big), d_status, nullptr, nullptr, s);
         if (rc != CGD_OK) return rc;
         CGD_HIP_TRY(hipMemcpyAsync(pin + P.status, base + L.status, L.maxbits - L.status, hipMemcpyDeviceToHost, s));
         CGD_HIP_TRY(hipStreamSynchronize(s));

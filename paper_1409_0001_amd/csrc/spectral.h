@@ -101,8 +101,9 @@ size_t spectral_bytes(const cgd_mesh m, int32_t F);
 // (da.F is not used), with W as scratch; at most kSpecFields.  Where a field
 // has a mode beyond float32 or not finite, its entries of bad and bad_host
 // (nullable, cleared by the caller) are set and the field is left as it was.
+// timing: nullable.
 cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, double* W, int* bad, int* bad_host,
-                            hipStream_t s);
+                            Timing* timing, hipStream_t s);
 // The diffusion of cgd_diffuse by the direct solve; waits for the stream.
 cgd_status diffuse_spectral(cgd_mesh m, const DiffuseArgs& da, hipStream_t s);
 void destroy_spectral(cgd_mesh m);

@@ -1265,7 +1265,7 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
 }
 
 cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, double* W, int* bad, int* bad_host,
-                            hipStream_t s) {
+                            Timing* timing, hipStream_t s) {
     cgd_status rc = spectral_tables(m, s);
     if (rc != CGD_OK) return rc;
     if (++m->spec->calls == 0) ++m->spec->calls;  // (0 is what the notes start from)
@@ -1352,17 +1352,23 @@ cgd_status spectral_enqueue(cgd_mesh m, const DiffuseArgs& da, int n_fields, dou
         x.out = field;
         x.vec2 = reinterpret_cast<uintptr_t>(field) % 8 == 0 && tb.off % 2 == 0 &&
                  (tb.rows_y ? (tb.sy | tb.sz) % 2 == 0 : tb.pitch % 2 == 0) && (nf == 1 || m->cells % 2 == 0);
-        rc = launch_pass<0, true>(x, nf, s);
+        // a timed pass: 12 bytes per cell along x (kind 0), 16 along the other axes (kind 1)
+        auto timed = [&](int kind, cgd_status (*launch)(const SpecPass&, int, hipStream_t), const SpecPass& p) {
+            const int t = timing ? timing_begin(timing, s) : -1;
+            const cgd_status r = launch(p, nf, s);
+            if (timing) timing_end(timing, t, kind, (kind ? 16.0 : 12.0) * (double)tb.cells * nf, s);
+            return r;
+        };
+        rc = timed(0, launch_pass<0, true>, x);
         if (rc == CGD_OK && tb.cells < m->cells) {
             const int64_t rows = (int64_t)tb.box.nn[1] * tb.box.nn[2];
             hipLaunchKernelGGL(k_outside, dim3((unsigned)std::min<int64_t>(2048, (rows + 3) / 4), nf), dim3(256), 0, s, x,
                                tb.box);
         }
-        if (rc == CGD_OK && rank == 3) rc = launch_pass<0, false>(pass[1], nf, s);
-        if (rc == CGD_OK) rc = launch_pass<2, false>(z, nf, s);
-        if (rc == CGD_OK && rank == 3) rc = launch_pass<1, false>(pass[1], nf, s);
-        if (rc != CGD_OK) return rc;
-        rc = launch_pass<1, true>(x, nf, s);
+        if (rc == CGD_OK && rank == 3) rc = timed(1, launch_pass<0, false>, pass[1]);
+        if (rc == CGD_OK) rc = timed(1, launch_pass<2, false>, z);
+        if (rc == CGD_OK && rank == 3) rc = timed(1, launch_pass<1, false>, pass[1]);
+        if (rc == CGD_OK) rc = timed(0, launch_pass<1, true>, x);
         if (rc != CGD_OK) return rc;
     }
     CGD_HIP_TRY(hipGetLastError());
@@ -1378,7 +1384,7 @@ cgd_status diffuse_spectral(cgd_mesh m, const DiffuseArgs& da, hipStream_t s) {
     int* bad_host = reinterpret_cast<int*>(static_cast<char*>(m->pinned) + kPinStatus);
     for (int f = 0; f < da.F; ++f) bad_host[f] = 0;
     rc = spectral_enqueue(m, da, da.F, reinterpret_cast<double*>(base + kSmallFixed),
-                          reinterpret_cast<int*>(base + kOffStatus), bad_host, s);
+                          reinterpret_cast<int*>(base + kOffStatus), bad_host, &m->timing, s);
     if (rc != CGD_OK) return rc;
     CGD_HIP_TRY(hipStreamSynchronize(s));
     timing_collect(&m->timing);

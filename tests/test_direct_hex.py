@@ -223,3 +223,23 @@ def test_batched_hands_over_single_right_hand_sides(gpu_lib, kind):
     assert status == want == (0 if kind == "overflow" else -5)
     if kind == "infinite":
         assert "right-hand side 3" in message
+
+
+def test_direct_passes_are_timed(gpu_lib):
+    """With timing enabled, the transform passes are recorded: two along x,
+    three along the other axes, with the bytes they move."""
+    import torch
+    cgd = gpu_lib
+    shape = (128, 40, 33)
+    mesh = cgd.HexMesh(shape)
+    e0 = torch.from_numpy(_field(shape, 2, 5)).cuda()
+    cgd.timing_enable(mesh, True)
+    for _ in range(2):
+        cgd.diffuse(mesh, e0.clone(), 0.05, 3)
+    cgd.timing_enable(mesh, False)
+    cgd.diffuse(mesh, e0.clone(), 0.05, 3)
+    t = cgd.timing_read(mesh, reset=True)
+    assert t["cg_sweep1"][0] == 4 and t["cg_sweep2"][0] == 6
+    assert t["cg_sweep1"][1] > 0 and t["cg_sweep2"][1] > 0
+    assert t["cg_sweep1"][2] == 24.0 * mesh.cells and t["cg_sweep2"][2] == 32.0 * mesh.cells
+    assert not any(v[0] for k, v in t.items() if k not in ("cg_sweep1", "cg_sweep2"))
