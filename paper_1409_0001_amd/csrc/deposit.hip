@@ -1029,7 +1029,8 @@ struct OrderPlan {
 // bin and scatter, in ten of 2048 they take 7.4.
 static bool order_plan(int64_t cells, int64_t total, int32_t n_snap, int32_t F, OrderPlan* p) {
     int cpt, nt;
-    if (F > 4 || !tile_plan(cells, total, F, &cpt, &nt) || nt > kStageMaxTiles || tile_nsub("CGD_DEPOSIT_NSUB") != 1)
+    if (F > 4 || !tile_plan(cells, total, F, &cpt, &nt) || nt > kStageMaxTiles || tile_nsub("CGD_DEPOSIT_NSUB") != 1 ||
+        tile_nsub("CGD_DEPOSIT_BIN_NSUB") != 1)
         return false;
     if (!getenv("CGD_DEPOSIT_CPT"))
         while ((int64_t)n_snap * nt < 512 && cpt > 64) {

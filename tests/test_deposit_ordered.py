@@ -81,3 +81,19 @@ def test_finished_values_at_the_ends_of_float32(gpu_lib, scale):
     pos = rng.random((n, 3)).astype(np.float32)
     vals = (rng.normal(size=(2, n)) * scale).astype(np.float32)
     _check(gpu_lib, torch, (32, 16, 8), pos, vals, f"ordered deposit values of {scale}")
+
+
+@pytest.mark.parametrize("switch", ["CGD_DEPOSIT_NSUB", "CGD_DEPOSIT_BIN_NSUB"])
+def test_switches_of_the_counting_passes_reach_them(gpu_lib, switch, monkeypatch):
+    """Either switch alone: counted, scattered (timing kind "deposit_scatter"), the same bits."""
+    import torch
+    rng = np.random.default_rng(5)
+    pos = rng.random((50_000, 3)).astype(np.float32)
+    vals = rng.normal(size=(2, 50_000)).astype(np.float32)
+    monkeypatch.setenv(switch, "2")
+    _check(gpu_lib, torch, (40, 30, 20), pos, vals, f"deposit {switch}")
+    mesh = gpu_lib.HexMesh((40, 30, 20))
+    gpu_lib.timing_enable(mesh, True)
+    gpu_lib.deposit(mesh, torch.from_numpy(pos).cuda(), torch.from_numpy(vals).cuda(), stats=True)
+    gpu_lib.diffuse(mesh, torch.ones((1, mesh.cells), device="cuda"), 0.05, 1)
+    assert gpu_lib.timing_read(mesh)["deposit_scatter"][0] == 1
