@@ -1156,9 +1156,18 @@ size_t spectral_bytes(const cgd_mesh m, int32_t F) {
     return (size_t)fields_per_group(m, F) * (m->spec->cells * sizeof(double) + kTopSlots * kTopStride * sizeof(uint32_t));
 }
 
+// The environment switches that choose how the CG runs: set, they mean it.
+static bool switched_to_cg() {
+    for (const char* e : {"CGD_NO_DIRECT", "CGD_HEX_PRECOND_DEG", "CGD_HEX_LDS_ZC", "CGD_HEX_DIR", "CGD_HEX_DIR_NW",
+                          "CGD_HEX_DIR_ZC", "CGD_HEX_NO_SWAP", "CGD_HEX_TILE", "CGD_HEX_TILE1", "CGD_HEX_TILE2",
+                          "CGD_HEX_TILEZ", "CGD_NO_BUDGET"})
+        if (getenv(e)) return true;
+    return false;
+}
+
 // The direct solve stands in for the CG where nothing asks for the CG itself:
 // its iterations and residuals (statistics), a start from a guess, plain CG,
-// or a forced preconditioner degree; where the float32 result can meet the
+// or a switch of its own; where the float32 result can meet the
 // stopping rule's meaning (rounding the result alone leaves a relative
 // residual of up to lmax 2^-25, 4e-7 at dtau / h^2 = 1, so tolerances below
 // the default stay with the CG's recursive residual); where the CG would
@@ -1178,7 +1187,7 @@ size_t spectral_bytes(const cgd_mesh m, int32_t F) {
 bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, bool stats) {
     if (stats || da.x0_mode != 0 || da.precond != 0 || da.rtol < 5e-7) return false;
     if (m->kind == 2 ? !m->rop || getenv("CGD_RECT_SLOTS") : m->kind != 0) return false;
-    if (getenv("CGD_NO_DIRECT") || getenv("CGD_HEX_PRECOND_DEG")) return false;
+    if (switched_to_cg()) return false;
     const SpecTables* t = grid_of(m);
     if (!t || !t->ok) return false;
     const double dtau = da.bandwidth * da.bandwidth / 4.0 / da.n_steps * (da.scheme == 1 ? 0.5 : 1.0);

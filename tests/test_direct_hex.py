@@ -243,3 +243,21 @@ def test_direct_passes_are_timed(gpu_lib):
     assert t["cg_sweep1"][1] > 0 and t["cg_sweep2"][1] > 0
     assert t["cg_sweep1"][2] == 24.0 * mesh.cells and t["cg_sweep2"][2] == 32.0 * mesh.cells
     assert not any(v[0] for k, v in t.items() if k not in ("cg_sweep1", "cg_sweep2"))
+
+
+@pytest.mark.parametrize("switch", ["CGD_HEX_PRECOND_DEG=4", "CGD_HEX_LDS_ZC=4", "CGD_HEX_DIR=0", "CGD_HEX_DIR_NW=16",
+                                    "CGD_HEX_DIR_ZC=4", "CGD_HEX_NO_SWAP=1", "CGD_HEX_TILE=2,4", "CGD_NO_BUDGET=1"])
+def test_switches_of_the_cg_reach_it(gpu_lib, switch, monkeypatch):
+    """A call without statistics under a switch of the CG: the CG's bits."""
+    import torch
+    cgd = gpu_lib
+    shape = (64, 24, 20)
+    mesh = cgd.HexMesh(shape)
+    e0 = torch.from_numpy(_field(shape, 1, 9)).cuda()
+    print(f"case: switch {switch}", flush=True)
+    direct = cgd.diffuse(mesh, e0.clone(), 0.06, 3)[0]
+    monkeypatch.setenv(*switch.split("="))
+    got = cgd.diffuse(mesh, e0.clone(), 0.06, 3)[0]
+    want = cgd.diffuse(mesh, e0.clone(), 0.06, 3, stats=True)[0]
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+    assert not torch.equal(got, direct)
