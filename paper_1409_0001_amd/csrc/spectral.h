@@ -4,6 +4,7 @@
 #include <vector>
 
 #include "cgd_internal.h"
+#include "spectral_modes.h"
 
 namespace cgd {
 
@@ -38,6 +39,7 @@ struct SpecTables {
     double scale[3] = {};     // eigenvalue of A - I over dtau = scale * lam
     double diag = 0.0;        // bound of the diagonal of (A - I) / dtau
     std::vector<double> h[3]; // eigen axes: cell widths
+    AxisModes modes[3];       //    and their modes, until they are on the device
     int64_t off = 0;          // the box's first cell in a field
     int rows_y = 0;           // rows per plane where rows are not one after the other, else 0
     int64_t sy = 0, sz = 0;   //    and the strides between rows and planes in a field

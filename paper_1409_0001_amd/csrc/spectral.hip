@@ -960,106 +960,6 @@ cgd_status launch_pass(const SpecPass& a, int F, hipStream_t s) {
     return go(k_dense<MODE, XK, false, 16>, std::max(4, mt), 16);
 }
 
-// Eigenvalues d and eigenvectors (z[k], one array per eigenvalue) of the
-// symmetric tridiagonal matrix with diagonal d and off-diagonal e: QR steps
-// with Wilkinson's shift, each a chase of the bulge that the first rotation
-// makes (the method of Golub and Van Loan, "Matrix Computations", 8.3).  In
-// the basis q1 = c u + s v, q2 = -s u + c v of a rotation the 2 x 2 block
-// (a, b, g) has the diagonal c^2 a + 2 c s b + s^2 g, s^2 a - 2 c s b + c^2 g
-// and the off-diagonal (c^2 - s^2) b + c s (g - a).
-void tridiagonal_modes(std::vector<double>& d, std::vector<double> e, std::vector<std::vector<double>>& z) {
-    const int n = (int)d.size();
-    z.assign(n, std::vector<double>(n, 0.0));
-    for (int k = 0; k < n; ++k) z[k][k] = 1.0;
-    e.resize(n, 0.0);
-    const double eps = 2.3e-16;
-    int hi = n - 1;
-    for (int64_t guard = 0; hi > 0 && guard < 60 * (int64_t)n; ++guard) {
-        auto split = [&](int k) { return std::fabs(e[k]) <= eps * (std::fabs(d[k]) + std::fabs(d[k + 1])); };
-        if (split(hi - 1)) {
-            --hi;
-            continue;
-        }
-        int lo = hi - 1;
-        while (lo > 0 && !split(lo - 1)) --lo;
-        const double half = 0.5 * (d[hi - 1] - d[hi]), b = e[hi - 1];
-        const double mu = d[hi] - b * b / (half + std::copysign(std::hypot(half, b), half));
-        double x = d[lo] - mu, y = e[lo];
-        for (int k = lo; k < hi; ++k) {
-            const double r = std::hypot(x, y);
-            if (r == 0.0) break;
-            const double c = x / r, s = y / r;
-            const double p = d[k], q = e[k], g = d[k + 1];
-            d[k] = c * c * p + 2.0 * c * s * q + s * s * g;
-            d[k + 1] = s * s * p - 2.0 * c * s * q + c * c * g;
-            e[k] = (c * c - s * s) * q + c * s * (g - p);
-            if (k > lo) e[k - 1] = r;
-            if (k + 1 < hi) {
-                y = s * e[k + 1];
-                e[k + 1] *= c;
-            }
-            x = e[k];
-            double* u = z[k].data();
-            double* v = z[k + 1].data();
-            for (int i = 0; i < n; ++i) {
-                const double ui = u[i], vi = v[i];
-                u[i] = c * ui + s * vi;
-                v[i] = c * vi - s * ui;
-            }
-        }
-    }
-}
-
-// The eigenvector axis a of t: eigenvalues in stored order, and the packed
-// matrices (forward even, odd, inverse even, odd).
-void eigen_axis(const SpecTables& t, int a, std::vector<double>& lam, std::vector<double>& mats) {
-    const std::vector<double>& h = t.h[a];
-    const int n = t.n[a];
-    const bool sym = t.sym[a];
-    const int hm = sym ? (n + 1) / 2 : n, ho = sym ? n / 2 : 0, mt = (hm + 15) / 16;
-    std::vector<double> g(n + 1, 0.0), s(n), o(n, 0.0);
-    for (int i = 1; i < n; ++i) g[i] = 2.0 / (h[i - 1] + h[i]);
-    double oper = 0.0;
-    if (t.per[a]) {
-        g[0] = g[n] = 2.0 / (h[0] + h[n - 1]);
-        oper = -g[0] / std::sqrt(h[0] * h[n - 1]);
-    }
-    for (int i = 0; i < n; ++i) s[i] = (g[i] + g[i + 1]) / h[i];
-    for (int i = 0; i + 1 < n; ++i) o[i] = -g[i + 1] / std::sqrt(h[i] * h[i + 1]);
-    lam.assign(n, 0.0);
-    const size_t frag = (size_t)mt * 4 * mt * 64;
-    mats.assign(4 * frag, 0.0);
-    for (int odd = 0; odd < (ho ? 2 : 1); ++odd) {
-        // the half of the modes with x[n-1-m] = +-x[m], in the coordinates of
-        // m < ho (times 1 / sqrt 2 in full) and, even ones of an odd n, the
-        // middle cell; sign * o for the neighbour that is the mirror image
-        const int nn = odd ? ho : hm;
-        std::vector<double> d(s.begin(), s.begin() + nn), e(o.begin(), o.begin() + nn);
-        const double sg = odd ? -1.0 : 1.0;
-        if (sym) {
-            d[0] += n > 1 ? sg * oper : 0.0;
-            if (n % 2 == 0) d[nn - 1] += sg * o[ho - 1];
-            else if (!odd && nn > 1) e[nn - 2] *= std::sqrt(2.0);
-        }
-        std::vector<std::vector<double>> z;
-        tridiagonal_modes(d, e, z);
-        double* f = mats.data() + (odd ? frag : 0);
-        double* inv = mats.data() + (odd ? 3 : 2) * frag;
-        for (int k = 0; k < nn; ++k) {
-            lam[odd ? hm + k : k] = d[k];
-            for (int m = 0; m < nn; ++m) {
-                const double v = z[k][m] * (sym && m < ho ? std::sqrt(0.5) : 1.0);
-                // entry (row, col) of a packed matrix
-                auto at = [&](int row, int col) {
-                    return (((size_t)(row / 16) * 4 * mt + col / 4) * 64) + (size_t)(col % 4) * 16 + row % 16;
-                };
-                f[at(k, m)] = v * std::sqrt(h[m]);
-                inv[at(m, k)] = v / std::sqrt(h[m]);
-            }
-        }
-    }
-}
-
 }  // namespace
 
 // The cells that diffuse, as a box of axes the transforms take.
@@ -1156,6 +1056,19 @@ size_t spectral_bytes(const cgd_mesh m, int32_t F) {
     return (size_t)fields_per_group(m, F) * (m->spec->cells * sizeof(double) + kTopSlots * kTopStride * sizeof(uint32_t));
 }
 
+// The modes of the axes of uneven cells, on the first call that needs them; a
+// mesh for which they are not found stays with the CG.
+static bool modes_found(SpecTables* t) {
+    if (t->dev) return true;
+    try {
+        for (int a = 0; a < t->rank && t->ok; ++a)
+            if (t->eigen[a] && t->modes[a].lam.empty()) t->ok = axis_modes(t->h[a], t->sym[a], t->per[a], &t->modes[a]);
+    } catch (const std::bad_alloc&) {
+        return false;
+    }
+    return t->ok;
+}
+
 // The environment switches that choose how the CG runs: set, they mean it.
 static bool switched_to_cg() {
     for (const char* e : {"CGD_NO_DIRECT", "CGD_HEX_PRECOND_DEG", "CGD_HEX_LDS_ZC", "CGD_HEX_DIR", "CGD_HEX_DIR_NW",
@@ -1197,7 +1110,7 @@ bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, bool stats) {
     const double mcells = 1e-6 * (double)m->cells;
     if (25.0 + mcells * ps > da.n_steps * (50.0 + mcells * (m->kind == 0 ? 25.0 : 100.0))) return false;
     const double r = sqrt(1.0 + 2.0 * dtau * t->diag);
-    return 0.5 * r * log(2.0 * r / std::min(da.rtol, 1.0)) + 1.0 <= (double)da.max_iter;
+    return 0.5 * r * log(2.0 * r / std::min(da.rtol, 1.0)) + 1.0 <= (double)da.max_iter && modes_found(m->spec);
 }
 
 void destroy_spectral(cgd_mesh m) {
@@ -1246,18 +1159,11 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
             x.io = x.ie + frag;
         }
         if (t->eigen[a]) {
-            try {
-                std::vector<double> lam, mats;
-                eigen_axis(*t, a, lam, mats);
-                e = hipMemcpyAsync(x.lam, lam.data(), lam.size() * sizeof(double), hipMemcpyHostToDevice, s);
-                if (e == hipSuccess)
-                    e = hipMemcpyAsync(x.fe, mats.data(), mats.size() * sizeof(double), hipMemcpyHostToDevice, s);
-                if (e == hipSuccess) e = hipStreamSynchronize(s);  // the vectors go
-            } catch (const std::bad_alloc&) {
-                (void)hipFree(dev);
-                set_error("transform tables: host allocation failed");
-                return CGD_E_NOMEM;
-            }
+            const AxisModes& mo = t->modes[a];
+            e = hipMemcpyAsync(x.lam, mo.lam.data(), mo.lam.size() * sizeof(double), hipMemcpyHostToDevice, s);
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(x.fe, mo.mats.data(), mo.mats.size() * sizeof(double), hipMemcpyHostToDevice, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);  // (the modes go below)
         } else {
             hipLaunchKernelGGL(k_spec_tables, dim3(64), dim3(256), 0, s, n, (int)fft, x.lam, x.tw, x.pw, x.fe, x.fo, x.ie,
                                x.io);
@@ -1270,6 +1176,7 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
         return CGD_E_HIP;
     }
     t->dev = static_cast<double*>(dev);
+    for (AxisModes& mo : t->modes) mo = AxisModes();
     return CGD_OK;
 }
 
