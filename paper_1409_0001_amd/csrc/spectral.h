@@ -20,6 +20,11 @@ struct SpecAxis {
     double* io = nullptr;
 };
 
+struct AxisModes {
+    RotationGroups rot[2];
+    std::vector<double> lam;
+};
+
 // The cells that diffuse, lo .. lo + len of a grid of nn per axis.
 struct SpecBox {
     int nn[3], lo[3], len[3];

@@ -39,6 +39,7 @@
 #include <math.h>
 
 #include <stdlib.h>
+#include <string.h>
 
 #include <algorithm>
 #include <cfloat>
@@ -960,6 +961,86 @@ cgd_status launch_pass(const SpecPass& a, int F, hipStream_t s) {
     return go(k_dense<MODE, XK, false, 16>, std::max(4, mt), 16);
 }
 
+// Forms an axis's packed matrices from its modes' rotations: a thread per
+// cell (column of the eigenvector matrix z, in LDS as [vector][thread], with
+// one row more for what is not stored), the rotations in groups of four
+// sweeps (RotationGroups), whose chains overlap.  One wave per block, bound by
+// the rotations' latency: 65,000 (a half of 512 mirror-symmetric cells) in
+// 1,600 us; one sweep at a time 4,200 us.  Together with finding the
+// rotations, a first call on 512 x 32 x 16 cells takes 3.9 ms, where the host
+// formed z in 10.8 (the CG 5.9, making the mesh 11).
+// blockIdx.y: half (even, odd modes).
+struct ModeArgs {
+    const double2* cs[2];
+    const RotationGroups::Group* groups[2];
+    int n_groups[2];
+    int nn[2];          // vectors and cells of the half
+    int mt, ho;         // tiles of the packed matrices; cells that stand for two
+    const double* h;    // cell widths
+    double* f[2];
+    double* inv[2];
+};
+// x of lane k (the same k in all lanes).
+__device__ __forceinline__ double lane_value(double x, int k) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, k), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), k);
+    return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+__global__ __launch_bounds__(64) void k_spec_modes(ModeArgs a) {
+    constexpr int L = RotationGroups::kLanes, S = RotationGroups::kGroupSteps, B = 8;
+    static_assert(L * S == 64 && S % B == 0);
+    extern __shared__ double z[];
+    const int lane = threadIdx.x, half = blockIdx.y, nn = a.nn[half], m = blockIdx.x * 64 + lane;
+    if ((int)blockIdx.x * 64 >= nn) return;
+    for (int k = 0; k < nn; ++k) z[k * 64 + lane] = k == m ? 1.0 : 0.0;
+    // (a thread only touches its own column: no barrier)
+    const double2* cs = a.cs[half] + lane;
+    double2 next = a.n_groups[half] ? cs[0] : make_double2(1.0, 0.0);
+    for (int i = 0; i < a.n_groups[half]; ++i) {
+        const RotationGroups::Group g = a.groups[half][i];
+        const double* in = z + g.lo * 64 + lane;
+        double u[L] = {in[0]};
+        for (int t0 = 0; t0 < g.count; t0 += S) {
+            // a lane holds one of the 64 rotations of S steps; the next ones are in flight
+            const double2 mine = next;
+            cs += 64;
+            if (t0 + S < g.count || i + 1 < a.n_groups[half]) next = cs[0];
+#pragma unroll
+            for (int b = 0; b < S; b += B) {
+                double v[B];
+#pragma unroll
+                for (int t = 0; t < B; ++t) v[t] = in[64 * min(t0 + b + t + 1, g.rows - 1)];
+#pragma unroll
+                for (int t = 0; t < B; ++t) {
+#pragma unroll
+                    for (int j = 0; j < L; ++j) {
+                        const double c = lane_value(mine.x, (b + t) * L + j), s = lane_value(mine.y, (b + t) * L + j);
+                        const double o = c * u[j] + s * v[t];
+                        u[j] = c * v[t] - s * u[j];
+                        v[t] = o;
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < B; ++t) {
+                    const int r = t0 + b + t + 1 - L;
+                    z[(r >= 0 && r < g.rows ? g.lo + r : nn) * 64 + lane] = v[t];
+                }
+            }
+        }
+    }
+    if (m >= nn) return;
+    const double g = m < a.ho ? 0.70710678118654752440 : 1.0, r = sqrt(a.h[m]);
+    for (int k = 0; k < nn; ++k) {
+        // entry (row, col) of a packed matrix
+        auto at = [&](int row, int col) {
+            return (((size_t)(row / 16) * 4 * a.mt + col / 4) * 64) + (size_t)(col % 4) * 16 + row % 16;
+        };
+        const double v = z[k * 64 + lane] * g;
+        a.f[half][at(k, m)] = v * r;
+        a.inv[half][at(m, k)] = v / r;
+    }
+}
+
 }  // namespace
 
 // The cells that diffuse, as a box of axes the transforms take.
@@ -1062,7 +1143,8 @@ static bool modes_found(SpecTables* t) {
     if (t->dev) return true;
     try {
         for (int a = 0; a < t->rank && t->ok; ++a)
-            if (t->eigen[a] && t->modes[a].lam.empty()) t->ok = axis_modes(t->h[a], t->sym[a], t->per[a], &t->modes[a]);
+            if (t->eigen[a] && t->modes[a].lam.empty())
+                t->ok = axis_modes(t->h[a], t->sym[a], t->per[a], t->modes[a].rot, t->modes[a].lam);
     } catch (const std::bad_alloc&) {
         return false;
     }
@@ -1120,6 +1202,67 @@ void destroy_spectral(cgd_mesh m) {
     m->spec = nullptr;
 }
 
+// Doubles of an eigenvector axis's data on the device: eigenvalues, widths
+// (both padded to an even number), and per half the rotations and groups.
+static size_t group_doubles(const RotationGroups& r) {
+    return (r.groups.size() * sizeof(RotationGroups::Group) + 15) / 16 * 2;
+}
+static size_t modes_doubles(const AxisModes& mo, int n) {
+    size_t d = 2 * ((size_t)n + (n & 1));
+    for (const RotationGroups& r : mo.rot) d += r.cs.size() + group_doubles(r);
+    return d;
+}
+
+// An eigenvector axis's data and packed matrices; dst: modes_doubles, 16-byte
+// aligned.  Waits for the stream.
+static hipError_t upload_modes(const SpecTables& t, int a, double* dst, SpecAxis& x, hipStream_t s) {
+    const AxisModes& mo = t.modes[a];
+    const int n = t.n[a];
+    ModeArgs ma = {};
+    std::vector<double> up;
+    try {
+        up = mo.lam;
+        up.resize(modes_doubles(mo, n));
+    } catch (const std::bad_alloc&) {
+        return hipErrorOutOfMemory;
+    }
+    size_t at = (size_t)n + (n & 1);
+    ma.h = dst + at;
+    std::copy(t.h[a].begin(), t.h[a].end(), up.begin() + at);
+    at += (size_t)n + (n & 1);
+    for (int odd = 0; odd < 2; ++odd) {
+        const RotationGroups& r = mo.rot[odd];
+        ma.cs[odd] = reinterpret_cast<const double2*>(dst + at);
+        std::copy(r.cs.begin(), r.cs.end(), up.begin() + at);
+        at += r.cs.size();
+        ma.groups[odd] = reinterpret_cast<const RotationGroups::Group*>(dst + at);
+        if (!r.groups.empty()) memcpy(up.data() + at, r.groups.data(), r.groups.size() * sizeof(RotationGroups::Group));
+        at += group_doubles(r);
+        ma.n_groups[odd] = (int)r.groups.size();
+    }
+    x.lam = dst;
+    const size_t frag = dense_fragment(n, t.sym[a]);
+    ma.nn[0] = t.sym[a] ? (n + 1) / 2 : n;
+    ma.ho = ma.nn[1] = t.sym[a] ? n / 2 : 0;
+    ma.mt = (ma.nn[0] + 15) / 16;
+    ma.f[0] = x.fe;
+    ma.f[1] = x.fo;
+    ma.inv[0] = x.ie;
+    ma.inv[1] = x.io;
+    hipError_t e = hipMemcpyAsync(dst, up.data(), up.size() * sizeof(double), hipMemcpyHostToDevice, s);
+    const size_t lds = ((size_t)ma.nn[0] + 1) * 64 * sizeof(double);  // <= 128.5 KB (256 vectors)
+    if (e == hipSuccess && lds > 64 * 1024)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_spec_modes), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_spec_clear, dim3(64), dim3(256), 0, s, reinterpret_cast<uint32_t*>(x.fe), (int)(8 * frag));
+        hipLaunchKernelGGL(k_spec_modes, dim3((ma.nn[0] + 63) / 64, ma.ho ? 2 : 1), dim3(64), lds, s, ma);
+        e = hipGetLastError();
+    }
+    const hipError_t w = hipStreamSynchronize(s);  // (`up` goes)
+    return e == hipSuccess ? w : e;
+}
+
 static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
     SpecTables* t = m->spec;
     if (t->dev) return CGD_OK;
@@ -1128,6 +1271,13 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
         off[a] = total;
         total += t->eigen[a] ? (((size_t)t->n[a] + 1) & ~(size_t)1) + 4 * dense_fragment(t->n[a], t->sym[a])
                              : table_doubles(t->n[a]);
+    }
+    size_t off_modes[3] = {};
+    for (int a = 0; a < t->rank; ++a) {
+        if (!t->eigen[a]) continue;
+        total += total & 1;  // (16-byte rotations)
+        off_modes[a] = total;
+        total += modes_doubles(t->modes[a], t->n[a]);
     }
     const size_t neg = total;  // after the tables: a 32-bit word per field
     total += kSpecFields / 2;
@@ -1159,11 +1309,7 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
             x.io = x.ie + frag;
         }
         if (t->eigen[a]) {
-            const AxisModes& mo = t->modes[a];
-            e = hipMemcpyAsync(x.lam, mo.lam.data(), mo.lam.size() * sizeof(double), hipMemcpyHostToDevice, s);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(x.fe, mo.mats.data(), mo.mats.size() * sizeof(double), hipMemcpyHostToDevice, s);
-            if (e == hipSuccess) e = hipStreamSynchronize(s);  // (the modes go below)
+            e = upload_modes(*t, a, static_cast<double*>(dev) + off_modes[a], x, s);
         } else {
             hipLaunchKernelGGL(k_spec_tables, dim3(64), dim3(256), 0, s, n, (int)fft, x.lam, x.tw, x.pw, x.fe, x.fo, x.ie,
                                x.io);
@@ -1173,7 +1319,7 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
     if (e != hipSuccess) {
         (void)hipFree(dev);
         set_error(std::string("transform tables: ") + hipGetErrorString(e));
-        return CGD_E_HIP;
+        return e == hipErrorOutOfMemory ? CGD_E_NOMEM : CGD_E_HIP;
     }
     t->dev = static_cast<double*>(dev);
     for (AxisModes& mo : t->modes) mo = AxisModes();

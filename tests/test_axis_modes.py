@@ -12,13 +12,49 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 SHIM = r"""
 #include "spectral_modes.cpp"
+#include <algorithm>
 extern "C" int modes(int n, double* d, const double* e, double* z) {
     std::vector<double> dd(d, d + n), ee(e, e + n - 1);
-    std::vector<std::vector<double>> v;
-    if (!cgd::tridiagonal_modes(dd, ee, v)) return 0;
-    for (int k = 0; k < n; ++k) {
-        d[k] = dd[k];
-        for (int i = 0; i < n; ++i) z[k * n + i] = v[k][i];
+    cgd::Rotations r;
+    if (!cgd::tridiagonal_modes(dd, ee, r)) return 0;
+    std::copy(dd.begin(), dd.end(), d);
+    for (int k = 0; k < n * n; ++k) z[k] = k % (n + 1) == 0;
+    size_t q = 0;
+    for (const auto& s : r.sweeps) {
+        if (s.lo < 0 || s.count < 1 || s.lo + s.count >= n) return -1;
+        for (int k = s.lo; k < s.lo + s.count; ++k, q += 2)
+            for (int i = 0; i < n; ++i) {
+                const double u = z[k * n + i], v = z[(k + 1) * n + i];
+                z[k * n + i] = r.cs[q] * u + r.cs[q + 1] * v;
+                z[(k + 1) * n + i] = r.cs[q] * v - r.cs[q + 1] * u;
+            }
+    }
+    if (q != r.cs.size()) return -1;
+    // the same from the groups, as a device thread per column steps through them
+    cgd::RotationGroups g;
+    cgd::group_rotations(r, g);
+    constexpr int L = cgd::RotationGroups::kLanes;
+    for (int i = 0; i < n; ++i) {
+        std::vector<double> col(n, 0.0);
+        col[i] = 1.0;
+        const double* cs = g.cs.data();
+        for (const auto& s : g.groups) {
+            if (s.lo < 0 || s.rows < 2 || s.lo + s.rows > n || s.count % cgd::RotationGroups::kGroupSteps) return -2;
+            double u[L] = {col[s.lo]};
+            for (int t = 0; t < s.count; ++t) {
+                double v = col[s.lo + std::min(t + 1, s.rows - 1)];
+                for (int j = 0; j < L; ++j, cs += 2) {
+                    const double o = cs[0] * u[j] + cs[1] * v;
+                    u[j] = cs[0] * v - cs[1] * u[j];
+                    v = o;
+                }
+                const int r = t + 1 - L;
+                if (r >= 0 && r < s.rows) col[s.lo + r] = v;
+            }
+        }
+        if (cs != g.cs.data() + g.cs.size()) return -3;
+        for (int k = 0; k < n; ++k)
+            if (std::fabs(col[k] - z[k * n + i]) > 1e-15) return -4;
     }
     return 1;
 }
@@ -40,6 +76,7 @@ def _modes(lib, d, e):
     z = np.zeros((n, n))
     p = ctypes.POINTER(ctypes.c_double)
     ok = lib.modes(n, d.ctypes.data_as(p), e.ctypes.data_as(p), z.ctypes.data_as(p))
+    assert ok >= 0, ok  # (sweeps within the matrix, all rotations used, the groups the same)
     return bool(ok), d, z
 
 
