@@ -11,7 +11,7 @@ namespace cgd {
 // Tables of one axis (device pointers; see k_spec_tables).
 struct SpecAxis {
     int n = 0;
-    double* lam = nullptr;   // eigenvalues at the stored positions [n] (cosine axes: 4 sin^2(pi k / 2n))
+    double* lam = nullptr;   // eigenvalues at the stored positions [n] (closed forms: see k_spec_tables)
     double2* tw = nullptr;   // FFT lengths: e^{-2 pi i q / n} [n]
     double2* pw = nullptr;   //    and e^{-i pi k / 2n} [n / 2]
     double* fe = nullptr;    // dense lengths: packed matrices, forward even and odd modes,
@@ -38,7 +38,7 @@ struct SpecTables {
     bool ok = false;          // the transforms apply to this mesh
     int rank = 0;
     int n[3] = {1, 1, 1};
-    bool eigen[3] = {};       // modes by eigenvectors (else cosine modes)
+    bool eigen[3] = {};       // modes by eigenvectors (else cosines, and sines on a periodic axis)
     bool sym[3] = {};         // even and odd modes about the axis's middle
     bool per[3] = {};
     double scale[3] = {};     // eigenvalue of A - I over dtau = scale * lam

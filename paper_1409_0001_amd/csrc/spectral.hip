@@ -27,11 +27,12 @@
 // operator of that box is I + dtau d sum_a M_a^-1 K_a, and the modes of an
 // axis are the eigenvectors of its tridiagonal M_a^-1/2 K_a M_a^-1/2 (of the
 // cyclic one on a periodic axis), scaled by sqrt(h) on the way in and
-// 1 / sqrt(h) on the way out: cosines where the widths are equal between
-// zero-flux ends.  Cells outside the box keep their values.
+// 1 / sqrt(h) on the way out: where the widths are equal, cosines between
+// zero-flux ends, cosines and sines on a periodic axis.  Cells outside the
+// box keep their values.
 //
 // A transform of length 128, 256, 512 or 1024 runs as a complex FFT of two
-// lines at once (k_fft); any other length up to 512 (and eigenvector modes) as
+// lines at once (k_fft); any other length up to 512 (and other modes) as
 // two half-size matrix products on the float64 matrix cores, the even modes
 // from x[m] + x[N-1-m] and the odd ones from x[m] - x[N-1-m] (k_dense): every
 // axis that is its own mirror image has only such modes; one that is not
@@ -871,7 +872,9 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
 // Per axis: the eigenvalues 4 sin^2(pi k / 2n) at the stored positions, then
 // for an FFT length e^{-2 pi i q / n} [n] and e^{-i pi k / 2n} [n / 2], for a
 // dense length the four packed half-size matrices (orthonormal scaling).
-__global__ __launch_bounds__(256) void k_spec_tables(int n, int fft, double* lam, double2* tw, double2* pw, double* fe,
+// per: a periodic axis, 4 sin^2(pi k / n) and the matrices of the cosines
+// (even) and sines (odd) of 2 pi k (m + 1/2) / n.
+__global__ __launch_bounds__(256) void k_spec_tables(int n, int fft, int per, double* lam, double2* tw, double2* pw, double* fe,
                                                     double* fo, double* ie, double* io) {
     const int hm = (n + 1) / 2, ho = n / 2, mt = (hm + 15) / 16, ks = 4 * mt;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -879,6 +882,7 @@ __global__ __launch_bounds__(256) void k_spec_tables(int n, int fft, double* lam
     for (int64_t p = t0; p < n; p += stride) {
         int k;
         if (fft) k = p == 0 ? 0 : (p == 1 ? n / 2 : ((p & 1) ? n - (int)p / 2 : (int)p / 2));
+        else if (per) k = 2 * (p < hm ? (int)p : (int)p - hm + 1);
         else k = p < hm ? 2 * (int)p : 2 * ((int)p - hm) + 1;
         const double s = sinpi(0.5 * k / n);
         lam[p] = 4.0 * s * s;
@@ -905,10 +909,15 @@ __global__ __launch_bounds__(256) void k_spec_tables(int n, int fft, double* lam
             const int64_t ph = ((int64_t)k * (2 * m + 1)) % (4 * (int64_t)n);
             return sqrt((k ? 2.0 : 1.0) / n) * cospi((double)ph / (2.0 * n));
         };
+        // ... and of the sine of (even) k at point m
+        auto sine = [&](int k, int m) {
+            const int64_t ph = ((int64_t)k * (2 * m + 1)) % (4 * (int64_t)n);
+            return sqrt((k == n ? 1.0 : 2.0) / n) * sinpi((double)ph / (2.0 * n));
+        };
         fe[i] = row < hm && col < hm ? entry(2 * row, col) : 0.0;
-        fo[i] = row < ho && col < ho ? entry(2 * row + 1, col) : 0.0;
+        fo[i] = row < ho && col < ho ? (per ? sine(2 * row + 2, col) : entry(2 * row + 1, col)) : 0.0;
         ie[i] = row < hm && col < hm ? entry(2 * col, row) : 0.0;
-        io[i] = row < ho && col < ho ? entry(2 * col + 1, row) : 0.0;
+        io[i] = row < ho && col < ho ? (per ? sine(2 * col + 2, row) : entry(2 * col + 1, row)) : 0.0;
     }
 }
 
@@ -925,8 +934,10 @@ size_t dense_fragment(int n, bool sym = true) {
     return mt * 4 * mt * 64;
 }
 
-size_t table_doubles(int n) {
-    if (fft_length(n)) return (size_t)n + 2 * (size_t)n + (size_t)n;
+bool uses_fft(const SpecTables& t, int a) { return !t.eigen[a] && !t.per[a] && fft_length(t.n[a]); }
+
+size_t table_doubles(int n, bool fft) {
+    if (fft) return (size_t)n + 2 * (size_t)n + (size_t)n;
     return (((size_t)n + 1) & ~(size_t)1) + 4 * dense_fragment(n);
 }
 
@@ -1092,7 +1103,7 @@ static void analyse_grid(const cgd_mesh m, SpecTables* t) {
                 diag = std::max(diag, (2.0 / (w0 + h[i]) + 2.0 / (h[i] + w1)) / h[i]);
             }
             t->per[r] = (ro->per >> a & 1) && n == nn[a];
-            t->eigen[r] = !even || t->per[r];
+            t->eigen[r] = !even;
             if (t->eigen[r]) t->h[r] = h;
         } else {
             diag = 2.0 / (mean * mean);
@@ -1101,7 +1112,7 @@ static void analyse_grid(const cgd_mesh m, SpecTables* t) {
         t->scale[r] = t->eigen[r] ? d : d / (mean * mean);
         t->diag += d * diag;
         if (!sym && (t->per[r] || n > 256)) return;
-        if (n > 512 && (t->eigen[r] || !fft_length(n))) return;
+        if (n > 512 && !uses_fft(*t, r)) return;
         st *= n;
     }
     if (t->rank < 2) return;
@@ -1188,7 +1199,7 @@ bool spectral_applies(cgd_mesh m, const DiffuseArgs& da, bool stats) {
     const double dtau = da.bandwidth * da.bandwidth / 4.0 / da.n_steps * (da.scheme == 1 ? 0.5 : 1.0);
     double ps = 0.0;
     for (int a = 0; a < t->rank; ++a)
-        ps += 2.0 * (!t->eigen[a] && fft_length(t->n[a]) ? 2.45 : 3.3 + (t->sym[a] ? 0.021 : 0.042) * t->n[a]);
+        ps += 2.0 * (uses_fft(*t, a) ? 2.45 : 3.3 + (t->sym[a] ? 0.021 : 0.042) * t->n[a]);
     const double mcells = 1e-6 * (double)m->cells;
     if (25.0 + mcells * ps > da.n_steps * (50.0 + mcells * (m->kind == 0 ? 25.0 : 100.0))) return false;
     const double r = sqrt(1.0 + 2.0 * dtau * t->diag);
@@ -1270,7 +1281,7 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
     for (int a = 0; a < t->rank; ++a) {
         off[a] = total;
         total += t->eigen[a] ? (((size_t)t->n[a] + 1) & ~(size_t)1) + 4 * dense_fragment(t->n[a], t->sym[a])
-                             : table_doubles(t->n[a]);
+                             : table_doubles(t->n[a], uses_fft(*t, a));
     }
     size_t off_modes[3] = {};
     for (int a = 0; a < t->rank; ++a) {
@@ -1297,7 +1308,7 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
         x = SpecAxis{};
         x.n = n;
         x.lam = p;
-        const bool fft = !t->eigen[a] && fft_length(n);
+        const bool fft = uses_fft(*t, a);
         if (fft) {
             x.tw = reinterpret_cast<double2*>(p + n);
             x.pw = x.tw + n;
@@ -1311,8 +1322,8 @@ static cgd_status spectral_tables(cgd_mesh m, hipStream_t s) {
         if (t->eigen[a]) {
             e = upload_modes(*t, a, static_cast<double*>(dev) + off_modes[a], x, s);
         } else {
-            hipLaunchKernelGGL(k_spec_tables, dim3(64), dim3(256), 0, s, n, (int)fft, x.lam, x.tw, x.pw, x.fe, x.fo, x.ie,
-                               x.io);
+            hipLaunchKernelGGL(k_spec_tables, dim3(64), dim3(256), 0, s, n, (int)fft, (int)t->per[a], x.lam, x.tw, x.pw,
+                               x.fe, x.fo, x.ie, x.io);
             e = hipGetLastError();
         }
     }

@@ -147,3 +147,27 @@ def test_rect_not_finite_outside_the_box(gpu_lib, where, bad, monkeypatch):
         if not env:  # (the CG leaves the field beside it to its own tolerance)
             assert torch.allclose(t[0], torch.ones_like(t[0]), rtol=1e-6)
     assert status == [-5, -5]
+
+
+# even numbers of cells and odd, one short of and beyond a tile, FFT lengths (which a periodic axis takes as
+# matrices), the longest
+@pytest.mark.parametrize("n", [2, 3, 31, 33, 128, 255, 512])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_periodic_axis_of_even_cells(gpu_lib, n, axis):
+    """Cosines and sines in closed form; the other axes uneven and a cosine axis."""
+    import torch
+    cgd = gpu_lib
+    shape = [7, 6, 5]
+    shape[axis] = n
+    e = [_edges(shape[a], 0.1, shape[a] / 24.0, "even" if a in (axis, (axis + 1) % 3) else "random", a) for a in range(3)]
+    per = tuple(a == axis for a in range(3))
+    mesh = cgd.RectMesh(*e, periodic=per)
+    rng = np.random.default_rng(n + axis)
+    e0 = (rng.random((2, mesh.cells)) ** 3).astype(np.float32)
+    e0[1] -= 0.3
+    print(f"case: direct periodic {shape} axis {axis}", flush=True)
+    out = cgd.diffuse(mesh, torch.from_numpy(e0).cuda(), 0.3, 3)[0].cpu().numpy()
+    ref = O.diffuse_rect(e0.astype(np.float64), e, 0.3, 3, solver="direct", periodic=per)
+    w = np.sqrt(O.rect_volumes(e))
+    for k in range(2):
+        assert np.linalg.norm(w * (out[k].astype(np.float64) - ref[k])) <= 5 * 2.0 ** -24 * np.linalg.norm(w * e0[k]), k
