@@ -97,3 +97,66 @@ def test_switches_of_the_counting_passes_reach_them(gpu_lib, switch, monkeypatch
     gpu_lib.deposit(mesh, torch.from_numpy(pos).cuda(), torch.from_numpy(vals).cuda(), stats=True)
     gpu_lib.diffuse(mesh, torch.ones((1, mesh.cells), device="cuda"), 0.05, 1)
     assert gpu_lib.timing_read(mesh)["deposit_scatter"][0] == 1
+
+
+# Full-size chunks (8192 particles at two and three fields, 6144 at four), which start at 256 chunks, and tiles of
+# 2048 records and more, for the 1024-thread accumulation: one particle short of the line, at it, and a ragged rest
+@pytest.mark.parametrize("F,n", [(2, 256 * 8192 - 1), (2, 256 * 8192), (2, 256 * 8192 + 4321), (3, 256 * 8192 + 7),
+                                 (4, 256 * 6144 - 1), (4, 256 * 6144), (4, 256 * 6144 + 6143)])
+def test_full_size_chunks(gpu_lib, F, n):
+    import torch
+    rng = np.random.default_rng(F)
+    pos = rng.random((n, 3)).astype(np.float32)
+    vals = rng.normal(size=(F, n)).astype(np.float32)
+    pos[::1001, 1] = 1.5            # outside
+    pos[5, 2] = np.nan
+    vals[0, 7] = np.inf
+    vals[F - 1, n - 1] = np.nan
+    _check(gpu_lib, torch, (64, 64, 63), pos, vals, f"ordered deposit, full chunks F={F} n={n}")
+
+
+@pytest.mark.parametrize("F", [2, 4])
+def test_full_size_chunks_rectilinear(gpu_lib, F):
+    import torch
+    cgd = gpu_lib
+    n, shape = 256 * 8192 + 55, (64, 60, 62)
+    rng = np.random.default_rng(F)
+    edges = []
+    for m in shape:
+        w = 0.4 + rng.random(m)
+        e = np.concatenate([[0.0], np.cumsum(w)]) / w.sum()
+        e[-1] = 1.0
+        edges.append(e)
+    pos = (1.02 * rng.random((n, 3)) - 0.01).astype(np.float32)
+    vals = rng.normal(size=(F, n)).astype(np.float32)
+    print(f"case: ordered deposit, full chunks, rectilinear F={F}", flush=True)
+    mesh = cgd.RectMesh(*edges)
+    acc = torch.empty((F, mesh.cells), dtype=torch.int64, device="cuda")
+    field, st = cgd.deposit(mesh, torch.from_numpy(pos).cuda(), torch.from_numpy(vals).cuda(), acc=acc, stats=True)
+    ref = O.deposit_rect(pos, vals, edges)
+    assert np.array_equal(acc.cpu().numpy(), ref["acc"])
+    assert np.array_equal(field.cpu().numpy().view(np.uint32), ref["field32"].view(np.uint32))
+    assert st.n_dropped == ref["n_dropped"]
+
+
+@pytest.mark.parametrize("F", [2, 4])
+def test_full_size_chunks_batched(gpu_lib, F):
+    """Uneven snapshots (one empty, one of one particle) whose total takes
+    full-size chunks: each the bits of its own call, which takes small ones."""
+    import torch
+    cgd = gpu_lib
+    shape = (64, 64, 62)
+    counts = [900_001, 0, 1, 700_000, 600_123]
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    n = int(off[-1])
+    assert n >= 256 * 8192
+    rng = np.random.default_rng(F)
+    pos = torch.from_numpy(rng.random((n, 3)).astype(np.float32)).cuda()
+    vals = torch.from_numpy(rng.normal(size=(F, n)).astype(np.float32)).cuda()
+    mesh = cgd.HexMesh(shape)
+    print(f"case: ordered deposit, full chunks, batched F={F}", flush=True)
+    out = cgd.coarse_grain_batched(mesh, off, pos, vals, 0.05, 2)
+    for j in range(len(counts)):
+        s = slice(int(off[j]), int(off[j + 1]))
+        one = cgd.coarse_grain(mesh, pos[s].contiguous(), vals[:, s].contiguous(), 0.05, 2)[0]
+        assert torch.equal(one.view(torch.int32), out[j].view(torch.int32)), j

@@ -261,3 +261,49 @@ def test_switches_of_the_cg_reach_it(gpu_lib, switch, monkeypatch):
     want = cgd.diffuse(mesh, e0.clone(), 0.06, 3, stats=True)[0]
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
     assert not torch.equal(got, direct)
+
+
+# more cells than a group of fields takes at once (16.7M): fields in two groups, an even and an odd number of cells
+@pytest.mark.parametrize("shape,F", [((256, 256, 64), 6), ((255, 257, 65), 5)])
+def test_fields_in_several_groups(gpu_lib, shape, F):
+    import torch
+    cgd = gpu_lib
+    mesh = cgd.HexMesh(shape)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    e0 = torch.rand((F, mesh.cells), device="cuda", generator=g) ** 4
+    e0[1] -= 0.5
+    print(f"case: groups {shape} F={F}", flush=True)
+    out = cgd.diffuse(mesh, e0.clone(), 0.02, 3)[0]
+    assert not torch.equal(out[0], e0[0])
+    for f in range(F):
+        one = cgd.diffuse(mesh, e0[f:f + 1].clone(), 0.02, 3)[0]
+        assert torch.equal(one[0].view(torch.int32), out[f].view(torch.int32)), f
+    n = 30_000
+    pos = torch.rand((3 * n, 3), device="cuda", generator=g)
+    vals = torch.rand((2, 3 * n), device="cuda", generator=g)
+    off = np.array([0, n, 2 * n, 3 * n], np.int64)
+    batch = cgd.coarse_grain_batched(mesh, off, pos, vals, 0.02, 3)
+    for j in range(3):
+        s = slice(j * n, (j + 1) * n)
+        one = cgd.coarse_grain(mesh, pos[s].contiguous(), vals[:, s].contiguous(), 0.02, 3)[0]
+        assert torch.equal(one.view(torch.int32), batch[j].view(torch.int32)), j
+
+
+@pytest.mark.parametrize("shape", [(128, 40, 33), (50, 30, 20)])
+def test_other_streams(gpu_lib, shape):
+    """The first call (which makes the tables) on one stream, others on
+    another and on the default one, each after its input on that stream."""
+    import torch
+    cgd = gpu_lib
+    e0 = torch.from_numpy(_field(shape, 2, 5))
+    want = cgd.diffuse(cgd.HexMesh(shape), e0.cuda(), 0.05, 3)[0]
+    mesh = cgd.HexMesh(shape)
+    host = e0.pin_memory()
+    torch.cuda.synchronize()
+    for s in (torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.default_stream()):
+        with torch.cuda.stream(s):
+            f = host.to("cuda", non_blocking=True) * 1.0
+            got = cgd.diffuse(mesh, f, 0.05, 3)[0]
+            same = torch.equal(got.view(torch.int32), want.view(torch.int32))
+        assert same
