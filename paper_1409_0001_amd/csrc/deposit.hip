@@ -1024,9 +1024,12 @@ struct OrderPlan {
 // have fewer than 512, so that the accumulation fills the 256 compute units
 // on small grids too (24^3 cells are one largest tile: 9.9 us on one unit).
 // Chunks are as large as a block's LDS orders (16384 particles at F = 1,
-// 8192 at 2 or 3, 6144 at 4), for long runs, where that still makes 512
+// 8192 at 2 or 3, 6144 at 4), for long runs, where that still makes 80
 // blocks, else 2048: 20,000 particles in two chunks of 16384 took 42 us to
-// bin and scatter, in ten of 2048 they take 7.4.
+// bin and scatter, in ten of 2048 they take 7.4.  The whole deposit, large
+// against small chunks: 64 blocks of large ones 103 and 100 us on 256 x 256 x
+// 512 cells, 38 and 35 on 160^3, 4 fields of 128^3 49 and 46; 80 blocks 103
+// and 109, 39 and 40, 49 and 48; 255 blocks 114 and 138, 66 and 87, 60 and 71.
 static bool order_plan(int64_t cells, int64_t total, int32_t n_snap, int32_t F, OrderPlan* p) {
     int cpt, nt;
     if (F > 4 || !tile_plan(cells, total, F, &cpt, &nt) || nt > kStageMaxTiles || tile_nsub("CGD_DEPOSIT_NSUB") != 1 ||
@@ -1040,7 +1043,7 @@ static bool order_plan(int64_t cells, int64_t total, int32_t n_snap, int32_t F, 
     const int most = F == 1 ? 16384 : (F <= 3 ? 8192 : 6144);
     p->cpt = cpt;
     p->ntiles = nt;
-    p->chunk = total >= (int64_t)256 * most ? most : 2048;
+    p->chunk = total >= (int64_t)80 * most ? most : 2048;
     p->starts_bytes = 2 * ((size_t)(total / p->chunk) + n_snap + 1) * (nt + 1);
     return true;
 }

@@ -99,10 +99,12 @@ def test_switches_of_the_counting_passes_reach_them(gpu_lib, switch, monkeypatch
     assert gpu_lib.timing_read(mesh)["deposit_scatter"][0] == 1
 
 
-# Full-size chunks (8192 particles at two and three fields, 6144 at four), which start at 256 chunks, and tiles of
-# 2048 records and more, for the 1024-thread accumulation: one particle short of the line, at it, and a ragged rest
-@pytest.mark.parametrize("F,n", [(2, 256 * 8192 - 1), (2, 256 * 8192), (2, 256 * 8192 + 4321), (3, 256 * 8192 + 7),
-                                 (4, 256 * 6144 - 1), (4, 256 * 6144), (4, 256 * 6144 + 6143)])
+# Full-size chunks (16384 particles at one field, 8192 at two and three, 6144 at four), which start at 80 chunks: one
+# particle short of the line, at it, and a ragged rest; more than 2048 records per tile of 8192 sums and more, for the
+# 1024-thread accumulation
+@pytest.mark.parametrize("F,n", [(1, 80 * 16384 - 1), (1, 80 * 16384), (2, 80 * 8192 - 1), (2, 80 * 8192 + 4321),
+                                 (3, 80 * 8192), (4, 80 * 6144 - 1), (4, 80 * 6144), (2, 256 * 8192 + 4321),
+                                 (3, 256 * 8192 + 7), (4, 256 * 6144 + 6143)])
 def test_full_size_chunks(gpu_lib, F, n):
     import torch
     rng = np.random.default_rng(F)
@@ -112,14 +114,15 @@ def test_full_size_chunks(gpu_lib, F, n):
     pos[5, 2] = np.nan
     vals[0, 7] = np.inf
     vals[F - 1, n - 1] = np.nan
-    _check(gpu_lib, torch, (64, 64, 63), pos, vals, f"ordered deposit, full chunks F={F} n={n}")
+    shape = (128, 128, 65) if F == 4 else (128, 128, 130)
+    _check(gpu_lib, torch, shape, pos, vals, f"ordered deposit, full chunks F={F} n={n}")
 
 
 @pytest.mark.parametrize("F", [2, 4])
 def test_full_size_chunks_rectilinear(gpu_lib, F):
     import torch
     cgd = gpu_lib
-    n, shape = 256 * 8192 + 55, (64, 60, 62)
+    n, shape = 256 * 8192 + 55, (128, 128, 65 if F == 4 else 130)
     rng = np.random.default_rng(F)
     edges = []
     for m in shape:
@@ -145,7 +148,7 @@ def test_full_size_chunks_batched(gpu_lib, F):
     full-size chunks: each the bits of its own call, which takes small ones."""
     import torch
     cgd = gpu_lib
-    shape = (64, 64, 62)
+    shape = (128, 128, 40)
     counts = [900_001, 0, 1, 700_000, 600_123]
     off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
     n = int(off[-1])
