@@ -705,9 +705,10 @@ __device__ inline float finish_value(long long v, int S, double V, double rs, bo
     const double d = (double)v, q = d * rs;
     const unsigned long long b = (unsigned long long)__double_as_longlong(q);
     const uint32_t low = (uint32_t)b & 0x1fffffffu, e = (uint32_t)(b >> 52) & 0x7ffu;
-    if (fast && low - (0x10000000u - 8u) > 16u && e - 897u < 253u) return (float)q;  // 2^-126 <= |q| < 2^127
-    if (!v) return 0.f;
-    return (float)(ldexp(d, -S) / V);
+    const bool rounded = fast && low - (0x10000000u - 8u) > 16u && e - 897u < 253u;  // 2^-126 <= |q| < 2^127
+    float r = fast ? (float)q : 0.f;
+    if (!rounded && v) r = (float)(ldexp(d, -S) / V);  // (v = 0, most cells of a sparse grid: no branch taken)
+    return r;
 }
 
 // Pass 4: one workgroup per tile (of all snapshots): exact int64 sums in LDS
@@ -900,11 +901,20 @@ __global__ __launch_bounds__(NT) void k_tile_accum(TileArgs a) {
             const size_t o = ((size_t)j * a.F + f) * a.cells + c0;
             const double rs = ldexp(1.0, -S[f]) / a.vol;
             const bool fast = !a.vcell && rs >= 0x1p-900 && rs <= 0x1p900;
-            for (int i = threadIdx.x; i < nc; i += NT) {
-                const long long v = (long long)lacc[f * a.cpt + i];
-                if (SEG) lacc[f * a.cpt + i] = 0ull;
-                a.field[o + i] = finish_value(v, S[f], a.vcell ? a.vcell[c0 + i] : a.vol, rs, fast);
-                if (a.acc) a.acc[o + i] = v;
+            // (four cells per thread at a time: their LDS reads overlap)
+            unsigned long long* const la = lacc + f * a.cpt;
+            for (int i0 = threadIdx.x; i0 < nc; i0 += U * NT) {
+                long long v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = (long long)la[min(i0 + u * NT, nc - 1)];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = i0 + u * NT;
+                    if (i >= nc) break;
+                    if (SEG) la[i] = 0ull;
+                    a.field[o + i] = finish_value(v[u], S[f], a.vcell ? a.vcell[c0 + i] : a.vol, rs, fast);
+                    if (a.acc) a.acc[o + i] = v[u];
+                }
             }
         }
         __syncthreads();
@@ -1196,8 +1206,16 @@ cgd_status tiled_deposit(cgd_mesh m, const TiledDeposit& d, Timing* timing, hipS
     int t15 = timing ? timing_begin(timing, s) : -1;
     cgd_status rc;
     if (!ordered) rc = d.F >= 2 ? launch_accum<true, false, kTBlock>(a, s) : launch_accum<false, false, kTBlock>(a, s);
-    // (a tile of few records is a quarter workgroup's work)
-    else if (np_ < 2048.0 * all) rc = d.F >= 2 ? launch_accum<true, true, 256>(a, s) : launch_accum<false, true, 256>(a, s);
+    // A quarter workgroup where at least two fit a compute unit (tiles of up
+    // to 8192 sums, 64 KB) and the tile has few records: four on a unit (up to
+    // 4096 sums) leave the grid fewer idle slots in its last round as well.
+    // Measured, quarter against whole: 160^3 cells in 1,000 tiles of 4096, 4M
+    // particles 49 and 62 us, 128^3 in 512, 4M 48 and 49, 16M 152 and 140; 275 x
+    // 147 x 93, 2 fields, in tiles of 8192, 0.9M 49 and 55, 3.8M 79 and 84, but 200
+    // x 200 x 150 3M 58 and 54.  A sparse grid in largest tiles (16384 sums, one
+    // workgroup per unit) is finished by few threads otherwise: 256 x 256 x 512
+    // cells, 1M particles 179 and 102.
+    else if (d.F * cpt <= 8192 && np_ < (d.F * cpt <= 4096 ? 16384.0 : 2048.0) * all) rc = d.F >= 2 ? launch_accum<true, true, 256>(a, s) : launch_accum<false, true, 256>(a, s);
     else rc = d.F >= 2 ? launch_accum<true, true, kTBlock>(a, s) : launch_accum<false, true, kTBlock>(a, s);
     if (rc != CGD_OK) return rc;
     if (timing)

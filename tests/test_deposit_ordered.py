@@ -163,3 +163,15 @@ def test_full_size_chunks_batched(gpu_lib, F):
         s = slice(int(off[j]), int(off[j + 1]))
         one = cgd.coarse_grain(mesh, pos[s].contiguous(), vals[:, s].contiguous(), 0.05, 2)[0]
         assert torch.equal(one.view(torch.int32), out[j].view(torch.int32)), j
+
+
+def test_sparse_grid_of_largest_tiles(gpu_lib):
+    """One particle in a thousand cells, tiles of 16384 sums, a ragged one: a
+    whole workgroup per tile; and the same cells with more records per tile
+    than a quarter workgroup takes, in smaller tiles (1024 cells each)."""
+    import torch
+    rng = np.random.default_rng(6)
+    for shape, n in (((256, 256, 130), 9_000), ((128, 64, 64), 512 * 16384 + 3)):
+        pos = rng.random((n, 3)).astype(np.float32)
+        vals = rng.normal(size=(1, n)).astype(np.float32)
+        _check(gpu_lib, torch, shape, pos, vals, f"ordered deposit {shape} n={n}")
