@@ -809,7 +809,7 @@ cgd_status coarse_grain_batched(cgd_mesh m, int32_t n_snap, const int64_t* offse
     const BLayout L = batched_layout(n_rhs, n_snap, da.n_steps);
     const size_t small = L.small;
     // deposit: the tiled path's bucketed records, else int64 accumulators
-    const size_t tile_bytes = tiled_deposit_temp_bytes((int64_t)cells, total, n_snap, F);
+    const size_t tile_bytes = tiled_deposit_temp_bytes((int64_t)cells, total, n_snap, F, false);
     const bool tiled = tile_bytes > 0;
     const size_t dep_bytes = tiled ? tile_bytes : (size_t)n_rhs * cells * 8;
     const size_t solver_bytes = direct       ? spectral_bytes(m, n_rhs)

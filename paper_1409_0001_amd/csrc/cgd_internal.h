@@ -174,8 +174,8 @@ struct TiledDeposit {
     const double* vcell = nullptr;
 };
 // Bytes of `temp`; 0 when the grid or the particle count rules the tiled
-// deposit out (then the direct atomic deposit is used).
-size_t tiled_deposit_temp_bytes(int64_t cells, int64_t total, int32_t n_snap, int32_t F);
+// deposit out (then the direct atomic deposit is used).  rect: TiledDeposit's.
+size_t tiled_deposit_temp_bytes(int64_t cells, int64_t total, int32_t n_snap, int32_t F, bool rect);
 cgd_status tiled_deposit(cgd_mesh m, const TiledDeposit& d, Timing* timing, hipStream_t s);
 
 // cg_hex.hip

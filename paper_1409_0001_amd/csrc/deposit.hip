@@ -1040,7 +1040,11 @@ struct OrderPlan {
 // against small chunks: 64 blocks of large ones 103 and 100 us on 256 x 256 x
 // 512 cells, 38 and 35 on 160^3, 4 fields of 128^3 49 and 46; 80 blocks 103
 // and 109, 39 and 40, 49 and 48; 255 blocks 114 and 138, 66 and 87, 60 and 71.
-static bool order_plan(int64_t cells, int64_t total, int32_t n_snap, int32_t F, OrderPlan* p) {
+// Rectilinear grids, whose blocks search the edges for longer: from 200 blocks
+// on, and not where they are a little more than the 256 that run at once (128 x
+// 128 x 256: 160 blocks 81 and 68 us, 200 83 and 81, 255 87 and 90, 300 134 and
+// 107, 400 140 and 130, 512 148 and 154).
+static bool order_plan(int64_t cells, int64_t total, int32_t n_snap, int32_t F, bool rect, OrderPlan* p) {
     int cpt, nt;
     if (F > 4 || !tile_plan(cells, total, F, &cpt, &nt) || nt > kStageMaxTiles || tile_nsub("CGD_DEPOSIT_NSUB") != 1 ||
         tile_nsub("CGD_DEPOSIT_BIN_NSUB") != 1)
@@ -1053,12 +1057,13 @@ static bool order_plan(int64_t cells, int64_t total, int32_t n_snap, int32_t F, 
     const int most = F == 1 ? 16384 : (F <= 3 ? 8192 : 6144);
     p->cpt = cpt;
     p->ntiles = nt;
-    p->chunk = total >= (int64_t)80 * most ? most : 2048;
+    const int64_t blocks = total / most;
+    p->chunk = (rect ? blocks >= 200 && (blocks <= 256 || blocks >= 400) : blocks >= 80) ? most : 2048;
     p->starts_bytes = 2 * ((size_t)(total / p->chunk) + n_snap + 1) * (nt + 1);
     return true;
 }
 
-size_t tiled_deposit_temp_bytes(int64_t cells, int64_t total, int32_t n_snap, int32_t F) {
+size_t tiled_deposit_temp_bytes(int64_t cells, int64_t total, int32_t n_snap, int32_t F, bool rect) {
     int cpt, nt;
     if (!tile_plan(cells, total, F, &cpt, &nt)) return 0;
     const size_t recs = al256(rec_bytes(F) * total) + al256(4 * rv_fields(F) * total);
@@ -1066,7 +1071,7 @@ size_t tiled_deposit_temp_bytes(int64_t cells, int64_t total, int32_t n_snap, in
     OrderPlan op;
     // (the counting passes' bytes are the documented need; the ordered path's
     // are fewer but for the smallest calls)
-    return order_plan(cells, total, n_snap, F, &op) ? std::max(counted, recs + al256(op.starts_bytes)) : counted;
+    return order_plan(cells, total, n_snap, F, rect, &op) ? std::max(counted, recs + al256(op.starts_bytes)) : counted;
 }
 
 void deposit_info_init(DepositInfo* info, const ScaleForce& fs, hipStream_t s) {
@@ -1074,7 +1079,7 @@ void deposit_info_init(DepositInfo* info, const ScaleForce& fs, hipStream_t s) {
 }
 
 size_t deposit_hex_temp_bytes(const cgd_mesh m, int64_t n, int32_t F) {
-    return tiled_deposit_temp_bytes(m->cells, n, 1, F);
+    return tiled_deposit_temp_bytes(m->cells, n, 1, F, m->kind == 2);
 }
 
 template <int C, int NV>
@@ -1122,7 +1127,7 @@ cgd_status tiled_deposit(cgd_mesh m, const TiledDeposit& d, Timing* timing, hipS
     a.g = hex_bin(m);
     a.cells = m->cells;
     OrderPlan op;
-    const bool ordered = order_plan(m->cells, d.total, d.n_snap, d.F, &op);
+    const bool ordered = order_plan(m->cells, d.total, d.n_snap, d.F, d.rect, &op);
     if (ordered) {
         cpt = op.cpt;
         nt = op.ntiles;

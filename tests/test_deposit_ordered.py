@@ -118,11 +118,13 @@ def test_full_size_chunks(gpu_lib, F, n):
     _check(gpu_lib, torch, shape, pos, vals, f"ordered deposit, full chunks F={F} n={n}")
 
 
-@pytest.mark.parametrize("F", [2, 4])
-def test_full_size_chunks_rectilinear(gpu_lib, F):
+# rectilinear grids: full-size chunks from 200 to 256 and from 400 on
+@pytest.mark.parametrize("F,n", [(1, 200 * 16384 - 1), (1, 200 * 16384 + 9), (2, 256 * 8192 + 55), (2, 257 * 8192),
+                                 (3, 399 * 8192), (4, 400 * 6144 + 1)])
+def test_full_size_chunks_rectilinear(gpu_lib, F, n):
     import torch
     cgd = gpu_lib
-    n, shape = 256 * 8192 + 55, (128, 128, 65 if F == 4 else 130)
+    shape = (128, 128, 65 if F == 4 else 130)
     rng = np.random.default_rng(F)
     edges = []
     for m in shape:
