@@ -93,7 +93,7 @@ struct SpecPass {
     int32_t n_steps, cn;
     int* bad;       // device, per field: set by the gain pass where a value of W is beyond float32 or not finite
     int* bad_host;  // nullable: the same in pinned host memory
-    uint32_t* top;  // device, kTopSlots per field: the largest |value| in W after the gain pass (float32 bits)
+    uint32_t* top;  // device, kTopSlots per field: the largest |value| in W after the gain pass (upper 32 bits)
     uint32_t* neg;  // device, per field: `call` where the input holds a negative value
     uint32_t call;
     double cut;     // results below cut * (the largest of top) of a field without negative values are 0

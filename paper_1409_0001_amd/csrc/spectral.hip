@@ -43,7 +43,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <cfloat>
 #include <cmath>
 #include <new>
 #include <string>
@@ -150,7 +149,12 @@ __device__ __forceinline__ void mark_bad(const SpecPass& a) {
     __hip_atomic_store(a.bad + blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (a.bad_host) a.bad_host[blockIdx.y] = 1;
 }
-__device__ __forceinline__ bool carried(double x) { return fabs(x) <= (double)FLT_MAX; }
+// |x|'s upper 32 bits, which order as |x| does (infinities and NaN above all
+// numbers): 2^128 and more is beyond float32.
+__device__ __forceinline__ uint32_t upper(double x) {
+    return (uint32_t)((unsigned long long)__double_as_longlong(x) >> 32) & 0x7fffffffu;
+}
+constexpr uint32_t kBeyond = 0x47f00000u;
 // The first pass (x forward) clears what the gain pass notes per field.
 __device__ __forceinline__ void clear_notes(const SpecPass& a) {
     if (blockIdx.x) return;
@@ -165,19 +169,19 @@ __device__ __forceinline__ bool is_bad(const SpecPass& a) {
 // no earlier call has left there, so nothing has to be cleared first.  A
 // plain store (every wave stores the same, and only later kernels read it):
 // one that goes past the XCD's L2 took x forward of 4 x 128^3 from 17 to 53
-// us.  (All threads of a wave.)
-__device__ __forceinline__ void mark_negative(const SpecPass& a, bool negative) {
-    if (__ballot(negative) && (threadIdx.x & 63) == 0) a.neg[blockIdx.y] = a.call;
+// us.  least: the least value the thread has seen.  (All threads of a wave.)
+__device__ __forceinline__ void mark_negative(const SpecPass& a, float least) {
+    if (__ballot(least < 0.f) && (threadIdx.x & 63) == 0) a.neg[blockIdx.y] = a.call;
 }
-// The largest |value| the gain pass leaves in W, in one of a field's
-// kTopSlots cache lines (one word per field took the gain pass of 4 x 128^3
-// from 29 to 60 us).  (All threads of a wave.)
-__device__ __forceinline__ void note_top(const SpecPass& a, double big) {
-    float b = (float)fmin(big, (double)FLT_MAX);
-    for (int o = 32; o > 0; o >>= 1) b = fmaxf(b, __shfl_xor(b, o));
+// The largest |value| the gain pass leaves in W (its upper 32 bits), in one of
+// a field's kTopSlots cache lines: one word per field took the gain pass of 4
+// x 128^3 from 29 to 60 us, and a look at the word before the atomic, which
+// nothing waits for, that of 2 x 96 x 64 x 80 from 16 to 19.  (All threads of
+// a wave.)
+__device__ __forceinline__ void note_top(const SpecPass& a, uint32_t top) {
+    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o));
     const unsigned wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if ((threadIdx.x & 63) == 0)
-        atomic_max_if_larger(a.top + (size_t)(blockIdx.y * kTopSlots + wave % kTopSlots) * kTopStride, __float_as_uint(b));
+    if ((threadIdx.x & 63) == 0) atomicMax(a.top + (size_t)(blockIdx.y * kTopSlots + wave % kTopSlots) * kTopStride, top);
 }
 // Results of a field without negative values are right to about 2^-53 of the
 // largest plane mean times the square root of a plane's cells, whatever
@@ -192,7 +196,8 @@ __device__ __forceinline__ float cut_of(const SpecPass& a) {
     uint32_t top = 0u;
 #pragma unroll
     for (int i = 0; i < kTopSlots; ++i) top = max(top, a.top[(size_t)(blockIdx.y * kTopSlots + i) * kTopStride]);
-    const float c = a.neg[blockIdx.y] == a.call ? 0.f : (float)(a.cut * (double)__uint_as_float(top));
+    const double t = __longlong_as_double((long long)((unsigned long long)top << 32));
+    const float c = a.neg[blockIdx.y] == a.call ? 0.f : (float)(a.cut * t);
     return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(c)));  // (the same in all lanes: a scalar register)
 }
 __device__ __forceinline__ float result(double x, float cut) {
@@ -399,8 +404,8 @@ __device__ __forceinline__ void pair_of(v4d m, Cd w, bool k0, double s, double s
 // Large fields are bound by memory: 256 x 256 x 512, one field, whose W of
 // 268 MB the memory-side cache does not hold: forward and back along x 70 and
 // 82 us (403 MB in and out; 61 and 57 with float32 W), y 98 and 87 (537 MB,
-// 5.5 to 6.2 TB/s; 53 and 50), the gain pass along z 160 (118).  4 fields of
-// 128^3 (67 MB): 19, 22, 21, 21 and 39 us (17, 18, 15, 16, 29).
+// 5.5 to 6.2 TB/s; 53 and 50), the gain pass along z 159 (118).  4 fields of
+// 128^3 (67 MB): 19, 22, 21, 21 and 37 us (17, 18, 15, 16, 29).
 template <int N, int MODE, bool XK>
 __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPass a) {
     constexpr int T = N / kE, P = fft_pairs<N, XK>(), H = kE / 2;
@@ -461,11 +466,11 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
                     xb[j] = make_float2(in[fbase2 + e], in[fbase2 + e + 1]);
                 }
             }
-            bool negative = false;
+            float least = 0.f;
 #pragma unroll
             for (int j = 0; j < H; ++j)
-                negative = negative || xa[j].x < 0.f || xa[j].y < 0.f || xb[j].x < 0.f || xb[j].y < 0.f;
-            mark_negative(a, negative);
+                least = fminf(fminf(least, fminf(xa[j].x, xa[j].y)), fminf(xb[j].x, xb[j].y));
+            mark_negative(a, least);
 #pragma unroll
             for (int j = 0; j < H; ++j) {
                 v[j] = {xa[j].x, two ? xb[j].x : 0.f};
@@ -496,10 +501,10 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
             for (int j = 0; j < kE; ++j) v[j].y = two ? v[j].y : 0.0;
         }
         if (MODE == 2) {
-            bool ok = true;
+            uint32_t most = 0u;
 #pragma unroll
-            for (int j = 0; j < kE; ++j) ok = ok && carried(v[j].x) && carried(v[j].y);
-            if (!ok && live) mark_bad(a);
+            for (int j = 0; j < kE; ++j) most = max(most, max(upper(v[j].x), upper(v[j].y)));
+            if (live && most >= kBeyond) mark_bad(a);
         }
         fft_line<N, P, XK>(v, sh, t, p, tw);
         t = again(t);
@@ -597,10 +602,10 @@ __global__ __launch_bounds__((fft_pairs<N, XK>() * N / kE), 4) void k_fft(SpecPa
     fft_line<N, P, XK>(v, sh, t, p, tw);
     t = again(t);
     if (MODE == 2) {
-        double big = 0.0;
+        uint32_t top = 0u;
 #pragma unroll
-        for (int j = 0; j < kE; ++j) big = fmax(big, fmax(fabs(v[j].x), fabs(v[j].y)));
-        note_top(a, live ? big : 0.0);
+        for (int j = 0; j < kE; ++j) top = max(top, max(upper(v[j].x), upper(v[j].y)));
+        note_top(a, live ? top : 0u);
     }
     if (XK) {
         const float cut = cut_of(a);
@@ -682,8 +687,8 @@ __device__ __forceinline__ int d_row(int r, int lane) { return 4 * r + (lane >> 
 // the float64 matrix cores, which bound it together with the phases), 51 ->
 // 50 along strided 147, gain pass along 93 66 -> 65 (with float32 vectors
 // between the passes; with float64 ones 62 and 65, 54 and 48, 70); 96 x 64 x
-// 80 cells, 2 fields: 19.4 -> 15.1 us for the gain pass (now 19.7), 13.6 ->
-// 10.5 and 11.7 -> 8.9 along x (now 12.6 and 9.7).
+// 80 cells, 2 fields: 19.4 -> 15.1 us for the gain pass (now 17.4), 13.6 ->
+// 10.5 and 11.7 -> 8.9 along x (now 12.0 and 9.8).
 template <int MODE, bool XK, bool SPLIT, int kTL>
 __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     extern __shared__ double shd[];
@@ -714,7 +719,8 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     };
     // E and O: x[m] +- x[N-1-m], or (inverse) the even and odd modes.  Loads
     // at clamped places, four pairs in flight per thread.
-    bool negative = false, within = true;
+    float least = 0.f;
+    uint32_t most = 0u;
     auto fill = [&](const auto* __restrict__ src, int64_t step, int m0, int dm, int line, bool ok) {
         for (int m = m0; m < rows; m += 4 * dm) {
             std::remove_cv_t<std::remove_reference_t<decltype(*src)>> u[4], w[4];
@@ -726,11 +732,11 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
             }
             if (MODE == 0 && XK) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) negative = negative || (ok && (u[i] < 0 || w[i] < 0));
+                for (int i = 0; i < 4; ++i) least = fminf(least, fminf(u[i], w[i]));  // (!ok: some of the box)
             }
             if (MODE == 2) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) within = within && (!ok || (carried(u[i]) && carried(w[i])));
+                for (int i = 0; i < 4; ++i) most = max(most, ok ? max(upper(u[i]), upper(w[i])) : 0u);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -749,12 +755,12 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
             if constexpr (MODE == 0) fill(in + (ok ? base_of(l0 + line, true) : a.off), 1, lane, 64, line, ok);
             else fill(W + (ok ? base_of(l0 + line, false) : 0), 1, lane, 64, line, ok);
         }
-        if (MODE == 0) mark_negative(a, negative);
+        if (MODE == 0) mark_negative(a, least);
     } else {
         const int line = threadIdx.x % kTL;
         const bool ok = l0 + line < a.lines;
         fill(W + (ok ? base_of(l0 + line, false) : 0), es, threadIdx.x / kTL, nw * 64 / kTL, line, ok);
-        if (MODE == 2 && !within) mark_bad(a);
+        if (MODE == 2 && most >= kBeyond) mark_bad(a);
     }
     __syncthreads();
     v4d ae[CT], ao[CT];
@@ -843,7 +849,7 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
     }
     multiply(a.ie, a.io);
     const float cut = XK ? cut_of(a) : 0.f;
-    double big = 0.0;
+    uint32_t top = 0u;
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
 #pragma unroll
@@ -860,11 +866,11 @@ __global__ __launch_bounds__(1024) void k_dense(SpecPass a) {
                 double* dst = W + base_of(l0 + line, false);
                 dst[es * m] = p;
                 if (m < ho) dst[es * (n - 1 - m)] = q;
-                big = fmax(big, fmax(fabs(p), m < ho ? fabs(q) : 0.0));
+                top = max(top, max(upper(p), m < ho ? upper(q) : 0u));
             }
         }
     }
-    if (MODE == 2) note_top(a, big);
+    if (MODE == 2) note_top(a, top);
 }
 
 // ------------------------------------------------------------------ tables
