@@ -264,7 +264,7 @@ def diffuse(mesh: Mesh, field, bandwidth, n_steps, rtol=1e-6, max_iter=1000, x0_
     """Diffuses field [F, cells] in place for T = bandwidth^2 / 4 in n_steps
     backward-Euler ("be") or Crank-Nicolson ("cn") steps.  x0_mode 3 seeds
     every step with model(e^n) (a UNet made for this mesh's grid).  Returns
-    (field, Stats or None)."""
+    (field, Stats or None); stats as in coarse_grain."""
     torch = _torch()
     lib = _abi.load()
     F = int(field.shape[0])
@@ -282,7 +282,10 @@ def diffuse(mesh: Mesh, field, bandwidth, n_steps, rtol=1e-6, max_iter=1000, x0_
 def coarse_grain(mesh: Mesh, pos, values, bandwidth, n_steps, rtol=1e-6, max_iter=1000, x0_mode=0,
                  check_every=4, field=None, stats=False, stream=None, model=None, precond=0, scheme="be"):
     """The whole method (Section 2.6): PCM deposition, then diffusion.
-    Returns (field [F, cells], Stats or None)."""
+    Returns (field [F, cells], Stats or None).  With stats the CG solves, whose
+    iterations and residuals they hold; without, the direct solve where it
+    applies (include/cgd.h, cgd_diffuse): the two agree within the CG's
+    tolerance, not bit for bit."""
     torch = _torch()
     lib = _abi.load()
     n = int(pos.shape[0])
