@@ -1137,7 +1137,12 @@ static const SpecTables* grid_of(cgd_mesh m) {
     if (!m->spec) {
         SpecTables* t = new (std::nothrow) SpecTables();
         if (!t) return nullptr;
-        analyse_grid(m, t);
+        try {
+            analyse_grid(m, t);
+        } catch (const std::bad_alloc&) {
+            delete t;
+            return nullptr;
+        }
         m->spec = t;
     }
     return m->spec;
@@ -1163,6 +1168,7 @@ static bool modes_found(SpecTables* t) {
             if (t->eigen[a] && t->modes[a].lam.empty())
                 t->ok = axis_modes(t->h[a], t->sym[a], t->per[a], t->modes[a].rot, t->modes[a].lam);
     } catch (const std::bad_alloc&) {
+        for (AxisModes& mo : t->modes) mo = AxisModes();  // (half an axis is no axis: the next call starts again)
         return false;
     }
     return t->ok;
